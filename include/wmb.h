@@ -261,8 +261,9 @@ int wmb_autotune(wmb_ctx *c, int32_t reps, int32_t *chosen, int32_t nchosen);
    one zone ahead).  Groups not named keep their shape.  WMB_EINVAL if a
    pencil shape exceeds 1024 threads or 64 KiB of LDS, or a marching shape
    is asked for x or beyond 256.  Invalidates the captured graphs.  The
-   defaults are the marching form (64 pencils a block) for the y and z
-   sweeps in FP32 and the pencil form elsewhere.  Tile entries: (3, 0, 0, w)
+   defaults follow from the patch extents and counts: the pencil form with
+   the width that keeps the most threads resident, and in FP32 the marching
+   form for the y and z sweeps of large batches.  Tile entries: (3, 0, 0, w)
    sets the widest Steps 3-4 tile along x to w zones (4..40, default 40);
    (4, 0, 0, z) the zones of a Steps 8-11 tile plane (256, or 512 in FP32;
    the default is the one that leaves fewer threads idle); (5, 0, 0, m) the

@@ -1963,6 +1963,23 @@ hipError_t launch_ct_half(void* pool, const PatchDev* pt, const WorkItem* wk, in
     return hipGetLastError();
 }
 
+// blocks of a kernel that the current device holds at once (0: not known)
+template <typename K>
+int resident_blocks(K kernel, int threads) {
+    int dev = 0, per_cu = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, threads, 0) != hipSuccess) {
+        (void)hipGetLastError();  // planning only: the caller plans without it
+        return 0;
+    }
+    return per_cu * cus;
+}
+template <typename R>
+int ct_half_resident() { return resident_blocks(ct_half_kernel<R>, TILE_THREADS); }
+template <typename R>
+int update_resident(int threads) { return resident_blocks(update_kernel<R, false>, threads); }
+
 // queue != nullptr: the persistent form, with as many blocks as are
 // resident at once (a multiple of 8), over a list of nblk items (a multiple
 // of 8, as xcd_order pads it); queue holds 9 counters, zero between launches
@@ -2134,6 +2151,8 @@ hipError_t launch_diag(const void* pool, const PatchDev* pt, const WorkItem* wk,
     template hipError_t launch_corr_xy<R>(void*, const PatchDev*, const WorkItem*, int, const DevParams&,           \
                                           const Coef<R>&, int, const StepConst*, int, int, unsigned long long*,         \
                                           hipStream_t);                                                                  \
+    template int ct_half_resident<R>();                                                                                 \
+    template int update_resident<R>(int);                                                                               \
     template hipError_t launch_diag<R>(const void*, const PatchDev*, const WorkItem*, int, const DevParams&, int,        \
                                        double*, const unsigned long long*, double, double, double*, hipStream_t);
 WMB_INST(float)

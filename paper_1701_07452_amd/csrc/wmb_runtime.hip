@@ -7,7 +7,9 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <mutex>
+#include <queue>
 #include <string>
 #include <vector>
 
@@ -25,6 +27,8 @@ template <typename R> hipError_t launch_update(void*, const PatchDev*, const Wor
 template <typename R> hipError_t launch_sweep(int, int, void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, int, int, int, unsigned long long*, hipStream_t);
 template <typename R> hipError_t launch_corr_xy(void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, int, int, unsigned long long*, hipStream_t);
 template <typename R> hipError_t launch_march(int, int, void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, int, int, int, unsigned long long*, hipStream_t);
+template <typename R> int ct_half_resident();
+template <typename R> int update_resident(int);
 template <typename R> hipError_t launch_diag(const void*, const PatchDev*, const WorkItem*, int, const DevParams&, int, double*, const unsigned long long*, double, double, double*, hipStream_t);
 }  // namespace wmb
 
@@ -202,43 +206,77 @@ void release(wmb_ctx* c, void* p) {
 // neither the patch numbering nor uneven patch sizes leave XCDs idle); each
 // queue takes its units largest first.  Queues are padded with empty items
 // (patch = -1) that exit at once.
+//
+// A batch of few units leaves XCDs idle that way (one patch would run on one
+// XCD, an eighth of the chip): where the fullest XCD would hold over 1.08
+// times the mean, units above a 64th of the list are cut into contiguous
+// pieces of that size, which are then placed on their own.  Batches of about
+// 100 even units or more keep whole units.
 constexpr int NXCD = 8;
 std::vector<WorkItem> xcd_order(const std::vector<WorkItem>& items, const std::vector<int>* group = nullptr,
                                 bool tiles = false) {
-    // work and first appearance of every unit in the list
-    std::vector<int> slot;  // unit -> index in order
+    auto weight = [&](const WorkItem& w) -> long long {
+        return tiles ? (long long)(w.b & 0xffff) * (w.b >> 16) * ((w.c >> 16) - (w.c & 0xffff)) : 1;
+    };
+    // units in the order of their first appearance, and their work
+    std::vector<int> slot, unit(items.size());
     std::vector<long long> work;
-    std::vector<std::vector<WorkItem>> per;
-    for (const WorkItem& w : items) {
-        const int u = group ? (*group)[w.patch] : w.patch;
+    long long total = 0;
+    for (size_t i = 0; i < items.size(); i++) {
+        const int u = group ? (*group)[items[i].patch] : items[i].patch;
         if (u >= (int)slot.size()) slot.resize(u + 1, -1);
-        if (slot[u] < 0) {
-            slot[u] = (int)per.size();
-            per.emplace_back();
-            work.push_back(0);
+        if (slot[u] < 0) slot[u] = (int)work.size(), work.push_back(0);
+        unit[i] = slot[u];
+        work[unit[i]] += weight(items[i]);
+        total += weight(items[i]);
+    }
+    // units to XCDs, largest first; the order they were placed in and each one's XCD
+    std::vector<int> byload, xcd;
+    auto place = [&]() -> long long {
+        byload.resize(work.size());
+        xcd.resize(work.size());
+        for (size_t i = 0; i < byload.size(); i++) byload[i] = (int)i;
+        std::stable_sort(byload.begin(), byload.end(), [&](int a, int b) { return work[a] > work[b]; });
+        long long load[NXCD] = {0};
+        for (int i : byload) {
+            int best = 0;
+            for (int x = 1; x < NXCD; x++)
+                if (load[x] < load[best]) best = x;
+            load[best] += work[i];
+            xcd[i] = best;
         }
-        const long long wt = tiles ? (long long)(w.b & 0xffff) * (w.b >> 16) * ((w.c >> 16) - (w.c & 0xffff)) : 1;
-        work[slot[u]] += wt;
-        per[slot[u]].push_back(w);
+        return *std::max_element(load, load + NXCD);
+    };
+    if (place() * NXCD * 100 > total * 108) {
+        const long long piece = std::max<long long>(1, total / (8 * NXCD));
+        std::vector<long long> whole = work, done(work.size(), 0);
+        std::vector<int> first(work.size(), -1), last(work.size(), -1);
+        work.clear();
+        for (size_t i = 0; i < items.size(); i++) {
+            const int u = unit[i];
+            const long long np = (whole[u] + piece - 1) / piece;
+            const int k = (int)(done[u] * np / whole[u]);  // the piece this item starts in
+            if (last[u] != k) last[u] = k, first[u] = (int)work.size(), work.push_back(0);
+            unit[i] = first[u];
+            work[unit[i]] += weight(items[i]);
+            done[u] += weight(items[i]);
+        }
+        place();
     }
-    std::vector<int> byload(per.size());
-    for (size_t i = 0; i < byload.size(); i++) byload[i] = (int)i;
-    std::stable_sort(byload.begin(), byload.end(), [&](int a, int b) { return work[a] > work[b]; });
-    long long load[NXCD] = {0};
-    std::vector<std::vector<WorkItem>> q(NXCD);
-    for (int i : byload) {
-        int best = 0;
-        for (int x = 1; x < NXCD; x++)
-            if (load[x] < load[best]) best = x;
-        load[best] += work[i];
-        for (const WorkItem& w : per[i]) q[best].push_back(w);
-    }
-    size_t len = 0;
-    for (auto& v : q) len = v.size() > len ? v.size() : len;
-    std::vector<WorkItem> out;
-    out.reserve(len * NXCD);
-    for (size_t j = 0; j < len; j++)
-        for (int x = 0; x < NXCD; x++) out.push_back(j < q[x].size() ? q[x][j] : WorkItem{-1, 0, 0, 0});
+    // each XCD's queue: its units in the order they were placed, a unit's items in theirs
+    std::vector<int> start(work.size() + 1, 0), at(work.size());
+    for (int u : unit) start[u + 1]++;
+    for (size_t u = 0; u < work.size(); u++) start[u + 1] += start[u];
+    std::copy(start.begin(), start.end() - 1, at.begin());
+    std::vector<int> byunit(items.size());
+    for (size_t i = 0; i < items.size(); i++) byunit[at[unit[i]]++] = (int)i;
+    size_t len[NXCD] = {0}, most = 0;
+    for (size_t u = 0; u < work.size(); u++) len[xcd[u]] += start[u + 1] - start[u];
+    for (int x = 0; x < NXCD; x++) most = std::max(most, len[x]);
+    std::vector<WorkItem> out(most * NXCD, WorkItem{-1, 0, 0, 0});
+    size_t pos[NXCD] = {0};
+    for (int u : byload)
+        for (int i = start[u]; i < start[u + 1]; i++) out[NXCD * pos[xcd[u]]++ + xcd[u]] = items[byunit[i]];
     return out;
 }
 
@@ -739,8 +777,53 @@ int build_diag_list(wmb_ctx* c) {
 // rows cut no cache lines), then along y into parts with at most maxz zones
 // per tile plane and 32 per edge.  Item fields (origins biased by 16, they
 // may be negative): a = i0 | j0 << 16, b = tx | ty << 16, c = k0 | k1 << 16
-// with k1 exclusive.
+// with k1 exclusive.  zlen: the planes are cut into near-equal chunks of at
+// most zlen, one item each (0: as plan_zlen finds best).
 constexpr int TILE_BIAS = 16;
+
+// Planes a block of a marching tile kernel takes.  A block walks its planes
+// one after another (about 7 us a plane in FP64 Steps 8-11, 4 us in Steps
+// 3-4), and with few patches there are fewer blocks than the chip holds, so
+// the planes are cut into chunks, each with about two planes more of
+// prologue.  The chunk length is the one whose blocks (tiles[p] columns of
+// ez[p] planes) finish first when `cap` run at a time in list order.  Batches
+// of more than 4 cap blocks are not cut: measured at 256^3 FP32 (1024 blocks,
+// cap 512) Steps 8-11 take 1.20 ms whole, 1.21 in two, 1.32 in four chunks;
+// one 32^3 FP64 patch 240 us whole, 39 in chunks of two; 64 patches of 48^3
+// FP32 (320 blocks) 651 whole, 513 in three.
+int plan_zlen(const std::vector<int>& tiles, const std::vector<int>& ez, int cap) {
+    long long blocks = 0;
+    int emax = 0;
+    for (size_t p = 0; p < ez.size(); p++) blocks += tiles[p], emax = std::max(emax, ez[p]);
+    if (cap < 1 || blocks > 4LL * cap || emax < 2) return std::max(emax, 1);
+    int best = emax;
+    long long best_t = -1;
+    for (int m = 1, last = 0; m <= emax; m++) {
+        const int zlen = (emax + m - 1) / m;
+        if (zlen == last) continue;
+        last = zlen;
+        if (zlen < 2) break;
+        std::vector<int> len;
+        for (size_t p = 0; p < ez.size(); p++) {
+            const int mz = (ez[p] + zlen - 1) / zlen;
+            for (int t = 0; t < tiles[p]; t++)
+                for (int b = 0; b < mz; b++)
+                    len.push_back((int)((long long)ez[p] * (b + 1) / mz - (long long)ez[p] * b / mz) + 2);
+        }
+        std::sort(len.rbegin(), len.rend());
+        std::priority_queue<long long, std::vector<long long>, std::greater<long long>> busy;
+        long long t = 0;
+        for (int l : len) {
+            long long at = 0;
+            if ((int)busy.size() == cap) at = busy.top(), busy.pop();
+            busy.push(at + l);
+            t = std::max(t, at + l);
+        }
+        if (best_t < 0 || t < best_t) best_t = t, best = zlen;
+        if ((long long)len.size() > 8LL * cap) break;  // more chunks only add prologues
+    }
+    return best;
+}
 // x-rows: patches linked by their x face neighbours (a periodic ring or a
 // chain between domain boundaries), numbered by their smallest patch id;
 // the unit of xcd_order for the update and the ghost exchange
@@ -752,10 +835,15 @@ std::vector<int> x_rows(const wmb_ctx* c) { return rows_of(c->npatch, c->desc.da
 bool in_plan(const wmb_ctx* c, int p) { return c->hpatch[p].present && c->hpatch[p].active; }
 
 std::vector<WorkItem> tile_items(const wmb_ctx* c, int lo, int hi, int zlo, int zhi, int txmax_allowed, int maxz,
-                                 const std::vector<int>* group, int sgroup = -1, int ermax = 0, int edmax = 0) {
+                                 const std::vector<int>* group, int cap, int sgroup = -1, int ermax = 0,
+                                 int edmax = 0) {
     std::vector<WorkItem> items;
+    struct Cut {
+        int ex, ey, mx, my;
+    };
+    std::vector<Cut> cuts;
+    std::vector<int> tiles, ez;
     for (int p = 0; p < c->npatch; p++) {
-        if (!in_plan(c, p) || (sgroup >= 0 && c->pgroup[p] != sgroup)) continue;
         const int* n = c->desc[p].n;
         const int ex = n[0] + hi - lo + 1, ey = n[1] + hi - lo + 1;
         const int mx = (ex + txmax_allowed - 1) / txmax_allowed;
@@ -766,22 +854,43 @@ std::vector<WorkItem> tile_items(const wmb_ctx* c, int lo, int hi, int zlo, int 
         if (ermax > 0) tymax = std::min(tymax, ermax / (txmax + 2) - 2);
         if (edmax > 0) tymax = std::min(tymax, edmax / (txmax + 1) - 1);
         const int my = (ey + tymax - 1) / tymax;
-        const int k0 = zlo + TILE_BIAS, k1 = n[2] + zhi + 1 + TILE_BIAS;
-        for (int by = 0; by < my; by++) {
-            const int j0 = lo + (int)((long long)ey * by / my), j1 = lo + (int)((long long)ey * (by + 1) / my);
-            for (int bx = 0; bx < mx; bx++) {
-                const int i0 = lo + (int)((long long)ex * bx / mx), i1 = lo + (int)((long long)ex * (bx + 1) / mx);
-                items.push_back(WorkItem{p, (i0 + TILE_BIAS) | ((j0 + TILE_BIAS) << 16), (i1 - i0) | ((j1 - j0) << 16),
-                                         k0 | (k1 << 16)});
+        cuts.push_back({ex, ey, mx, my});
+        if (sgroup >= 0 && c->pgroup[p] != sgroup) continue;
+        tiles.push_back(mx * my);  // frozen and absent ones too: the chunks do not depend on the plan
+        ez.push_back(n[2] + zhi + 1 - zlo);
+    }
+    const int zlen = plan_zlen(tiles, ez, cap);
+    for (int p = 0; p < c->npatch; p++) {
+        if (!in_plan(c, p) || (sgroup >= 0 && c->pgroup[p] != sgroup)) continue;
+        const Cut& q = cuts[p];
+        const int e = c->desc[p].n[2] + zhi + 1 - zlo, mz = (e + zlen - 1) / zlen;
+        for (int bz = 0; bz < mz; bz++) {
+            const int k0 = zlo + (int)((long long)e * bz / mz) + TILE_BIAS;
+            const int k1 = zlo + (int)((long long)e * (bz + 1) / mz) + TILE_BIAS;
+            for (int by = 0; by < q.my; by++) {
+                const int j0 = lo + (int)((long long)q.ey * by / q.my), j1 = lo + (int)((long long)q.ey * (by + 1) / q.my);
+                for (int bx = 0; bx < q.mx; bx++) {
+                    const int i0 = lo + (int)((long long)q.ex * bx / q.mx), i1 = lo + (int)((long long)q.ex * (bx + 1) / q.mx);
+                    items.push_back(WorkItem{p, (i0 + TILE_BIAS) | ((j0 + TILE_BIAS) << 16),
+                                             (i1 - i0) | ((j1 - j0) << 16), k0 | (k1 << 16)});
+                }
             }
         }
     }
     return xcd_order(items, group, true);
 }
 
-int build_tile_list(wmb_ctx* c, int lo, int hi, int zlo, int zhi, int txmax_allowed, int maxz,
-                    const std::vector<int>* group, DevList& out, int sgroup = -1, int ermax = 0, int edmax = 0) {
-    std::vector<WorkItem> items = tile_items(c, lo, hi, zlo, zhi, txmax_allowed, maxz, group, sgroup, ermax, edmax);
+// blocks of Steps 3-4 and of Steps 8-11 (tile planes of Z zones) the chip holds at once
+int cth_cap(const wmb_ctx* c) { return c->esize == 4 ? ct_half_resident<float>() : ct_half_resident<double>(); }
+int upd_cap(const wmb_ctx* c, int Z) { return c->esize == 4 ? update_resident<float>(Z) : update_resident<double>(Z); }
+
+// The Steps 3-4 tiles, at most tx zones wide along x and 256 a plane
+std::vector<WorkItem> cth_items(const wmb_ctx* c, int tx, int sgroup = -1) {
+    return tile_items(c, -2, 2, -2, 2, tx, 256, nullptr, cth_cap(c), sgroup);
+}
+
+int build_cth_list(wmb_ctx* c, int tx, DevList& out, int sgroup = -1) {
+    std::vector<WorkItem> items = cth_items(c, tx, sgroup);
     out.n = (int)items.size();
     return upload(c, &out.d, items);
 }
@@ -793,7 +902,7 @@ int build_tile_list(wmb_ctx* c, int lo, int hi, int zlo, int zhi, int txmax_allo
 int upd_txmax(int Z) { return Z > 256 ? 48 : 32; }
 std::vector<WorkItem> upd_items(const wmb_ctx* c, int Z, const std::vector<int>* rows, int sgroup = -1) {
     const int es = (int)c->esize;
-    return tile_items(c, 0, -1, 0, -1, upd_txmax(Z), Z, rows, sgroup, upd_er_plane(es), upd_ed_plane(es));
+    return tile_items(c, 0, -1, 0, -1, upd_txmax(Z), Z, rows, upd_cap(c, Z), sgroup, upd_er_plane(es), upd_ed_plane(es));
 }
 int build_upd_list(wmb_ctx* c, int Z, const std::vector<int>* rows, DevList& out, int sgroup = -1) {
     std::vector<WorkItem> items = upd_items(c, Z, rows, sgroup);
@@ -845,7 +954,7 @@ int build_ct_update_lists(wmb_ctx* c) {
         *L = DevList{};
     }
     const std::vector<int> rows = x_rows(c);
-    int rc = build_tile_list(c, -2, 2, -2, 2, c->cth_tx, 256, nullptr, c->wl_cth);
+    int rc = build_cth_list(c, c->cth_tx, c->wl_cth);
     if (!rc) rc = build_upd_list(c, c->upd_zones, &rows, c->wl_upd);
     if (c->ngroups > 1 && c->wl_cth_g.size() < (size_t)c->ngroups) {
         c->wl_cth_g.resize(c->ngroups);
@@ -856,7 +965,7 @@ int build_ct_update_lists(wmb_ctx* c) {
             release(c, L->d);
             *L = DevList{};
         }
-        rc = build_tile_list(c, -2, 2, -2, 2, c->cth_tx, 256, nullptr, c->wl_cth_g[g], g);
+        rc = build_cth_list(c, c->cth_tx, c->wl_cth_g[g], g);
         if (!rc) rc = build_upd_list(c, c->upd_zones, &rows, c->wl_upd_g[g], g);
     }
     return rc;
@@ -889,31 +998,46 @@ int build_fill_lists(wmb_ctx* c) {
     return WMB_OK;
 }
 
-int choose_W(int d, int P, size_t es) {
-    // y and z in FP32: the marching form (coalesced, no barrier; about 120
-    // VGPRs, 4 waves a SIMD); in FP64 it needs 256 VGPRs and the pencil form
-    // is kept
-    if (d != 0 && es == 4) return -64;
-    if (d == 0) {
-        // about 256 threads a block, packed into whole 64-lane waves: the
-        // pencil count whose P * W wastes the fewest lanes, nearest to 256
-        int best = 256 / P < 1 ? 1 : 256 / P;
-        double bs = -1.0;
-        for (int W = 1; (size_t)P * W <= 1024 && es * 16 * (size_t)P * W <= 64 * 1024; W++) {
-            const int t = P * W;
-            if (t < 128 && (size_t)P * (W + 1) <= 1024) continue;
-            const double fill = (double)t / (double)((t + 63) / 64 * 64);
-            const double score = fill - 0.02 * (t > 256 ? t - 256 : 256 - t) / 64.0;
-            if (score > bs) {
-                bs = score;
-                best = W;
-            }
-        }
-        return best;
+// Default shape of the sweeps along d with pencils of P zones, npen pencils in
+// the batch (stage 0: Step 1, 1: the corrector, which along z in FP32 reads
+// the stored records).
+//   Marching form: one wave holds 64 pencils, so it needs waves for every
+// SIMD.  In FP32 the z corrector from records takes it from 2048 waves on
+// (two a SIMD: 146 against 169 us at 64 x 48^3, 385 against 434 at 512 x
+// 32^3, but 133 against 63 on 36 uneven patches of 870 waves), the Step-1
+// sweeps from 4096 waves of pencils of 60 zones on (483 against 506 us at 64
+// x 64^3, but 698 against 640 at 512 x 32^3).  In FP64 (256 VGPRs) the pencil
+// form below is as fast or faster (y corrector at 512 x 32^3 1.94 against
+// 2.08 ms).
+//   Pencil form: W so that the most threads are resident.  A block's waves
+// are dealt to the 4 SIMDs, so a block of 5 waves takes the room of 8: at
+// 512 x 32^3 in FP64 (4 waves a SIMD) the x sweep of 6 pencils (240 threads)
+// takes 1.40 ms, of 8 (320) 1.81; in FP32 (8 waves a SIMD) the y sweep of 12
+// pencils 0.64, of 10 0.69.  Along y and z a wave reads W consecutive zones
+// a row, so a larger W wins at equal residency (FP64 y corrector 1.94 ms at
+// 12, 2.17 at 6).  Fewer blocks than CUs halve the gain.
+int choose_W(int d, int P, size_t es, int stage, long long npen, bool prot) {
+    const long long waves = npen / 64;
+    if (d != 0 && es == 4) {
+        if (d == 2 && stage == 1 ? waves >= 2048 : (waves >= 4096 && P >= 60)) return d == 2 && stage == 1 ? -256 : -64;
     }
-    int W = 16;
-    while (W > 1 && ((size_t)P * W > 1024 || es * 16 * (size_t)P * W > 64 * 1024)) W /= 2;
-    return W;
+    const int simd = es == 4 ? (prot ? 7 : 8) : 4;  // waves a SIMD the registers allow
+    int best = 1;
+    double bs = -1.0;
+    for (int W = 1; (size_t)P * W <= 1024 && es * 16 * (size_t)P * W <= 64 * 1024; W++) {
+        const int t = P * W, w = (t + 63) / 64;
+        const size_t lds = es * 16 * (size_t)t;
+        int res = w <= 4 ? 4 * simd / w : simd / ((w + 3) / 4);
+        res = std::min(res, (int)(160 * 1024 / lds));
+        double score = (double)res * t;
+        score *= 1.0 - t / 4096.0;  // at equal residency smaller blocks wait less at their barriers
+        if (d != 0) score *= W / (W + 2.0);
+        const double blocks = (double)((npen + W - 1) / W);
+        if (blocks < 256.0) score *= 0.5 + blocks / 512.0;
+        if (t < 64) score *= 0.5;
+        if (score > bs * 1.0001) bs = score, best = W;
+    }
+    return best;
 }
 
 // Which pencils of the transverse range [tlo, n+thi]^2 a list covers: all, the
@@ -1068,6 +1192,7 @@ int set_xy(wmb_ctx* c, int rb) {
 }
 
 int build_sweeps(wmb_ctx* c) {
+    const bool prot = c->p.rho_protect > 0.0 || c->p.p_protect > 0.0;
     for (int d = 0; d < 3; d++) {
         for (int stage = 0; stage < 2; stage++) {
             const int zlo = stage == 0 ? -4 : -3;
@@ -1088,7 +1213,12 @@ int build_sweeps(wmb_ctx* c) {
                 G.tlo = tlo;
                 G.thi = thi;
                 G.n = n;
-                int rc = set_group_W(c, d, stage, G, choose_W(d, G.P, c->esize));
+                long long npen = 0;
+                for (int p = 0; p < c->npatch; p++)
+                    if (c->desc[p].n[d] == n)
+                        npen += (long long)(c->desc[p].n[(d + 1) % 3] + thi - tlo + 1) *
+                                (c->desc[p].n[(d + 2) % 3] + thi - tlo + 1);
+                int rc = set_group_W(c, d, stage, G, choose_W(d, G.P, c->esize, stage, npen, prot));
                 if (rc) return rc;
                 c->sweeps[d][stage].push_back(G);
             }
@@ -1157,10 +1287,10 @@ int replan(wmb_ctx* c) {
             rc = put(G.wxyg[g], xy_items(c, G.n, c->xy_rows, g));
     }
     const std::vector<int> rows = x_rows(c);
-    if (!rc) rc = put(c->wl_cth, tile_items(c, -2, 2, -2, 2, c->cth_tx, 256, nullptr));
+    if (!rc) rc = put(c->wl_cth, cth_items(c, c->cth_tx));
     if (!rc) rc = put(c->wl_upd, upd_items(c, c->upd_zones, &rows));
     for (int g = 0; g < c->ngroups && c->ngroups > 1 && !rc; g++) {
-        rc = put(c->wl_cth_g[g], tile_items(c, -2, 2, -2, 2, c->cth_tx, 256, nullptr, g));
+        rc = put(c->wl_cth_g[g], cth_items(c, c->cth_tx, g));
         if (!rc) rc = put(c->wl_upd_g[g], upd_items(c, c->upd_zones, &rows, g));
     }
     if (regrid) free_graphs(c);
@@ -1626,7 +1756,7 @@ int autotune_t(wmb_ctx* c, int reps) {
         auto time_tiles = [&](int kind, int v, float* ms) -> int {
             DevList L;
             // kind 0: Steps 3-4; 1: Steps 8-11, one block a tile; 2: the same on the queues
-            int rc3 = kind == 0 ? build_tile_list(c, -2, 2, -2, 2, v, 256, nullptr, L)
+            int rc3 = kind == 0 ? build_cth_list(c, v, L)
                                 : build_upd_list(c, v, &rows, L);
             if (rc3) return cleanup(rc3);
             tl = L.d;  // released by cleanup on an error exit

@@ -202,3 +202,42 @@ def test_diagnostics_parity(wmb, prec):
         assert dng < 1e-13
     sim.close()
     orc.close()
+
+
+# batches of few patches, whose marching blocks are cut into chunks of planes
+# and whose blocks are spread over the XCDs in pieces of a patch
+FEW = {
+    "one": ([33], [9], [40]),           # one patch, chunks of two planes
+    "thin": ([16, 48], [8], [5]),       # fewer planes than a chunk and its prologue
+    "uneven_z": ([12], [40], [7, 40, 19]),
+}
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("grid", sorted(FEW))
+def test_few_patches(wmb, grid, prec):
+    """Three steps of one to three patches against the oracle, FP64 within
+    1e-11 of each field's scale, FP32 within 1e-5 relative L1 (the parity
+    bars of the batches)."""
+    G = I.patch_grid(*FEW[grid])
+    N = G.shape
+    dx = (1.0 / max(N),) * 3
+    q, b = I.random_smooth(N, 21, dx=dx)
+    if prec == 1:
+        q, b = as_f32(q), as_f32(b)
+    sim = gpu_sim(wmb, G, q, b, prec, dx=dx)
+    orc = oracle_sim(G, q, b, dx=dx)
+    for _ in range(3):
+        dt = sim.compute_dt()
+        sim.run_steps(1)
+        orc.fill_ghosts()
+        orc.advance(dt)
+    qg, bg = I.gather(G, [sim.get_state(i) for i in range(G.npatch)])
+    qo, bo = oracle_gather(G, orc)
+    for c in range(8):
+        if prec == 0:
+            assert rel_max(qg[c], qo[c]) < 1e-11, (c, rel_max(qg[c], qo[c]))
+        elif c in (0, 7):
+            assert _rel_l1(qg[c], qo[c]) < 1e-5, c
+    sim.close()
+    orc.close()
