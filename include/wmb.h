@@ -169,7 +169,11 @@ int wmb_compute_dt(wmb_ctx *c, double *dt_out);
    x part of the next ghost exchange; at a domain boundary the patch's own
    x-ghosts by zero gradient; next to a frozen neighbour it copies that
    neighbour's zones into its own x-ghosts instead); other ghosts are left to
-   wmb_fill_ghosts.  Frozen patches are not advanced. */
+   wmb_fill_ghosts.  Frozen patches are not advanced.  Shared-halo steps, of
+   batches whose patches all have one size, all 26 neighbours, and are all
+   active (and no scratch groups): a lane whose zone lies beyond its patch
+   reads the neighbour's own zone, no face or edge is computed twice, and the
+   step writes no ghosts (wmb_get_stored and wmb_fill_ghosts form them). */
 int wmb_advance(wmb_ctx *c, double dt);
 
 /* nsteps x (fill ghosts, compute dt, advance) with dt kept on the device,
@@ -181,7 +185,8 @@ int wmb_advance(wmb_ctx *c, double dt);
    run as concurrent branches (library-owned streams, default priority),
    except that the fused corrector is followed by the z sweep that reads its
    records; the
-   x pass is enqueued first when the state was set since.  Results are
+   x pass is enqueued first when the state was set since.  Shared-halo steps
+   have no exchange, and their graph is one chain.  Results are
    bitwise those of the eager calls.  Enqueue only; this is the timed call. */
 int wmb_run_steps(wmb_ctx *c, int32_t nsteps);
 
@@ -189,8 +194,9 @@ int wmb_run_steps(wmb_ctx *c, int32_t nsteps);
    the zone volume; max_divb_raw = max |div b| with div b = sum_d (b_d(+) -
    b_d(-)) / dx_d; max_divb_norm = max_divb_raw * min(dx) / B_rms; n_floored =
    floor activations since wmb_init_patches; n_protected = faces that took the
-   HLL flux since wmb_init_patches (every computed face of every stage,
-   including faces in the ghost halo).  Any output pointer may be NULL. */
+   HLL flux since wmb_init_patches (every face of every stage, once for each
+   patch whose update reads it through its ghost halo, also where a
+   shared-halo step computes it once).  Any output pointer may be NULL. */
 int wmb_diagnostics(wmb_ctx *c, double totals[8], double *max_divb_norm, double *max_divb_raw,
                     int64_t *n_floored, int64_t *n_protected);
 
@@ -216,7 +222,8 @@ int wmb_diagnostics_noalloc(wmb_ctx *c, double *dev_out);
    5 Step-6/7 fluxes (3 x 8 x vol), 6 Step-9 edge EMFs (3 x vol; only after
    a step run with wmb_keep_stages on, else WMB_ESTATE).  Values outside the
    ranges the step needs are unspecified; with scratch groups only the
-   patches of the last group hold their own.  Other stages (the Step-3 edges are
+   patches of the last group hold their own.  After a shared-halo step the
+   ranges of the ghosts are formed again first, from the step's start.  Other stages (the Step-3 edges are
    overwritten by Step 9) give WMB_EINVAL.  Synchronous. */
 int wmb_debug_stage(wmb_ctx *c, int32_t patch, int32_t stage, double *out);
 
@@ -232,7 +239,7 @@ int wmb_debug_stage(wmb_ctx *c, int32_t patch, int32_t stage, double *out);
    registers, half the waves).  The choice never
    changes results (both forms compute every face with the same
    arithmetic).  It then times whole graph-replayed steps with the x and y
-   correctors fused into one launch (bands of 6, 9, 12 or 18 rows, where
+   correctors fused into one launch (bands of 4 to 18 rows, where
    the blocks fit, each with three shapes of the z corrector that reads the
    records it stores) against the separate sweeps, and the tiles of Steps 3-4
    (the widest tile along x: 40, 20 or 13 zones, 256 zones a plane) and of

@@ -88,6 +88,25 @@ struct WorkItem {
     int c;  // sweeps: last pencil (inclusive); tiles: k0 | k1 << 16 (biased, k1 exclusive)
 };
 
+// Shared-halo steps: the neighbour table, NBR_ROW words a patch.  For the
+// state regions: the pool word of the zone that (0, 0, 0) of the patch's frame
+// would be in the neighbour on each side (index 9 sz + 3 sy + sx with 0 below,
+// 1 inside, 2 above), then the first word of the patches at each z (below,
+// own, above), from which the nine lie within 4 GiB; from NBR_SCR on the same
+// for the step intermediates.  nbr == nullptr: the halo scheme.
+struct SharedHalo {
+    const unsigned* nbr;
+};
+constexpr int NBR_ROW = 64, NBR_SCR = 32;
+
+// Layout of the intermediates in shared-halo steps: fields of the patch's own
+// n_x n_y n_z zones, without ghosts, so that the rows of a 16-, 32- or 64-zone
+// patch are whole cache lines; the field stride (words) is a multiple of 32
+// words plus three, so that the fields of a zone spread over the memory channels.
+__host__ __device__ constexpr unsigned scratch_stride(int nx, int ny, int nz) {
+    return (((unsigned)nx * ny * nz + 31u) & ~31u) + 96u;
+}
+
 // Fused x/y corrector items (one z-plane band of a patch): a = k + XY_BIAS,
 // b = (y0 + XY_BIAS) | (y1 + XY_BIAS) << 16 for the band's y-face rows
 // [y0, y1) (plane k and rows may be -1).

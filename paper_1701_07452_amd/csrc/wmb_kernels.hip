@@ -125,12 +125,113 @@ __device__ __forceinline__ void bstore(double v, __amdgpu_buffer_rsrc_t r, unsig
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)voff, (int)soff, 0);
 }
 
+// Shared-halo addressing (SH kernels).  The patches of the batch have the same
+// extents, so a field lies at the same offset from every patch's zone, and a
+// zone of the patch or of a neighbour is named by its own place alone:
+//   by its byte offset in the patch's z-layer (the nine patches around a
+//   patch at the same z, which lie within 4 GiB), read through that layer's
+//   buffer descriptor, one VGPR and no address arithmetic a load; for all that
+//   a block reads on planes that are the same for its lanes;
+//   by its word in the pool where the lanes of a wave are on both sides of a
+//   z boundary: one 64-bit shift-and-add a load.  (A structured buffer does
+//   not reach further: measured, its index times its stride wraps at 32 bits.)
+struct PoolRef {
+    const char* p;
+};
+template <typename R>
+__device__ __forceinline__ R sload(R, PoolRef pool, unsigned word, unsigned soff) {
+    return *(reinterpret_cast<const R*>(pool.p + soff) + word);
+}
+
 __device__ __forceinline__ long long sidx(const PatchDev& P, int i, int j, int k) {
     return ((long long)k * P.N[1] + j) * P.N[0] + i;
 }
 
 __device__ __forceinline__ long long stride_of(const PatchDev& P, int a) {
     return a == 0 ? 1LL : (a == 1 ? (long long)P.N[0] : (long long)P.N[0] * P.N[1]);
+}
+
+// The neighbour table's row of a patch (NBR_ROW words): for the side on each
+// axis (9 sz + 3 sy + sx; 0 below, 1 inside, 2 above) the pool word of the
+// zone that (0, 0, 0) of the patch's frame would be in that neighbour, then
+// the first word of each of the three z-layers.
+__device__ __forceinline__ const unsigned* nb_row(const unsigned* __restrict__ nbr, int patch) {
+    return nbr + NBR_ROW * patch;
+}
+__device__ __forceinline__ int nb_side(int i, int n) { return (i >= 0) + (i >= n); }
+// zone (i, j, k) of the frame as a word of the pool; st: strides in words
+__device__ __forceinline__ unsigned nb_zone(const unsigned* __restrict__ T, const int n[3], const unsigned st[3], int i,
+                                            int j, int k) {
+    return T[9 * nb_side(k, n[2]) + 3 * nb_side(j, n[1]) + nb_side(i, n[0])] + (unsigned)i + (unsigned)j * st[1] +
+           (unsigned)k * st[2];
+}
+__device__ __forceinline__ unsigned uniform(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
+// the z-layer that plane k of the frame lies in (the same for the whole
+// block): its descriptor, and a zone of it as a byte offset; for the state
+// (T a row of the table, st the state's strides) or the intermediates (T +
+// NBR_SCR, their strides)
+template <typename R>
+struct Layer {
+    const unsigned* t;  // its nine entries
+    unsigned first;     // its first word
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(R* pool) const { return patch_rsrc(pool + first, 0xFFFFFFFFu); }
+    __device__ __forceinline__ unsigned entry(int side) const { return (uniform(t[side]) - first) * (unsigned)sizeof(R); }
+    __device__ __forceinline__ unsigned entry(bool which, int yes, int no) const { return which ? entry(yes) : entry(no); }
+    __device__ __forceinline__ unsigned zone(const int n[3], const unsigned st[3], int i, int j, int k) const {
+        return (t[3 * nb_side(j, n[1]) + nb_side(i, n[0])] - first + (unsigned)i + (unsigned)j * st[1] +
+                (unsigned)k * st[2]) * (unsigned)sizeof(R);
+    }
+};
+template <typename R>
+__device__ __forceinline__ Layer<R> nb_layer(const unsigned* __restrict__ T, int nz, int k) {
+    const int z = nb_side(k, nz);
+    return Layer<R>{T + 9 * z, uniform(T[27 + z])};
+}
+
+// Where a marching tile kernel reads a position's data: the intermediates'
+// field at byte offset f, at the position's zone (c), its neighbours one up
+// along x, y and z (e, n, u), one down along x, y and both (w, s, sw), and the
+// state's field at the zone (q).
+//   HaloPos    the patch's own region, ghosts included (byte offset x)
+//   SharedPos  byte offsets in the layer of the position's plane (r), of the
+//              plane above for u (ru), in the state's layer for q (rq)
+template <typename R>
+struct HaloPos {
+    __amdgpu_buffer_rsrc_t rs, rw;
+    unsigned x, s0, s1, s2;
+    __device__ __forceinline__ R c(unsigned f) const { return bload(R(0), rw, x, f); }
+    __device__ __forceinline__ R e(unsigned f) const { return bload(R(0), rw, x + s0, f); }
+    __device__ __forceinline__ R n(unsigned f) const { return bload(R(0), rw, x + s1, f); }
+    __device__ __forceinline__ R u(unsigned f) const { return bload(R(0), rw, x + s2, f); }
+    __device__ __forceinline__ R w(unsigned f) const { return bload(R(0), rw, x - s0, f); }
+    __device__ __forceinline__ R s(unsigned f) const { return bload(R(0), rw, x - s1, f); }
+    __device__ __forceinline__ R sw(unsigned f) const { return bload(R(0), rw, x - s0 - s1, f); }
+    __device__ __forceinline__ R q(unsigned f) const { return bload(R(0), rs, x, f); }
+};
+template <typename R>
+struct SharedPos {
+    __amdgpu_buffer_rsrc_t r, ru, rq;
+    unsigned vc, ve, vn, vu, vw, vs, vsw, vq;
+    __device__ __forceinline__ R c(unsigned f) const { return bload(R(0), r, vc, f); }
+    __device__ __forceinline__ R e(unsigned f) const { return bload(R(0), r, ve, f); }
+    __device__ __forceinline__ R n(unsigned f) const { return bload(R(0), r, vn, f); }
+    __device__ __forceinline__ R u(unsigned f) const { return bload(R(0), ru, vu, f); }
+    __device__ __forceinline__ R w(unsigned f) const { return bload(R(0), r, vw, f); }
+    __device__ __forceinline__ R s(unsigned f) const { return bload(R(0), r, vs, f); }
+    __device__ __forceinline__ R sw(unsigned f) const { return bload(R(0), r, vsw, f); }
+    __device__ __forceinline__ R q(unsigned f) const { return bload(R(0), rq, vq, f); }
+};
+
+// Patches of the halo scheme that form the face f along D at transverse
+// coordinates t1, t2 of a patch (its own and the neighbours whose ghost
+// region it lies in): what a protected face counts for, so that the counter
+// does not depend on which scheme ran.  Step 1 forms the faces [-2, n+2] and
+// rows [-3, n+2] of a patch, the corrector [-1, n+1] and [-1, n].
+template <int STAGE>
+__device__ __forceinline__ unsigned long long face_copies(int f, int nd, int t1, int n1, int t2, int n2) {
+    constexpr int F = STAGE == 1 ? 2 : 1, T = STAGE == 1 ? 2 : 0;
+    auto rows = [](int t, int n) { return 1 + (t <= T) + (t >= n - T - 1); };
+    return (unsigned long long)((1 + (f <= F) + (f >= nd - F)) * rows(t1, n1) * rows(t2, n2));
 }
 
 // FP64 floors on one zone (density raised with momentum kept, then pressure
@@ -430,12 +531,21 @@ struct UpdTile {
 };
 constexpr int TILE_BIAS = 16;  // tile origins are stored biased (they may be negative)
 
+struct Yes {
+    static constexpr bool value = true;
+};
+struct No {
+    static constexpr bool value = false;
+};
+
 // q = r / m for r, m >= 1 with r m < 65536, from a 16-bit reciprocal
 __device__ __forceinline__ int small_div(int r, int recip) { return (r * recip) >> 16; }
 
 // ---------------------------------------------------------------------------
 // Steps 3-4 fused.  A block owns a column tile of the in-plane box
-// [-2, n+2]^2 and marches over the planes z in [-2, n+2].  Iteration k forms
+// [-2, n+2]^2 and marches over the planes z in [-2, n+2] (SH: of the patch's
+// own zones [0, n)^3, whose lower neighbours' fluxes and E^r come from the
+// patch that formed them).  Iteration k forms
 //   phase 1  the Step-3 edge EMFs of plane k+1 (Step-1 fluxes, E^r of Step 2)
 //            into LDS, three planes deep, so one barrier a plane suffices,
 //   phase 2  b^{n+1/2} = b^n - (dt/2) curl E (Step 4, Stokes form) on the
@@ -447,10 +557,11 @@ __device__ __forceinline__ int small_div(int r, int recip) { return (r * recip) 
 // are formed (from in-bounds ghost memory) but never read.
 // ---------------------------------------------------------------------------
 
-template <typename R>
+template <typename R, bool SH>
 __global__ void __launch_bounds__(TILE_THREADS) ct_half_kernel(R* __restrict__ pool, const PatchDev* __restrict__ patches,
                                                                const WorkItem* __restrict__ work, Coef<R> cf, int ghost,
-                                                               int cur, const StepConst* __restrict__ sc) {
+                                                               int cur, const StepConst* __restrict__ sc,
+                                                               const unsigned* __restrict__ nbr) {
     __shared__ R s_ed[3 * 3 * CTH_EDMAX];  // [plane mod 3][component][j (tx+1) + i]
     const WorkItem w = work[blockIdx.x];
     if (w.patch < 0) return;  // padding item (whole block)
@@ -466,7 +577,10 @@ __global__ void __launch_bounds__(TILE_THREADS) ct_half_kernel(R* __restrict__ p
     const __amdgpu_buffer_rsrc_t rs = patch_rsrc(pool + P.base, (unsigned)F_STATE * VB);     // state
     const __amdgpu_buffer_rsrc_t rw = patch_rsrc(pool + P.sbase, (unsigned)F_SCRATCH * VB);  // step intermediates
     const unsigned bs = (unsigned)((cur ? F_ST1 : F_ST0) + 8) * VB;
-    const unsigned FX = (unsigned)F_FL1 * VB, FY = FX + 7 * VB, FZ = FY + 7 * VB, ER = (unsigned)F_ER * VB;
+    // SH: the intermediates' layout without ghosts (strides in words, the field stride in bytes)
+    const unsigned ssw[3] = {1u, (unsigned)P.n[0], (unsigned)(P.n[0] * P.n[1])};
+    const unsigned VW = SH ? scratch_stride(P.n[0], P.n[1], P.n[2]) * ES : VB;
+    const unsigned FX = (unsigned)F_FL1 * VW, FY = FX + 7 * VW, FZ = FY + 7 * VW, ER = (unsigned)F_ER * VW;
     const R tau = sc_hdt(*sc, R(0));
     const R ix = cf.idx[0], iy = cf.idx[1], iz = cf.idx[2];
     const R z0 = R(0);
@@ -475,7 +589,16 @@ __global__ void __launch_bounds__(TILE_THREADS) ct_half_kernel(R* __restrict__ p
     auto zoff = [&](int i, int j, int k) -> unsigned {
         return (unsigned)sidx(P, i0 + i + g, j0 + j + g, k + g) * ES;
     };
-    auto ld = [&](unsigned voff, unsigned soff) -> R { return bload(z0, rw, voff, soff); };
+    // SH: byte offsets in the z-layer of plane p (L); those of the extra edges
+    // are held over the march and looked up where it enters the next layer
+    const unsigned* T = SH ? nb_row(nbr, w.patch) + NBR_SCR : nullptr;
+    auto halo = [&](int i, int j, int p) { return HaloPos<R>{rs, rw, zoff(i, j, p), s0, s1, s2}; };
+    auto look = [&](const Layer<R>& L, int i, int j, int p) {
+        const int x = i0 + i, y = j0 + j;
+        const __amdgpu_buffer_rsrc_t r = L.rsrc(pool);
+        return SharedPos<R>{r, r, r, L.zone(P.n, ssw, x, y, p), 0u, 0u, 0u, L.zone(P.n, ssw, x - 1, y, p),
+                            L.zone(P.n, ssw, x, y - 1, p), L.zone(P.n, ssw, x - 1, y - 1, p), 0u};
+    };
 
     const bool owner = t < tx * ty;
     const int zj = owner ? small_div(t, 65536 / tx + 1) : 0, zi = owner ? t - zj * tx : 0;
@@ -486,55 +609,93 @@ __global__ void __launch_bounds__(TILE_THREADS) ct_half_kernel(R* __restrict__ p
     // Step 3 at tile-local edge position (i, j) of plane p, components in mask.
     // cx: m_y, flux_y[B_z], E^r_x at (i, j) and E^r_x at (i, j-1) of plane p-1;
     // cy: m_x, flux_x[B_z], E^r_y at (i, j) and E^r_y at (i-1, j) of plane p-1
-    // (carried, loaded when fresh); replaced by those of plane p.
-    auto ed_item = [&](int i, int j, int p, int mask, R(&cx)[4], R(&cy)[4], bool fresh) {
-        const unsigned xo = zoff(i, j, p);
+    // (carried, loaded from the position below when fresh); replaced by those
+    // of plane p.
+    auto ed_item = [&](int i, int j, int p, const auto& q, int mask, R(&cx)[4], R(&cy)[4], auto fresh) {
+        constexpr bool FRESH = decltype(fresh)::value;
+        auto below = [&] {
+            if constexpr (SH) return look(nb_layer<R>(T, P.n[2], p - 1), i, j, p - 1);
+            else return halo(i, j, p - 1);
+        };
         R* dst = s_ed + ((p + 3) % 3) * 3 * CTH_EDMAX + j * TXE + i;
         if (mask & 1) {  // E_x: a = y, b = z
-            if (fresh) {
-                cx[0] = ld(xo - s2, FY), cx[1] = ld(xo - s2, FY + 5 * VB);
-                cx[2] = ld(xo - s2, ER), cx[3] = ld(xo - s2 - s1, ER);
+            if constexpr (FRESH) {
+                const auto lo = below();
+                cx[0] = lo.c(FY), cx[1] = lo.c(FY + 5 * VW);
+                cx[2] = lo.c(ER), cx[3] = lo.s(ER);
             }
-            const R ma = ld(xo, FY), fa5 = ld(xo, FY + 5 * VB);
-            const R mb = ld(xo, FZ), fb6 = ld(xo, FZ + 6 * VB), mba = ld(xo - s1, FZ), fb6a = ld(xo - s1, FZ + 6 * VB);
-            const R e0 = ld(xo, ER), ea = ld(xo - s1, ER);
+            const R ma = q.c(FY), fa5 = q.c(FY + 5 * VW);
+            const R mb = q.c(FZ), fb6 = q.c(FZ + 6 * VW), mba = q.s(FZ), fb6a = q.s(FZ + 6 * VW);
+            const R e0 = q.c(ER), ea = q.s(ER);
             dst[0] = edge_combine(-fa5, -cx[1], fb6, fb6a, ma, cx[0], mb, mba, e0, ea, cx[2], cx[3]);
             cx[0] = ma, cx[1] = fa5, cx[2] = e0, cx[3] = ea;
         }
         if (mask & 2) {  // E_y: a = z, b = x
-            if (fresh) {
-                cy[0] = ld(xo - s2, FX), cy[1] = ld(xo - s2, FX + 6 * VB);
-                cy[2] = ld(xo - s2, ER + VB), cy[3] = ld(xo - s2 - s0, ER + VB);
+            if constexpr (FRESH) {
+                const auto lo = below();
+                cy[0] = lo.c(FX), cy[1] = lo.c(FX + 6 * VW);
+                cy[2] = lo.c(ER + VW), cy[3] = lo.w(ER + VW);
             }
-            const R ma = ld(xo, FZ), fa5 = ld(xo, FZ + 5 * VB), mab = ld(xo - s0, FZ), fa5b = ld(xo - s0, FZ + 5 * VB);
-            const R mb = ld(xo, FX), fb6 = ld(xo, FX + 6 * VB);
-            const R e0 = ld(xo, ER + VB), eb = ld(xo - s0, ER + VB);
+            const R ma = q.c(FZ), fa5 = q.c(FZ + 5 * VW), mab = q.w(FZ), fa5b = q.w(FZ + 5 * VW);
+            const R mb = q.c(FX), fb6 = q.c(FX + 6 * VW);
+            const R e0 = q.c(ER + VW), eb = q.w(ER + VW);
             dst[CTH_EDMAX] = edge_combine(-fa5, -fa5b, fb6, cy[1], ma, mab, mb, cy[0], e0, cy[2], eb, cy[3]);
             cy[0] = mb, cy[1] = fb6, cy[2] = e0, cy[3] = eb;
         }
         if (mask & 4) {  // E_z: a = x, b = y
-            const R ma = ld(xo, FX), fa5 = ld(xo, FX + 5 * VB), mab = ld(xo - s1, FX), fa5b = ld(xo - s1, FX + 5 * VB);
-            const R mb = ld(xo, FY), fb6 = ld(xo, FY + 6 * VB), mba = ld(xo - s0, FY), fb6a = ld(xo - s0, FY + 6 * VB);
-            const unsigned ez = ER + 2 * VB;
-            dst[2 * CTH_EDMAX] = edge_combine(-fa5, -fa5b, fb6, fb6a, ma, mab, mb, mba, ld(xo, ez), ld(xo - s0, ez),
-                                              ld(xo - s1, ez), ld(xo - s0 - s1, ez));
+            const R ma = q.c(FX), fa5 = q.c(FX + 5 * VW), mab = q.s(FX), fa5b = q.s(FX + 5 * VW);
+            const R mb = q.c(FY), fb6 = q.c(FY + 6 * VW), mba = q.w(FY), fb6a = q.w(FY + 6 * VW);
+            const unsigned ez = ER + 2 * VW;
+            dst[2 * CTH_EDMAX] = edge_combine(-fa5, -fa5b, fb6, fb6a, ma, mab, mb, mba, q.c(ez), q.w(ez),
+                                              q.s(ez), q.sw(ez));
         }
     };
 
     R cx_o[4], cy_o[4], cx_x[4], cy_x[4];
     const int gi = i0 + zi, gj = j0 + zj;
-    const bool ix_in = gi >= -1 && gi <= P.n[0], jy_in = gj >= -1 && gj <= P.n[1];
+    const bool ix_in = SH || (gi >= -1 && gi <= P.n[0]), jy_in = SH || (gj >= -1 && gj <= P.n[1]);
     const int e = zj * TXE + zi;
 
-    if (owner) ed_item(zi, zj, k0, 7, cx_o, cy_o, true);
-    if (extra) ed_item(xi, xj, k0, xmask, cx_x, cy_x, true);
+    unsigned xc = 0u, xw = 0u, xs = 0u, xsw = 0u;  // the extra edge's position
+    Layer<R> L{};
+    if (SH) L = nb_layer<R>(T, P.n[2], k0);
+    const unsigned w0 = ES, w1 = ssw[1] * ES, w2 = ssw[2] * ES;
+    const unsigned lane = ((unsigned)gi + (unsigned)gj * ssw[1]) * ES;
+    // the tile's own zone on plane p (layer L): its lower neighbours cost a select each
+    auto own = [&](int p) {
+        if constexpr (SH) {
+            const __amdgpu_buffer_rsrc_t r = L.rsrc(pool);
+            const unsigned v = lane + (unsigned)p * w2, c = L.entry(4), xm = L.entry(3), ym = L.entry(1);
+            return SharedPos<R>{r, r, r, v + c, 0u, 0u, 0u, v - w0 + (gi == 0 ? xm : c), v - w1 + (gj == 0 ? ym : c),
+                                v - w0 - w1 + (gi == 0 ? (gj == 0 ? L.entry(0) : xm) : (gj == 0 ? ym : c)), 0u};
+        } else {
+            return halo(zi, zj, p);
+        }
+    };
+    auto edge = [&](int p) {
+        if constexpr (SH) {
+            const bool in = p == k0 || p == P.n[2];
+            const int x = i0 + xi, y = j0 + xj;
+            xc = in ? L.zone(P.n, ssw, x, y, p) : xc + w2;
+            xw = in ? L.zone(P.n, ssw, x - 1, y, p) : xw + w2;
+            xs = in ? L.zone(P.n, ssw, x, y - 1, p) : xs + w2;
+            xsw = in ? L.zone(P.n, ssw, x - 1, y - 1, p) : xsw + w2;
+            const __amdgpu_buffer_rsrc_t r = L.rsrc(pool);
+            return SharedPos<R>{r, r, r, xc, 0u, 0u, 0u, xw, xs, xsw, 0u};
+        } else {
+            return halo(xi, xj, p);
+        }
+    };
+    if (owner) ed_item(zi, zj, k0, own(k0), 7, cx_o, cy_o, Yes{});
+    if (extra) ed_item(xi, xj, k0, edge(k0), xmask, cx_x, cy_x, Yes{});
     for (int k = k0; k < k1; k++) {
-        if (owner) ed_item(zi, zj, k + 1, 7, cx_o, cy_o, false);
-        if (extra) ed_item(xi, xj, k + 1, xmask, cx_x, cy_x, false);
+        if (SH && k + 1 == P.n[2]) L = nb_layer<R>(T, P.n[2], k + 1);
+        if (owner) ed_item(zi, zj, k + 1, own(k + 1), 7, cx_o, cy_o, No{});
+        if (extra) ed_item(xi, xj, k + 1, edge(k + 1), xmask, cx_x, cy_x, No{});
         __syncthreads();
         if (owner) {
-            const bool kz_in = k >= -1 && k <= P.n[2];
-            const unsigned xo = zoff(zi, zj, k);
+            const bool kz_in = SH || (k >= -1 && k <= P.n[2]);
+            const unsigned xo = zoff(zi, zj, k), xb = SH ? lane + (unsigned)k * w2 : xo;
             const R* ex0 = s_ed + ((k + 3) % 3) * 3 * CTH_EDMAX;  // E_x, plane k
             const R* ey0 = ex0 + CTH_EDMAX;
             const R* ez0 = ex0 + 2 * CTH_EDMAX;
@@ -542,15 +703,15 @@ __global__ void __launch_bounds__(TILE_THREADS) ct_half_kernel(R* __restrict__ p
             const R* ey1 = ex1 + CTH_EDMAX;
             if (jy_in && kz_in) {
                 R curl = (ez0[e + TXE] - ez0[e]) * iy - (ey1[e] - ey0[e]) * iz;
-                bstore(bload(z0, rs, xo, bs) - tau * curl, rw, xo, (unsigned)F_BH * VB);
+                bstore(bload(z0, rs, xo, bs) - tau * curl, rw, xb, (unsigned)F_BH * VW);
             }
             if (ix_in && kz_in) {
                 R curl = (ex1[e] - ex0[e]) * iz - (ez0[e + 1] - ez0[e]) * ix;
-                bstore(bload(z0, rs, xo, bs + VB) - tau * curl, rw, xo, (unsigned)(F_BH + 1) * VB);
+                bstore(bload(z0, rs, xo, bs + VB) - tau * curl, rw, xb, (unsigned)(F_BH + 1) * VW);
             }
             if (ix_in && jy_in) {
                 R curl = (ey0[e + 1] - ey0[e]) * ix - (ex0[e + TXE] - ex0[e]) * iy;
-                bstore(bload(z0, rs, xo, bs + 2 * VB) - tau * curl, rw, xo, (unsigned)(F_BH + 2) * VB);
+                bstore(bload(z0, rs, xo, bs + 2 * VB) - tau * curl, rw, xb, (unsigned)(F_BH + 2) * VW);
             }
         }
     }
@@ -581,12 +742,13 @@ __global__ void __launch_bounds__(TILE_THREADS) ct_half_kernel(R* __restrict__ p
 
 // One tile of Steps 8-11 (all threads of the block); returns the block's
 // part of the signal-speed maximum of the new state (per thread).
-template <typename R>
+template <typename R, bool SH>
 __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ pool,
                                               const PatchDev* __restrict__ patches, const DevParams& prm,
                                               const Coef<R>& cf, int cur, const StepConst* __restrict__ sc,
                                               unsigned long long* __restrict__ nfloor, int keep_edges,
-                                              R* __restrict__ s_er, R* __restrict__ s_ed) {
+                                              R* __restrict__ s_er, R* __restrict__ s_ed,
+                                              const unsigned* __restrict__ nbr, int fz_slot) {
     constexpr int UPD_ERMAX = UpdTile<R>::er, UPD_EDMAX = UpdTile<R>::ed;
     if (w.patch < 0) return 0.0;  // padding item (whole block)
     const PatchDev P = patches[w.patch];
@@ -602,7 +764,11 @@ __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ 
     const __amdgpu_buffer_rsrc_t rw = patch_rsrc(pool + P.sbase, (unsigned)F_SCRATCH * VB);  // step intermediates
     const unsigned qs = (unsigned)(cur ? F_ST1 : F_ST0) * VB, bs = qs + 8 * VB;
     const unsigned qn = (unsigned)(cur ? F_ST0 : F_ST1) * VB, bn = qn + 8 * VB;
-    const unsigned FX = (unsigned)F_FL2 * VB, FY = FX + 7 * VB, FZ = FY + 7 * VB, BH = (unsigned)F_BH * VB;
+    // SH: the intermediates' layout without ghosts (strides in words, the field stride in bytes)
+    const unsigned ssw[3] = {1u, (unsigned)P.n[0], (unsigned)(P.n[0] * P.n[1])};
+    const unsigned VW = SH ? scratch_stride(P.n[0], P.n[1], P.n[2]) * ES : VB;
+    const unsigned FX = (unsigned)F_FL2 * VW, FY = FX + 7 * VW, BH = (unsigned)F_BH * VW;
+    const unsigned FZ = SH ? (unsigned)fz_slot * VW : FY + 7 * VW;  // where the z corrector left its fluxes
     const R hdt = sc_hdt(*sc, R(0)), dt = sc_dt(*sc, R(0));
     const R ix = cf.idx[0], iy = cf.idx[1], iz = cf.idx[2];
     const R z0 = R(0);
@@ -611,8 +777,17 @@ __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ 
     auto zoff = [&](int i, int j, int k) -> unsigned {
         return (unsigned)sidx(P, i0 + i + g, j0 + j + g, k + g) * ES;
     };
-    auto ld = [&](unsigned voff, unsigned soff) -> R { return bload(z0, rw, voff, soff); };
     auto lds = [&](unsigned voff, unsigned soff) -> R { return bload(z0, rs, voff, soff); };
+    // SH: byte offsets in the z-layer of the position's plane; those of the
+    // ring's E^r and of the extra edges are held over the march and looked up
+    // where it enters the next layer
+    const unsigned* T = SH ? nb_row(nbr, w.patch) : nullptr;
+    const unsigned stw[3] = {1u, s1 / ES, s2 / ES};
+    const unsigned w0 = ES, w1 = ssw[1] * ES, w2 = ssw[2] * ES;
+    auto layer = [&](int p) { return nb_layer<R>(T + NBR_SCR, P.n[2], p); };
+    auto slayer = [&](int p) { return nb_layer<R>(T, P.n[2], p); };  // the state's
+    auto vox = [&](const Layer<R>& L, int i, int j, int p) -> unsigned { return L.zone(P.n, ssw, i0 + i, j0 + j, p); };
+    auto halo = [&](int i, int j, int p) { return HaloPos<R>{rs, rw, zoff(i, j, p), s0, s1, s2}; };
 
     // own zone (every thread of a full tile), ring zone of E^r, extra edge position
     const bool owner = t < tx * ty;
@@ -639,29 +814,28 @@ __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ 
     // q - dt div F of rows 0-3 for the final update of the zone; r0, if
     // given, the rho rows of flux_x, flux_y and flux_z on the zone's lower
     // faces, which the zone's edges of Step 9 use again.
-    auto er_item = [&](int ex, int ey, int p, R(&fz)[4], R& bz, bool fresh, R* uf, R* r0) {
-        const unsigned xo = zoff(ex, ey, p);
+    auto er_item = [&](int ex, int ey, int p, const auto& a, R(&fz)[4], R& bz, bool fresh, R* uf, R* r0) {
         R u[4];
 #pragma unroll
         for (int c = 0; c < 4; c++) {
-            const unsigned cf0 = FX + c * VB, cf1 = FY + c * VB, cf2 = FZ + c * VB;
-            if (fresh) fz[c] = ld(xo, cf2);
-            const R fzn = ld(xo + s2, cf2);
-            const R fx = ld(xo, cf0), fy = ld(xo, cf1);
+            const unsigned cf0 = FX + c * VW, cf1 = FY + c * VW, cf2 = FZ + c * VW;
+            if (fresh) fz[c] = a.c(cf2);
+            const R fzn = a.u(cf2);
+            const R fx = a.c(cf0), fy = a.c(cf1);
             if (c == 0 && r0) r0[0] = fx, r0[1] = fy, r0[2] = fz[0];
             R div = R(0);
-            div += (ld(xo + s0, cf0) - fx) * ix;
-            div += (ld(xo + s1, cf1) - fy) * iy;
+            div += (a.e(cf0) - fx) * ix;
+            div += (a.n(cf1) - fy) * iy;
             div += (fzn - fz[c]) * iz;
-            const R q = lds(xo, qs + c * VB);
+            const R q = a.q(qs + c * VB);
             u[c] = q - hdt * div;
             if (uf) uf[c] = q - dt * div;
             fz[c] = fzn;
         }
-        if (fresh) bz = ld(xo, BH + 2 * VB);
-        const R bzn = ld(xo + s2, BH + 2 * VB);
-        R B0 = R(0.5) * (ld(xo, BH) + ld(xo + s0, BH));
-        R B1 = R(0.5) * (ld(xo, BH + VB) + ld(xo + s1, BH + VB));
+        if (fresh) bz = a.c(BH + 2 * VW);
+        const R bzn = a.u(BH + 2 * VW);
+        R B0 = R(0.5) * (a.c(BH) + a.e(BH));
+        R B1 = R(0.5) * (a.c(BH + VW) + a.n(BH + VW));
         R B2 = R(0.5) * (bz + bzn);
         bz = bzn;
         R ir = frcp(u[0]);
@@ -675,27 +849,37 @@ __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ 
     // Step 9 at tile-local edge position (i, j) of plane p, components in mask
     // (bit c).  cx: flux_y rows 0 and 5, cy: flux_x rows 0 and 6, both at (i, j)
     // of plane p-1 (carried, loaded when fresh); replaced by those of plane p.
-    auto ed_item = [&](int i, int j, int p, int mask, R(&cx)[2], R(&cy)[2], bool fresh, const R* r0) {
-        const unsigned xo = zoff(i, j, p);
+    auto ed_item = [&](int i, int j, int p, const auto& a, int mask, R(&cx)[2], R(&cy)[2], auto fresh, const R* r0) {
+        constexpr bool FRESH = decltype(fresh)::value;
+        auto below = [&] {
+            if constexpr (SH) {
+                const Layer<R> L = layer(p - 1);
+                const __amdgpu_buffer_rsrc_t r = L.rsrc(pool);
+                return SharedPos<R>{r, r, r, vox(L, i, j, p - 1), 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+            } else {
+                return halo(i, j, p - 1);
+            }
+        };
         // the rho rows on the position's lower faces (from Step 8 when given)
-        const R fx0 = r0 ? r0[0] : ld(xo, FX), fy0 = r0 ? r0[1] : ld(xo, FY), fz0 = r0 ? r0[2] : ld(xo, FZ);
+        const R fx0 = r0 ? r0[0] : a.c(FX), fy0 = r0 ? r0[1] : a.c(FY), fz0 = r0 ? r0[2] : a.c(FZ);
+        const unsigned xo = keep_edges ? zoff(i, j, p) : 0u;
         const int ri = (j + 1) * TXP + (i + 1), e = j * TXE + i;
         const R* ec = s_er + (p & 1) * 3 * UPD_ERMAX + ri;        // E^r of plane p at the edge's zone
         const R* ep = s_er + ((p - 1) & 1) * 3 * UPD_ERMAX + ri;  // plane p-1
         R* dst = s_ed + (p & 1) * 3 * UPD_EDMAX + e;
         if (mask & 1) {  // E_x: a = y, b = z
-            if (fresh) cx[0] = ld(xo - s2, FY), cx[1] = ld(xo - s2, FY + 5 * VB);
-            const R ma = fy0, fa5 = ld(xo, FY + 5 * VB);
-            const R mb = fz0, fb6 = ld(xo, FZ + 6 * VB), mba = ld(xo - s1, FZ), fb6a = ld(xo - s1, FZ + 6 * VB);
+            if constexpr (FRESH) cx[0] = below().c(FY), cx[1] = below().c(FY + 5 * VW);
+            const R ma = fy0, fa5 = a.c(FY + 5 * VW);
+            const R mb = fz0, fb6 = a.c(FZ + 6 * VW), mba = a.s(FZ), fb6a = a.s(FZ + 6 * VW);
             const R E = edge_combine(-fa5, -cx[1], fb6, fb6a, ma, cx[0], mb, mba, ec[0], ec[-TXP], ep[0], ep[-TXP]);
             dst[0] = E;
             if (keep_edges) bstore(E, rw, xo, (unsigned)F_ED * VB);
             cx[0] = ma, cx[1] = fa5;
         }
         if (mask & 2) {  // E_y: a = z, b = x
-            if (fresh) cy[0] = ld(xo - s2, FX), cy[1] = ld(xo - s2, FX + 6 * VB);
-            const R ma = fz0, fa5 = ld(xo, FZ + 5 * VB), mab = ld(xo - s0, FZ), fa5b = ld(xo - s0, FZ + 5 * VB);
-            const R mb = fx0, fb6 = ld(xo, FX + 6 * VB);
+            if constexpr (FRESH) cy[0] = below().c(FX), cy[1] = below().c(FX + 6 * VW);
+            const R ma = fz0, fa5 = a.c(FZ + 5 * VW), mab = a.w(FZ), fa5b = a.w(FZ + 5 * VW);
+            const R mb = fx0, fb6 = a.c(FX + 6 * VW);
             const R* c1 = ec + UPD_ERMAX;
             const R* p1 = ep + UPD_ERMAX;
             const R E = edge_combine(-fa5, -fa5b, fb6, cy[1], ma, mab, mb, cy[0], c1[0], p1[0], c1[-1], p1[-1]);
@@ -704,8 +888,8 @@ __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ 
             cy[0] = mb, cy[1] = fb6;
         }
         if (mask & 4) {  // E_z: a = x, b = y
-            const R ma = fx0, fa5 = ld(xo, FX + 5 * VB), mab = ld(xo - s1, FX), fa5b = ld(xo - s1, FX + 5 * VB);
-            const R mb = fy0, fb6 = ld(xo, FY + 6 * VB), mba = ld(xo - s0, FY), fb6a = ld(xo - s0, FY + 6 * VB);
+            const R ma = fx0, fa5 = a.c(FX + 5 * VW), mab = a.s(FX), fa5b = a.s(FX + 5 * VW);
+            const R mb = fy0, fb6 = a.c(FY + 6 * VW), mba = a.w(FY), fb6a = a.w(FY + 6 * VW);
             const R* c2 = ec + 2 * UPD_ERMAX;
             const R E = edge_combine(-fa5, -fa5b, fb6, fb6a, ma, mab, mb, mba, c2[0], c2[-1], c2[-TXP], c2[-1 - TXP]);
             dst[2 * UPD_EDMAX] = E;
@@ -721,34 +905,97 @@ __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ 
     R fz4 = R(0), bzc = R(0);  // flux_z row 4 and b^{n+1}_z on the lower face of plane k
     double sp = 0.0;
 
+    // SH: the layer of the plane at hand (L) and of the one above it (Lu)
+    unsigned rc = 0u, re = 0u, rn = 0u, ru = 0u, rq = 0u, xc = 0u, xw = 0u, xs = 0u;  // the ring's and the extra edge's positions
+    Layer<R> L{}, Lu{}, S{};  // S: the state's layer of the plane at hand
+    auto ring_at = [&](int p) {
+        if constexpr (SH) {
+            const bool low = p == k0 - 1, in = low || p == 0 || p == P.n[2];
+            rc = low ? vox(L, rx, ry, p) : ru;
+            ru = low || p + 1 == 0 || p + 1 == P.n[2] ? vox(Lu, rx, ry, p + 1) : rc + w2;
+            re = in ? vox(L, rx + 1, ry, p) : re + w2;
+            rn = in ? vox(L, rx, ry + 1, p) : rn + w2;
+            rq = in ? S.zone(P.n, stw, i0 + rx, j0 + ry, p) : rq + s2;
+            return SharedPos<R>{L.rsrc(pool), Lu.rsrc(pool), S.rsrc(pool), rc, re, rn, ru, 0u, 0u, 0u, rq};
+        } else {
+            return halo(rx, ry, p);
+        }
+    };
+    auto edge_at = [&](int p) {
+        if constexpr (SH) {
+            const bool in = p == k0 || p == P.n[2];
+            xc = in ? vox(L, xi, xj, p) : xc + w2;
+            xw = in ? vox(L, xi - 1, xj, p) : xw + w2;
+            xs = in ? vox(L, xi, xj - 1, p) : xs + w2;
+            const __amdgpu_buffer_rsrc_t r = L.rsrc(pool);
+            return SharedPos<R>{r, r, r, xc, 0u, 0u, 0u, xw, xs, 0u, 0u};
+        } else {
+            return halo(xi, xj, p);
+        }
+    };
+    // the tile's own zone: its in-plane neighbours cost a select each
+    const int gx = i0 + zi, gy = j0 + zj;
+    const unsigned lane = ((unsigned)gx + (unsigned)gy * ssw[1]) * ES, lanes = ((unsigned)gx + (unsigned)gy * stw[1]) * ES;
+    auto own_at = [&](int p, const Layer<R>& M, const Layer<R>& Mu) {
+        if constexpr (SH) {
+            const unsigned v = lane + (unsigned)p * w2, c = M.entry(4);
+            return SharedPos<R>{M.rsrc(pool), Mu.rsrc(pool), S.rsrc(pool), v + c, v + w0 + (gx == P.n[0] - 1 ? M.entry(5) : c),
+                                v + w1 + (gy == P.n[1] - 1 ? M.entry(7) : c), v + w2 + Mu.entry(4),
+                                v - w0 + (gx == 0 ? M.entry(3) : c), v - w1 + (gy == 0 ? M.entry(1) : c), 0u,
+                                lanes + (unsigned)p * s2 + S.entry(4)};
+        } else {
+            return halo(zi, zj, p);
+        }
+    };
     // prologue: E^r of planes k0-1 and k0, edges of plane k0
-    if (owner) er_item(zi, zj, k0 - 1, fz_o, bz_o, true, nullptr, nullptr);
-    if (ring) er_item(rx, ry, k0 - 1, fz_r, bz_r, true, nullptr, nullptr);
-    if (owner) er_item(zi, zj, k0, fz_o, bz_o, false, ufc, r0o);
-    if (ring) er_item(rx, ry, k0, fz_r, bz_r, false, nullptr, nullptr);
+    if (SH) L = layer(k0 - 1), Lu = layer(k0), S = slayer(k0 - 1);
+    if (owner) er_item(zi, zj, k0 - 1, own_at(k0 - 1, L, Lu), fz_o, bz_o, true, nullptr, nullptr);
+    if (ring) er_item(rx, ry, k0 - 1, ring_at(k0 - 1), fz_r, bz_r, true, nullptr, nullptr);
+    if (SH) L = Lu, Lu = layer(k0 + 1), S = slayer(k0);
+    const Layer<R> Lo = L, So = S;  // the patch's own
+    if (owner) er_item(zi, zj, k0, own_at(k0, L, Lu), fz_o, bz_o, false, ufc, r0o);
+    if (ring) er_item(rx, ry, k0, ring_at(k0), fz_r, bz_r, false, nullptr, nullptr);
     __syncthreads();
-    if (owner) ed_item(zi, zj, k0, 7, cx_o, cy_o, true, r0o);
-    if (extra) ed_item(xi, xj, k0, xmask, cx_x, cy_x, true, nullptr);
+    if (owner) ed_item(zi, zj, k0, own_at(k0, L, Lu), 7, cx_o, cy_o, Yes{}, r0o);
+    if (extra) ed_item(xi, xj, k0, edge_at(k0), xmask, cx_x, cy_x, Yes{}, nullptr);
     __syncthreads();
     for (int k = k0; k < k1; k++) {
-        if (owner) er_item(zi, zj, k + 1, fz_o, bz_o, false, ufn, r0o);
-        if (ring) er_item(rx, ry, k + 1, fz_r, bz_r, false, nullptr, nullptr);
+        if (SH) {
+            L = Lu;
+            if (k + 2 == P.n[2]) Lu = layer(k + 2);
+            if (k + 1 == P.n[2]) S = slayer(k + 1);
+        }
+        if (owner) er_item(zi, zj, k + 1, own_at(k + 1, L, Lu), fz_o, bz_o, false, ufn, r0o);
+        if (ring) er_item(rx, ry, k + 1, ring_at(k + 1), fz_r, bz_r, false, nullptr, nullptr);
         __syncthreads();
-        if (owner) ed_item(zi, zj, k + 1, 7, cx_o, cy_o, false, r0o);
-        if (extra) ed_item(xi, xj, k + 1, xmask, cx_x, cy_x, false, nullptr);
+        if (owner) ed_item(zi, zj, k + 1, own_at(k + 1, L, Lu), 7, cx_o, cy_o, No{}, r0o);
+        if (extra) ed_item(xi, xj, k + 1, edge_at(k + 1), xmask, cx_x, cy_x, No{}, nullptr);
         __syncthreads();
         if (owner) {
             const unsigned xo = zoff(zi, zj, k);
             R u[8];
 #pragma unroll
             for (int c = 0; c < 4; c++) u[c] = ufc[c];
+            // the zone and its upper neighbours on plane k
+            const auto a = own_at(k, Lo, L);
+            // the face field one up along x, y and z
+            auto bup = [&](int ax, unsigned f) -> R {
+                if constexpr (SH) {
+                    const unsigned v = lanes + (unsigned)k * s2;
+                    if (ax == 0) return bload(z0, So.rsrc(pool), v + s0 + So.entry(gx == P.n[0] - 1, 5, 4), f);
+                    if (ax == 1) return bload(z0, So.rsrc(pool), v + s1 + So.entry(gy == P.n[1] - 1, 7, 4), f);
+                    return bload(z0, S.rsrc(pool), v + s2 + S.entry(4), f);
+                } else {
+                    return lds(xo + (ax == 0 ? s0 : (ax == 1 ? s1 : s2)), f);
+                }
+            };
             // Step 10 on E (flux row 4)
             {
-                if (k == k0) fz4 = ld(xo, FZ + 4 * VB);
-                const R fz4n = ld(xo + s2, FZ + 4 * VB);
+                if (k == k0) fz4 = a.c(FZ + 4 * VW);
+                const R fz4n = a.u(FZ + 4 * VW);
                 R div = R(0);
-                div += (ld(xo + s0, FX + 4 * VB) - ld(xo, FX + 4 * VB)) * ix;
-                div += (ld(xo + s1, FY + 4 * VB) - ld(xo, FY + 4 * VB)) * iy;
+                div += (a.e(FX + 4 * VW) - a.c(FX + 4 * VW)) * ix;
+                div += (a.n(FY + 4 * VW) - a.c(FY + 4 * VW)) * iy;
                 div += (fz4n - fz4) * iz;
                 u[7] = lds(xo, qs + 7 * VB) - dt * div;
                 fz4 = fz4n;
@@ -762,13 +1009,13 @@ __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ 
             // Step 11 on the two faces of the zone along each axis (the lower
             // z-face is the upper one of the plane below)
             R bxl = lds(xo, bs) - dt * ((ez0[e + TXE] - ez0[e]) * iy - (ey1[e] - ey0[e]) * iz);
-            R bxr = lds(xo + s0, bs) - dt * ((ez0[e + 1 + TXE] - ez0[e + 1]) * iy - (ey1[e + 1] - ey0[e + 1]) * iz);
+            R bxr = bup(0, bs) - dt * ((ez0[e + 1 + TXE] - ez0[e + 1]) * iy - (ey1[e + 1] - ey0[e + 1]) * iz);
             R byl = lds(xo, bs + VB) - dt * ((ex1[e] - ex0[e]) * iz - (ez0[e + 1] - ez0[e]) * ix);
-            R byr = lds(xo + s1, bs + VB) -
+            R byr = bup(1, bs + VB) -
                     dt * ((ex1[e + TXE] - ex0[e + TXE]) * iz - (ez0[e + 1 + TXE] - ez0[e + TXE]) * ix);
             if (k == k0) bzc = lds(xo, bs + 2 * VB) - dt * ((ey0[e + 1] - ey0[e]) * ix - (ex0[e + TXE] - ex0[e]) * iy);
             R bzl = bzc;
-            R bzr = lds(xo + s2, bs + 2 * VB) - dt * ((ey1[e + 1] - ey1[e]) * ix - (ex1[e + TXE] - ex1[e]) * iy);
+            R bzr = bup(2, bs + 2 * VB) - dt * ((ey1[e + 1] - ey1[e]) * ix - (ex1[e + TXE] - ex1[e]) * iy);
             bzc = bzr;
             bstore(bxl, rs, xo, bn);
             bstore(byl, rs, xo, bn + VB);
@@ -776,7 +1023,9 @@ __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ 
             // shared right faces of the patch
             // (face n along x is the +x neighbour's face 0, which it writes
             // here itself: pushed, or pulled below when it is frozen)
-            if (i0 + zi == P.n[0] - 1 && P.nb[1] < 0) bstore(bxr, rs, xo + s0, bn);
+            // (SH: all of them are neighbours' own faces 0, formed alike; stored
+            // for the diagnostics)
+            if (i0 + zi == P.n[0] - 1 && (SH || P.nb[1] < 0)) bstore(bxr, rs, xo + s0, bn);
             if (j0 + zj == P.n[1] - 1) bstore(byr, rs, xo + s1, bn + VB);
             if (k == P.n[2] - 1) bstore(bzr, rs, xo + s2, bn + 2 * VB);
             u[4] = R(0.5) * (bxl + bxr);
@@ -790,9 +1039,10 @@ __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ 
             // row and plane, face neighbours share the y-z extent); at a domain
             // boundary (no neighbour) the boundary zone fills the patch's own
             // x-ghosts by zero gradient, b_x from the boundary face
+            // (SH: no step reads ghosts, so none are written)
             const int gi = i0 + zi;
 #pragma unroll
-            for (int side = 0; side < 2; side++) {
+            for (int side = 0; side < (SH ? 0 : 2); side++) {
                 const bool mine = side == 0 ? gi < g : gi >= P.n[0] - g;
                 if (!mine) continue;
                 const int nbq = P.nb[side];
@@ -861,19 +1111,24 @@ __device__ __forceinline__ double update_tile(const WorkItem w, R* __restrict__ 
 // 8 j + x, the order xcd_order gives) one after another from an atomic
 // counter; the last block to finish sets the counters back to zero, so the
 // launch needs no reset of its own (and none inside a captured graph).
-template <typename R, bool QUEUE>
-__global__ void __launch_bounds__(UpdTile<R>::threads) update_kernel(R* __restrict__ pool, const PatchDev* __restrict__ patches,
+template <typename R, bool QUEUE, bool SH>
+__global__ void __launch_bounds__(UpdTile<R>::threads, SH && !QUEUE ? (sizeof(R) == 4 ? 4 : 3) : 1) update_kernel(R* __restrict__ pool, const PatchDev* __restrict__ patches,
                                                               const WorkItem* __restrict__ work, int nitems,
                                                               unsigned int* __restrict__ queue, DevParams prm, Coef<R> cf,
                                                               int cur, const StepConst* __restrict__ sc,
                                                               unsigned long long* __restrict__ nfloor,
-                                                              unsigned long long* __restrict__ smax_bits, int keep_edges) {
+                                                              unsigned long long* __restrict__ smax_bits, int keep_edges,
+                                                              const unsigned* __restrict__ nbr,
+                                                              int fz_slot, StepConst* __restrict__ sc_used) {
     constexpr int UPD_ERMAX = UpdTile<R>::er, UPD_EDMAX = UpdTile<R>::ed;
     __shared__ R s_er[2 * 3 * UPD_ERMAX];  // [plane & 1][component][(ey+1)(tx+2) + ex+1]
     __shared__ R s_ed[2 * 3 * UPD_EDMAX];  // [plane & 1][component][j (tx+1) + i]
     double sp = 0.0;
+    // SH: keep this step's constants (wmb_debug_stage forms the stages again)
+    if (SH && blockIdx.x == 0 && threadIdx.x == 0) *sc_used = *sc;
     if (!QUEUE) {
-        sp = update_tile<R>(work[blockIdx.x], pool, patches, prm, cf, cur, sc, nfloor, keep_edges, s_er, s_ed);
+        sp = update_tile<R, SH>(work[blockIdx.x], pool, patches, prm, cf, cur, sc, nfloor, keep_edges, s_er, s_ed, nbr,
+                                fz_slot);
     } else {
         __shared__ int s_item;
         const int x = (int)(blockIdx.x & 7u), nq = nitems / 8;
@@ -883,8 +1138,8 @@ __global__ void __launch_bounds__(UpdTile<R>::threads) update_kernel(R* __restri
             const int j = s_item;
             __syncthreads();  // every thread has read s_item (and left the last tile's LDS)
             if (j >= nq) break;
-            sp = fmax(sp, update_tile<R>(work[8 * j + x], pool, patches, prm, cf, cur, sc, nfloor, keep_edges, s_er,
-                                         s_ed));
+            sp = fmax(sp, update_tile<R, SH>(work[8 * j + x], pool, patches, prm, cf, cur, sc, nfloor, keep_edges, s_er,
+                                             s_ed, nbr, fz_slot));
         }
         __threadfence();
         if (threadIdx.x == 0 && atomicAdd(queue + 8, 1u) == gridDim.x - 1) {
@@ -1036,6 +1291,39 @@ __device__ __forceinline__ void zone_fetch(__amdgpu_buffer_rsrc_t rs, __amdgpu_b
         for (int a = 0; a < 3; a++) {
             z.b[a][0] = bload(z0, rs, xo, bs + a * VB);
             z.b[a][1] = bload(z0, rs, xo, bs + a * VB + st[a] * ES);
+        }
+    }
+}
+
+// The same loads with shared-halo addressing: ld(a, f) reads the state's field
+// at byte offset f at the zone (a = 3) or one up along axis a, li(a, f) the
+// intermediates' likewise.
+template <typename R, int D, int STAGE, typename LoadS, typename LoadI>
+__device__ __forceinline__ void zone_fetch_sh(LoadS ld, LoadI li, unsigned qs, unsigned VB, unsigned VW,
+                                              ZoneRaw<R, STAGE>& z) {
+    constexpr int A1 = (D + 1) % 3, A2 = (D + 2) % 3;
+    if (STAGE == 3) {
+#pragma unroll
+        for (int r = 0; r < 7; r++) z.q[r] = li(3, (unsigned)(F_FL2 + 7 * D + r) * VW);
+        return;
+    }
+#pragma unroll
+    for (int c = 0; c < 8; c++) z.q[c] = ld(3, qs + c * VB);
+    if (STAGE == 2) {
+        const unsigned f1 = (unsigned)(F_FL1 + 7 * A1) * VW, f2 = (unsigned)(F_FL1 + 7 * A2) * VW;
+#pragma unroll
+        for (int r = 0; r < 7; r++) {
+            const int ra = r < 5 ? r : (r == 5 ? 6 : 5), rb = r < 5 ? r : (r == 5 ? 5 : 6);
+            z.fa[r][0] = li(3, f1 + ra * VW);
+            z.fa[r][1] = li(A1, f1 + ra * VW);
+            z.fb[r][0] = li(3, f2 + rb * VW);
+            z.fb[r][1] = li(A2, f2 + rb * VW);
+        }
+        const unsigned bs = qs + 8 * VB;
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            z.b[a][0] = ld(3, bs + a * VB);
+            z.b[a][1] = ld(a, bs + a * VB);
         }
     }
 }
@@ -1357,11 +1645,12 @@ __device__ __forceinline__ void store_flux(const R out[7], __amdgpu_buffer_rsrc_
     bstore(out[6], rs, xo, fo + 6 * VB);
 }
 
-template <typename R, int D, int STAGE, bool MM, bool PROT>
+template <typename R, int D, int STAGE, bool MM, bool PROT, bool SH>
 __global__ void __launch_bounds__(1024) sweep_kernel(R* __restrict__ pool, const PatchDev* __restrict__ patches,
                                                      const WorkItem* __restrict__ work, DevParams prm, Coef<R> cf,
                                                      int cur, const StepConst* __restrict__ sc, int P, int W, int zlo,
-                                                     unsigned long long* __restrict__ nprot) {
+                                                     unsigned long long* __restrict__ nprot,
+                                                     const unsigned* __restrict__ nbr) {
     extern __shared__ unsigned char smem_raw[];
     const int nthr = P * W;
     Rec8<R>* shp = reinterpret_cast<Rec8<R>*>(smem_raw);  // zone primitives
@@ -1404,23 +1693,65 @@ __global__ void __launch_bounds__(1024) sweep_kernel(R* __restrict__ pool, const
     const __amdgpu_buffer_rsrc_t rw = patch_rsrc(pool + Pt.sbase, (unsigned)F_SCRATCH * VB);  // step intermediates
     const unsigned qs = (unsigned)(cur ? F_ST1 : F_ST0) * VB;  // state copy
     const R z0 = R(0);
+    // SH: the zone, in the patch or its neighbour along D.  Along x and y it is
+    // in the patch's own z-layer; along z a wave holds zones of both layers
+    const PoolRef rp{reinterpret_cast<const char*>(pool)};
+    const unsigned* T = SH ? nb_row(nbr, wi.patch) : nullptr;
+    // the intermediates without ghosts: strides in words, the field stride in
+    // bytes, the thread's own zone (where it has one) as a byte offset
+    const unsigned ssw[3] = {1u, (unsigned)Pt.n[0], (unsigned)(Pt.n[0] * Pt.n[1])};
+    const unsigned VW = SH ? scratch_stride(Pt.n[0], Pt.n[1], Pt.n[2]) * ES : VB;
+    const unsigned xw = SH ? ((unsigned)zc[0] + (unsigned)zc[1] * ssw[1] + (unsigned)zc[2] * ssw[2]) * ES : xo;
+    Layer<R> L{}, Ls{};  // the state's and the intermediates' layer (x, y)
+    if (SH && D != 2) L = nb_layer<R>(T, Pt.n[2], 0), Ls = nb_layer<R>(T + NBR_SCR, Pt.n[2], 0);
+    const __amdgpu_buffer_rsrc_t rl = SH && D != 2 ? L.rsrc(pool) : rs, rls = SH && D != 2 ? Ls.rsrc(pool) : rw;
+    unsigned zv = 0u, zs = 0u;  // byte offset in the layer (x, y) or word of the pool (z): state, intermediates
+    if (SH && live) {
+        if (STAGE != 3) zv = D != 2 ? L.zone(Pt.n, st, zc[0], zc[1], zc[2]) : nb_zone(T, Pt.n, st, zc[0], zc[1], zc[2]);
+        if (STAGE != 1)
+            zs = D != 2 ? Ls.zone(Pt.n, ssw, zc[0], zc[1], zc[2]) : nb_zone(T + NBR_SCR, Pt.n, ssw, zc[0], zc[1], zc[2]);
+    }
+    auto zld = [&](unsigned f) -> R { return D != 2 ? bload(z0, rl, zv, f) : sload(z0, rp, zv, f); };
+    auto sld = [&](unsigned f) -> R { return D != 2 ? bload(z0, rls, zs, f) : sload(z0, rp, zs, f); };
 
     // ---------------- phase A: zone primitives ----------------
     if (live) {
         if (STAGE == 1 && D == 0) {
-            // Step 2: reference EMF E^r = -v x B from q^n on [-3, n+2]^3
-            if (zc[0] >= -3 && zc[0] <= Pt.n[0] + 2) {
+            // Step 2: reference EMF E^r = -v x B from q^n on [-3, n+2]^3 (SH: the patch's own zones)
+            if (zc[0] >= (SH ? 0 : -3) && zc[0] <= Pt.n[0] + (SH ? -1 : 2)) {
                 R u[8];
 #pragma unroll
                 for (int c = 0; c < 8; c++) u[c] = bload(z0, rs, xo, qs + c * VB);
                 R ir = frcp(u[0]);
                 R vx = u[1] * ir, vy = u[2] * ir, vz = u[3] * ir;
-                bstore(vz * u[5] - vy * u[6], rw, xo, (unsigned)F_ER * VB);
-                bstore(vx * u[6] - vz * u[4], rw, xo, (unsigned)(F_ER + 1) * VB);
-                bstore(vy * u[4] - vx * u[5], rw, xo, (unsigned)(F_ER + 2) * VB);
+                bstore(vz * u[5] - vy * u[6], rw, xw, (unsigned)F_ER * VW);
+                bstore(vx * u[6] - vz * u[4], rw, xw, (unsigned)(F_ER + 1) * VW);
+                bstore(vy * u[4] - vx * u[5], rw, xw, (unsigned)(F_ER + 2) * VW);
             }
         }
-        shp[tid] = zone_phase<R, D, STAGE>(rs, rw, xo, st, qs, VB, cf, prm, *sc);
+        if (SH) {
+            unsigned up[3] = {0u, 0u, 0u}, us[3] = {0u, 0u, 0u};  // one up along each axis: state, intermediates
+            if (STAGE == 2) {
+                for (int a = 0; a < 3; a++) {
+                    const int i = zc[0] + (a == 0), j = zc[1] + (a == 1), k = zc[2] + (a == 2);
+                    const bool lay = D != 2 && a != 2;
+                    up[a] = lay ? L.zone(Pt.n, st, i, j, k) : nb_zone(T, Pt.n, st, i, j, k);
+                    if (a != D) us[a] = lay ? Ls.zone(Pt.n, ssw, i, j, k) : nb_zone(T + NBR_SCR, Pt.n, ssw, i, j, k);
+                }
+            }
+            ZoneRaw<R, STAGE> z;
+            zone_fetch_sh<R, D, STAGE>(
+                [&](int a, unsigned f) -> R {
+                    return a == 3 ? zld(f) : (a == 2 || D == 2 ? sload(z0, rp, up[a], f) : bload(z0, rl, up[a], f));
+                },
+                [&](int a, unsigned f) -> R {
+                    return a == 3 ? sld(f) : (a == 2 || D == 2 ? sload(z0, rp, us[a], f) : bload(z0, rls, us[a], f));
+                },
+                qs, VB, VW, z);
+            shp[tid] = zone_record<R, D, STAGE>(z, cf, prm, *sc);
+        } else {
+            shp[tid] = zone_phase<R, D, STAGE>(rs, rw, xo, st, qs, VB, cf, prm, *sc);
+        }
     }
     __syncthreads();
 
@@ -1431,7 +1762,8 @@ __global__ void __launch_bounds__(1024) sweep_kernel(R* __restrict__ pool, const
     bool prot = false;
     const bool face = live && s >= 1;
     if (face) {
-        bf = (STAGE == 1) ? bload(z0, rs, xo, qs + (8 + D) * VB) : bload(z0, rw, xo, (unsigned)(F_BH + D) * VB);
+        if (SH) bf = STAGE == 1 ? zld(qs + (8 + D) * VB) : sld((unsigned)(F_BH + D) * VW);
+        else bf = (STAGE == 1) ? bload(z0, rs, xo, qs + (8 + D) * VB) : bload(z0, rw, xo, (unsigned)(F_BH + D) * VB);
         Rec8<R> gr;
         face_phase<R, PROT>(shp[tid - sstep], shp[tid], bf, lam, cf, e, alpha, nu, gr, prot);
         shg[tid] = gr;
@@ -1443,7 +1775,7 @@ __global__ void __launch_bounds__(1024) sweep_kernel(R* __restrict__ pool, const
         R cav[7], out[7];
         if (PROT && prot) {
             face_central<R, PROT>(shp[tid - sstep], shp[tid], bf, e, prot, cf, out);
-            atomicAdd(nprot, 1ULL);
+            atomicAdd(nprot, SH ? face_copies<STAGE>(zc[D], Pt.n[D], zc[FA], Pt.n[FA], zc[SA], Pt.n[SA]) : 1ULL);
         } else {
             const Rec8<R> Gm = shg[tid - sstep], G0 = shg[tid], Gp = shg[tid + sstep];
             R c[7];
@@ -1455,7 +1787,9 @@ __global__ void __launch_bounds__(1024) sweep_kernel(R* __restrict__ pool, const
             face_central<R, PROT>(shp[tid - sstep], shp[tid], bf, e, prot, cf, cav);
             face_combine(cav, c, sc_il(*sc, D, R(0)), out);
         }
-        store_flux<R, D>(out, rw, xo, (unsigned)((STAGE == 1 ? F_FL1 : F_FL2) + 7 * D) * VB, VB);
+        // (SH, STAGE 3: a neighbour's pencil may yet read the records, so the
+        // fluxes go to the Step-1 z rows, which the fused corrector has read)
+        store_flux<R, D>(out, rw, xw, (unsigned)((STAGE == 1 || (SH && STAGE == 3) ? F_FL1 : F_FL2) + 7 * D) * VW, VW);
     }
 }
 
@@ -1480,12 +1814,14 @@ struct MarchFace {
     bool prot;
 };
 
-template <typename R, int D, int STAGE, bool MM, bool PROT, bool PF2>
-__global__ void __launch_bounds__(256) march_kernel(R* __restrict__ pool, const PatchDev* __restrict__ patches,
+template <typename R, int D, int STAGE, bool MM, bool PROT, bool PF2, bool SH>
+__global__ void __launch_bounds__(256, SH && MM && !PROT && sizeof(R) == 4 ? 4 : 1) march_kernel(R* __restrict__ pool, const PatchDev* __restrict__ patches,
                                                     const WorkItem* __restrict__ work, DevParams prm, Coef<R> cf,
                                                     int cur, const StepConst* __restrict__ sc, int P, int zlo,
-                                                    unsigned long long* __restrict__ nprot) {
+                                                    unsigned long long* __restrict__ nprot,
+                                                    const unsigned* __restrict__ nbr) {
     static_assert(D == 1 || D == 2, "the marching form serves the y and z sweeps");
+    static_assert(!SH || STAGE != 2, "with shared halos the corrector from q^n takes the pencil form");
     constexpr int SA = (D == 1) ? 2 : 1;  // slow transverse axis (x is the fast one)
     constexpr unsigned ES = sizeof(R);
     const WorkItem wi = work[blockIdx.x];
@@ -1511,9 +1847,43 @@ __global__ void __launch_bounds__(256) march_kernel(R* __restrict__ pool, const 
     const __amdgpu_buffer_rsrc_t rw = patch_rsrc(pool + Pt.sbase, (unsigned)F_SCRATCH * VB);  // step intermediates
     const __amdgpu_buffer_rsrc_t rb = (STAGE == 1) ? rs : rw;  // the face field B_D: b^n or b^{n+1/2}
     const unsigned qs = (unsigned)(cur ? F_ST1 : F_ST0) * VB;
-    const unsigned bfo = (STAGE == 1) ? qs + (8 + D) * VB : (unsigned)(F_BH + D) * VB;
-    const unsigned fo = (unsigned)((STAGE == 1 ? F_FL1 : F_FL2) + 7 * D) * VB;
+    // SH: the intermediates' layout without ghosts (strides in words, the field stride in bytes)
+    const unsigned ssw[3] = {1u, (unsigned)Pt.n[0], (unsigned)(Pt.n[0] * Pt.n[1])};
+    const unsigned VW = SH ? scratch_stride(Pt.n[0], Pt.n[1], Pt.n[2]) * ES : VB;
+    const unsigned bfo = (STAGE == 1) ? qs + (8 + D) * VB : (unsigned)(F_BH + D) * VW;
+    const unsigned fo = (unsigned)((STAGE == 1 || (SH && STAGE == 3) ? F_FL1 : F_FL2) + 7 * D) * VW;
     const R z0 = R(0);
+    // SH: the zone's byte offset in its z-layer; it moves on along D, and the
+    // pencil crosses into the patch and out of it at the same zone for all lanes
+    // (Step 1 reads the state, the corrector from records the intermediates)
+    const unsigned* T = SH ? nb_row(nbr, wi.patch) + (STAGE == 1 ? 0 : NBR_SCR) : nullptr;
+    const unsigned sw = STAGE == 1 ? sD : ssw[D] * ES;
+    unsigned zv = 0u;
+    // the pencil's place in the layout without ghosts, at zone 0 along D
+    const unsigned xw = ((unsigned)zc[0] + (unsigned)zc[SA] * ssw[SA]) * ES;
+    int zd = zlo;
+    __amdgpu_buffer_rsrc_t rl = rs;
+    auto enter = [&]() {
+        int q[3] = {zc[0], zc[1], zc[2]};
+        q[D] = zd;
+        const Layer<R> L = nb_layer<R>(T, Pt.n[2], D == 2 ? zd : 0);
+        rl = L.rsrc(pool);
+        zv = L.zone(Pt.n, STAGE == 1 ? st : ssw, q[0], q[1], q[2]);
+    };
+    auto onward = [&]() {
+        zd++;
+        if (zd == 0 || zd == Pt.n[D]) enter();
+        else zv += sw;
+    };
+    // loads of the zone ahead (xz its byte offset; SH: at zv) and of its face field
+    auto fetch = [&](unsigned xz, ZoneRaw<R, STAGE>& z) {
+        auto ld = [&](int, unsigned f) -> R { return bload(z0, rl, zv, f); };
+        if (SH) zone_fetch_sh<R, D, STAGE>(ld, ld, qs, VB, VW, z);
+        else zone_fetch<R, D, STAGE>(rs, rw, xz, st, qs, VB, z);
+    };
+    auto face_field = [&](unsigned xz) -> R {
+        return SH ? bload(z0, rl, zv, bfo) : bload(z0, rb, xz, bfo);
+    };
 
     // Zone s's loads and face field requested one iteration ahead, so that
     // their latency overlaps the previous face's arithmetic: always in FP32
@@ -1524,12 +1894,15 @@ __global__ void __launch_bounds__(256) march_kernel(R* __restrict__ pool, const 
     // 256 VGPRs.
     constexpr bool PF = sizeof(R) == 4 && (STAGE != 2 || PF2);
     MarchFace<R> pv;  // zone s-1 and face s-1
-    pv.rec = zone_phase<R, D, STAGE>(rs, rw, xo, st, qs, VB, cf, prm, scv);
     ZoneRaw<R, STAGE> nx;
+    if (SH) enter();
+    fetch(xo, nx);
+    pv.rec = zone_record<R, D, STAGE>(nx, cf, prm, scv);
     R bfn = R(0);
     if constexpr (PF) {
-        zone_fetch<R, D, STAGE>(rs, rw, xo + sD, st, qs, VB, nx);
-        bfn = bload(z0, rb, xo + sD, bfo);
+        if (SH) onward();
+        fetch(xo + sD, nx);
+        bfn = face_field(xo + sD);
     }
     for (int s = 1; s < P; s++) {
         xo += sD;
@@ -1539,12 +1912,15 @@ __global__ void __launch_bounds__(256) march_kernel(R* __restrict__ pool, const 
             cu.rec = zone_record<R, D, STAGE>(nx, cf, prm, scv);
             bf = bfn;
             if (s + 1 < P) {
-                zone_fetch<R, D, STAGE>(rs, rw, xo + sD, st, qs, VB, nx);
-                bfn = bload(z0, rb, xo + sD, bfo);
+                if (SH) onward();
+                fetch(xo + sD, nx);
+                bfn = face_field(xo + sD);
             }
         } else {
-            cu.rec = zone_phase<R, D, STAGE>(rs, rw, xo, st, qs, VB, cf, prm, scv);
-            bf = bload(z0, rb, xo, bfo);
+            if (SH) onward();
+            fetch(xo, nx);
+            cu.rec = zone_record<R, D, STAGE>(nx, cf, prm, scv);
+            bf = face_field(xo);
         }
         face_phase<R, PROT>(pv.rec, cu.rec, bf, lam, cf, cu.e, cu.alpha, cu.nu, cu.gt, cu.prot);
         if (s >= 2 && s <= P - 2) face_central<R, PROT>(pv.rec, cu.rec, bf, cu.e, cu.prot, cf, cu.cav);
@@ -1558,7 +1934,7 @@ __global__ void __launch_bounds__(256) march_kernel(R* __restrict__ pool, const 
             if (PROT && pv.prot) {
 #pragma unroll
                 for (int r = 0; r < 7; r++) out[r] = pv.cav[r];
-                atomicAdd(nprot, 1ULL);
+                atomicAdd(nprot, SH ? face_copies<STAGE>(zlo + s - 1, Pt.n[D], zc[0], Pt.n[0], zc[SA], Pt.n[SA]) : 1ULL);
             } else {
                 R c[7];
                 auto glim = [&](int k, R& gL, R& gR) {
@@ -1568,7 +1944,9 @@ __global__ void __launch_bounds__(256) march_kernel(R* __restrict__ pool, const 
                 face_correction<R>(glim, pv.e, pv.alpha, pv.nu, cf, c);
                 face_combine(pv.cav, c, il, out);
             }
-            store_flux<R, D>(out, rw, xo - sD, fo, VB);
+            // (face s - 1; its zone in the layout without ghosts moves with s)
+            const unsigned xf = SH ? xw + (unsigned)(zlo + s - 1) * ssw[D] * ES : xo - sD;
+            store_flux<R, D>(out, rw, xf, fo, VW);
         }
         pv = cu;
     }
@@ -1606,15 +1984,15 @@ __global__ void __launch_bounds__(256) march_kernel(R* __restrict__ pool, const 
 __device__ __forceinline__ constexpr int row_a1(int r) { return r < 5 ? r : (r == 5 ? 6 : 5); }
 __device__ __forceinline__ constexpr int row_a2(int r) { return r < 5 ? r : (r == 5 ? 5 : 6); }
 
-template <typename R, int D, bool MM, bool PROT>
+template <typename R, int D, bool MM, bool PROT, bool SH>
 __device__ __forceinline__ void xy_flux(const Rec8<R>* shp, const Rec8<R>* shg, int tid, int step, R bf,
                                         const FaceEig<R>& e, const R alpha[7], const R nu[7], bool prot,
                                         const Coef<R>& cf, R il, __amdgpu_buffer_rsrc_t rw, unsigned xo, unsigned VB,
-                                        unsigned long long* nprot) {
+                                        unsigned long long* nprot, const PatchDev& Pt, int x, int y, int k) {
     R out[7];
     if (PROT && prot) {
         face_central<R, PROT>(shp[tid - step], shp[tid], bf, e, prot, cf, out);
-        atomicAdd(nprot, 1ULL);
+        atomicAdd(nprot, SH ? face_copies<2>(D == 0 ? x : y, Pt.n[D], D == 0 ? y : x, Pt.n[1 - D], k, Pt.n[2]) : 1ULL);
     } else {
         const Rec8<R> Gm = shg[tid - step], G0 = shg[tid], Gp = shg[tid + step];
         R c[7], cav[7];
@@ -1631,11 +2009,11 @@ __device__ __forceinline__ void xy_flux(const Rec8<R>* shp, const Rec8<R>* shg, 
 
 // FP64 blocks stay within 512 threads (the LDS bound of the launch implies
 // it), which leaves the FP64 kernel its 142 VGPRs without spilling.
-template <typename R, bool MM, bool PROT>
-__global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512)
+template <typename R, bool MM, bool PROT, bool SH>
+__global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512, sizeof(R) == 4 ? 6 : 1)
     corr_xy_kernel(R* __restrict__ pool, const PatchDev* __restrict__ patches, const WorkItem* __restrict__ work,
                    DevParams prm, Coef<R> cf, int cur, const StepConst* __restrict__ sc,
-                   unsigned long long* __restrict__ nprot) {
+                   unsigned long long* __restrict__ nprot, const unsigned* __restrict__ nbr) {
     extern __shared__ unsigned char smem_raw[];
     const int P = (int)blockDim.x, RT = (int)blockDim.y;
     Rec8<R>* shp = reinterpret_cast<Rec8<R>*>(smem_raw);  // zone records: x, then y
@@ -1650,18 +2028,51 @@ __global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512)
     const int k = wi.a - XY_BIAS;
     const int y0 = (wi.b & 0xffff) - XY_BIAS, y1 = (wi.b >> 16) - XY_BIAS;
     const int rows = y1 - y0 + 3;  // the band's rows, [y0 - 2, y1]
-    const int x = tx - 3, y = y0 - 2 + ty;
-    const bool live = ty < rows;
-    const bool faces = k >= -1 && k <= Pt.n[2];  // planes of x and y faces (others: z records only)
-    const bool own = live && y >= y0 && y < y1 && y <= Pt.n[1];     // the band's rows within [-1, n_y]
+    const int x = tx - (SH ? 2 : 3), y = y0 - 2 + ty;
+    const int h = SH ? 0 : 1;  // rows and columns formed beyond the patch
+    const bool faces = k >= -h && k < Pt.n[2] + h;  // planes of x and y faces (others: z records only)
+    const bool inx = x >= -h && x < Pt.n[0] + h;
+    // (SH: the corners of the band's halo serve no face and are not read)
+    const bool live = ty < rows && (!SH || inx || (y >= y0 && y < y1));
+    const bool own = live && y >= y0 && y < y1 && y < Pt.n[1] + h;  // the band's rows within [-1, n_y]
     const bool needX = faces && own;                                // x faces of this row
-    const bool needY = faces && live && x >= -1 && x <= Pt.n[0];    // y faces of this column
-    const bool needZ = own && x >= -1 && x <= Pt.n[0];              // the z predictor record
+    const bool needY = faces && live && inx;                        // y faces of this column
+    const bool needZ = own && inx;                                  // the z predictor record
     const int g = prm.ghost;
     const unsigned st[3] = {1u, (unsigned)Pt.N[0], (unsigned)(Pt.N[0] * Pt.N[1])};
     const unsigned xo = live ? ((unsigned)(x + g) + st[1] * (unsigned)(y + g) + st[2] * (unsigned)(k + g)) * ES : 0u;
     const unsigned VB = (unsigned)Pt.vol * ES;
     const StepConst scv = *sc;
+    // SH: the zone and the zones one up along x and y as byte offsets in the
+    // patch's z-layer, the zone above in that of the plane above
+    const unsigned* T = SH ? nb_row(nbr, wi.patch) : nullptr;
+    // the intermediates without ghosts: strides in words, the field stride in
+    // bytes, the thread's own zone (where it has one) as a byte offset
+    const unsigned ssw[3] = {1u, (unsigned)Pt.n[0], (unsigned)(Pt.n[0] * Pt.n[1])};
+    const unsigned VW = SH ? scratch_stride(Pt.n[0], Pt.n[1], Pt.n[2]) * ES : VB;
+    const unsigned xw = SH ? ((unsigned)x + (unsigned)y * ssw[1] + (unsigned)k * ssw[2]) * ES : xo;
+    Layer<R> L{}, Lu{}, Ls{}, Lsu{};  // the state's and the intermediates', of planes k and k + 1
+    unsigned zv = 0u, up[3] = {0u, 0u, 0u}, zs = 0u, us[3] = {0u, 0u, 0u};
+    if (SH) {
+        L = nb_layer<R>(T, Pt.n[2], k), Lu = nb_layer<R>(T, Pt.n[2], k + 1);
+        Ls = nb_layer<R>(T + NBR_SCR, Pt.n[2], k), Lsu = nb_layer<R>(T + NBR_SCR, Pt.n[2], k + 1);
+    }
+    if (SH && live) {
+        zv = L.zone(Pt.n, st, x, y, k);
+        up[0] = L.zone(Pt.n, st, x + 1, y, k);
+        up[1] = L.zone(Pt.n, st, x, y + 1, k);
+        up[2] = Lu.zone(Pt.n, st, x, y, k + 1);
+        zs = Ls.zone(Pt.n, ssw, x, y, k);
+        us[0] = Ls.zone(Pt.n, ssw, x + 1, y, k);
+        us[1] = Ls.zone(Pt.n, ssw, x, y + 1, k);
+        us[2] = Lsu.zone(Pt.n, ssw, x, y, k + 1);
+    }
+    const __amdgpu_buffer_rsrc_t rl = L.rsrc(pool), ru = Lu.rsrc(pool), rls = Ls.rsrc(pool), rus = Lsu.rsrc(pool);
+    // a field of the state and of the intermediates at the zone, and one up along a
+    auto zld = [&](unsigned f) -> R { return bload(R(0), rl, zv, f); };
+    auto uld = [&](int a, unsigned f) -> R { return bload(R(0), a == 2 ? ru : rl, up[a], f); };
+    auto sld = [&](unsigned f) -> R { return bload(R(0), rls, zs, f); };
+    auto usld = [&](int a, unsigned f) -> R { return bload(R(0), a == 2 ? rus : rls, us[a], f); };
     const __amdgpu_buffer_rsrc_t rs = patch_rsrc(pool + Pt.base, (unsigned)F_STATE * VB);     // state
     const __amdgpu_buffer_rsrc_t rw = patch_rsrc(pool + Pt.sbase, (unsigned)F_SCRATCH * VB);  // step intermediates
     const unsigned qs = (unsigned)(cur ? F_ST1 : F_ST0) * VB;
@@ -1672,21 +2083,27 @@ __global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512)
     if (live) {
         ZoneRaw<R, 2> zx, zy;
 #pragma unroll
-        for (int c = 0; c < 8; c++) zx.q[c] = zy.q[c] = bload(z0, rs, xo, qs + c * VB);
+        for (int c = 0; c < 8; c++)
+            zx.q[c] = zy.q[c] = SH ? zld(qs + c * VB) : bload(z0, rs, xo, qs + c * VB);
         const unsigned bs = qs + 8 * VB;
 #pragma unroll
         for (int a = 0; a < 3; a++) {
-            zx.b[a][0] = zy.b[a][0] = bload(z0, rs, xo, bs + a * VB);
-            zx.b[a][1] = zy.b[a][1] = bload(z0, rs, xo, bs + a * VB + st[a] * ES);
+            zx.b[a][0] = zy.b[a][0] = SH ? zld(bs + a * VB) : bload(z0, rs, xo, bs + a * VB);
+            zx.b[a][1] = zy.b[a][1] =
+                SH ? uld(a, bs + a * VB) : bload(z0, rs, xo, bs + a * VB + st[a] * ES);
         }
         R F[3][7][2];  // Step-1 fluxes along x, y, z at the zone and one zone up along their axis
+        // the x flux is read by the y and z predictors, the y flux by the x and z ones, the z flux by the x and y ones
+        const bool use[3] = {inx, own, faces};
 #pragma unroll
         for (int a = 0; a < 3; a++)
+            if (use[a]) {
 #pragma unroll
-            for (int r = 0; r < 7; r++) {
-                const unsigned fo = (unsigned)(F_FL1 + 7 * a + r) * VB;
-                F[a][r][0] = bload(z0, rw, xo, fo);
-                F[a][r][1] = bload(z0, rw, xo, fo + st[a] * ES);
+                for (int r = 0; r < 7; r++) {
+                    const unsigned fo = (unsigned)(F_FL1 + 7 * a + r) * VW;
+                    F[a][r][0] = SH ? sld(fo) : bload(z0, rw, xo, fo);
+                    F[a][r][1] = SH ? usld(a, fo) : bload(z0, rw, xo, fo + st[a] * ES);
+                }
             }
         // x predictor: transverse axes y (A1) and z (A2); y predictor: z (A1) and x (A2)
 #pragma unroll
@@ -1715,7 +2132,7 @@ __global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512)
                 }
             const Rec8<R> rz = zone_record<R, 2, 2>(zz, cf, prm, scv);
 #pragma unroll
-            for (int r = 0; r < 7; r++) bstore(rz.v[r], rw, xo, (unsigned)(F_FL2 + 14 + r) * VB);
+            for (int r = 0; r < 7; r++) bstore(rz.v[r], rw, xw, (unsigned)(F_FL2 + 14 + r) * VW);
         }
         // the z record first (stored at once), so that its temporaries are
         // dead before the x and y records are formed
@@ -1734,15 +2151,15 @@ __global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512)
         bool prot = false;
         const bool face = needX && tx >= 1;
         if (face) {
-            bf = bload(z0, rw, xo, (unsigned)F_BH * VB);
+            bf = SH ? sld((unsigned)F_BH * VW) : bload(z0, rw, xo, (unsigned)F_BH * VB);
             Rec8<R> gr;
             face_phase<R, PROT>(shp[tid - 1], shp[tid], bf, sc_lam(scv, 0, R(0)), cf, e, alpha, nu, gr, prot);
             shg[tid] = gr;
         }
         __syncthreads();
         if (face && tx >= 2 && tx <= P - 2)
-            xy_flux<R, 0, MM, PROT>(shp, shg, tid, 1, bf, e, alpha, nu, prot, cf, sc_il(scv, 0, R(0)), rw, xo, VB,
-                                    nprot);
+            xy_flux<R, 0, MM, PROT, SH>(shp, shg, tid, 1, bf, e, alpha, nu, prot, cf, sc_il(scv, 0, R(0)), rw, xw, VW,
+                                        nprot, Pt, x, y, k);
     }
     __syncthreads();  // the x records and g-tilde are read
     if (needY) shp[tid] = ry;
@@ -1756,15 +2173,15 @@ __global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512)
         bool prot = false;
         const bool face = needY && ty >= 1;
         if (face) {
-            bf = bload(z0, rw, xo, (unsigned)(F_BH + 1) * VB);
+            bf = SH ? sld((unsigned)(F_BH + 1) * VW) : bload(z0, rw, xo, (unsigned)(F_BH + 1) * VB);
             Rec8<R> gr;
             face_phase<R, PROT>(shp[tid - P], shp[tid], bf, sc_lam(scv, 1, R(0)), cf, e, alpha, nu, gr, prot);
             shg[tid] = gr;
         }
         __syncthreads();
         if (face && ty >= 2 && ty <= rows - 2)
-            xy_flux<R, 1, MM, PROT>(shp, shg, tid, P, bf, e, alpha, nu, prot, cf, sc_il(scv, 1, R(0)), rw, xo, VB,
-                                    nprot);
+            xy_flux<R, 1, MM, PROT, SH>(shp, shg, tid, P, bf, e, alpha, nu, prot, cf, sc_il(scv, 1, R(0)), rw, xw, VW,
+                                        nprot, Pt, x, y, k);
     }
 }
 
@@ -1957,9 +2374,14 @@ hipError_t launch_set_dt(StepConst* sc, double dt, const DevParams& prm, hipStre
 
 template <typename R>
 hipError_t launch_ct_half(void* pool, const PatchDev* pt, const WorkItem* wk, int nblk, const Coef<R>& cf, int g, int cur,
-                          const StepConst* sc, hipStream_t st) {
+                          const StepConst* sc, SharedHalo sh, hipStream_t st) {
     if (nblk <= 0) return hipSuccess;
-    hipLaunchKernelGGL(ct_half_kernel<R>, dim3(nblk), dim3(TILE_THREADS), 0, st, (R*)pool, pt, wk, cf, g, cur, sc);
+    if (sh.nbr)
+        hipLaunchKernelGGL((ct_half_kernel<R, true>), dim3(nblk), dim3(TILE_THREADS), 0, st, (R*)pool, pt, wk, cf, g, cur,
+                           sc, sh.nbr);
+    else
+        hipLaunchKernelGGL((ct_half_kernel<R, false>), dim3(nblk), dim3(TILE_THREADS), 0, st, (R*)pool, pt, wk, cf, g,
+                           cur, sc, sh.nbr);
     return hipGetLastError();
 }
 
@@ -1976,9 +2398,14 @@ int resident_blocks(K kernel, int threads) {
     return per_cu * cus;
 }
 template <typename R>
-int ct_half_resident() { return resident_blocks(ct_half_kernel<R>, TILE_THREADS); }
+int ct_half_resident(bool sh) {
+    return sh ? resident_blocks(ct_half_kernel<R, true>, TILE_THREADS) : resident_blocks(ct_half_kernel<R, false>, TILE_THREADS);
+}
 template <typename R>
-int update_resident(int threads) { return resident_blocks(update_kernel<R, false>, threads); }
+int update_resident(int threads, bool sh) {
+    return sh ? resident_blocks(update_kernel<R, false, true>, threads)
+              : resident_blocks(update_kernel<R, false, false>, threads);
+}
 
 // queue != nullptr: the persistent form, with as many blocks as are
 // resident at once (a multiple of 8), over a list of nblk items (a multiple
@@ -1986,42 +2413,50 @@ int update_resident(int threads) { return resident_blocks(update_kernel<R, false
 template <typename R>
 hipError_t launch_update(void* pool, const PatchDev* pt, const WorkItem* wk, int nblk, const DevParams& prm,
                          const Coef<R>& cf, int cur, const StepConst* sc, unsigned long long* nfl, unsigned long long* smax,
-                         int keep_edges, int threads, unsigned int* queue, hipStream_t st) {
+                         int keep_edges, int threads, unsigned int* queue, SharedHalo sh, int fz_slot, StepConst* sc_used,
+                         hipStream_t st) {
     if (nblk <= 0) return hipSuccess;
     if (threads < 64 || threads > UpdTile<R>::threads || threads % 64) return hipErrorInvalidValue;
-    if (!queue) {
-        hipLaunchKernelGGL((update_kernel<R, false>), dim3(nblk), dim3(threads), 0, st, (R*)pool, pt, wk, nblk, queue,
-                           prm, cf, cur, sc, nfl, smax, keep_edges);
+    if (sh.nbr && keep_edges) return hipErrorInvalidValue;
+    auto go = [&](auto kernel, int grid) -> hipError_t {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, st, (R*)pool, pt, wk, nblk, queue, prm, cf, cur, sc, nfl,
+                           smax, keep_edges, sh.nbr, fz_slot, sc_used);
         return hipGetLastError();
-    }
+    };
+    if (!queue) return sh.nbr ? go(update_kernel<R, false, true>, nblk) : go(update_kernel<R, false, false>, nblk);
     if (nblk % 8) return hipErrorInvalidValue;
-    int dev = 0, per_cu = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)update_kernel<R, true>, threads, 0);
-    if (e != hipSuccess) return e;
-    int grid = per_cu * cus;
-    grid -= grid % 8;
-    if (grid < 8) grid = 8;
-    if (grid > nblk) grid = nblk;
-    hipLaunchKernelGGL((update_kernel<R, true>), dim3(grid), dim3(threads), 0, st, (R*)pool, pt, wk, nblk, queue, prm,
-                       cf, cur, sc, nfl, smax, keep_edges);
-    return hipGetLastError();
+    auto queued = [&](auto kernel) -> hipError_t {
+        int dev = 0, per_cu = 0, cus = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kernel, threads, 0);
+        if (e != hipSuccess) return e;
+        int grid = per_cu * cus;
+        grid -= grid % 8;
+        if (grid < 8) grid = 8;
+        if (grid > nblk) grid = nblk;
+        return go(kernel, grid);
+    };
+    return sh.nbr ? queued(update_kernel<R, true, true>) : queued(update_kernel<R, true, false>);
 }
 
 template <typename R>
 hipError_t launch_sweep(int d, int stage, void* pool, const PatchDev* pt, const WorkItem* wk, int nblk, const DevParams& prm,
                         const Coef<R>& cf, int cur, const StepConst* sc, int P, int W, int zlo,
-                        unsigned long long* nprot, hipStream_t st) {
+                        unsigned long long* nprot, SharedHalo sh, hipStream_t st) {
     if (nblk <= 0) return hipSuccess;
     size_t shmem = sizeof(R) * 16 * (size_t)P * W;
     dim3 blk = (d == 0) ? dim3(P, W) : dim3(W, P);
     const bool mm = cf.beta_l == R(1);
     const bool pr = cf.rho_prot > R(0) || cf.p_prot > R(0);
+#define WMB_SW2(DD, SS, MM, PR, SH)                                                                                   \
+    hipLaunchKernelGGL((sweep_kernel<R, DD, SS, MM, PR, SH>), dim3(nblk), blk, shmem, st, (R*)pool, pt, wk, prm, cf, cur, \
+                       sc, P, W, zlo, nprot, sh.nbr)
 #define WMB_SW1(DD, SS, MM, PR)                                                                                       \
-    hipLaunchKernelGGL((sweep_kernel<R, DD, SS, MM, PR>), dim3(nblk), blk, shmem, st, (R*)pool, pt, wk, prm, cf, cur, sc, \
-                       P, W, zlo, nprot)
+    do {                                                                                                              \
+        if (sh.nbr) WMB_SW2(DD, SS, MM, PR, true);                                                                    \
+        else WMB_SW2(DD, SS, MM, PR, false);                                                                          \
+    } while (0)
 #define WMB_SW(DD, SS)                                                                                                \
     do {                                                                                                              \
         if (mm && !pr) WMB_SW1(DD, SS, true, false);                                                                  \
@@ -2041,6 +2476,7 @@ hipError_t launch_sweep(int d, int stage, void* pool, const PatchDev* pt, const 
         else if (d == 1) WMB_SW(1, 2);
         else WMB_SW(2, 2);
     }
+#undef WMB_SW2
 #undef WMB_SW1
 #undef WMB_SW
     return hipGetLastError();
@@ -2051,7 +2487,7 @@ hipError_t launch_sweep(int d, int stage, void* pool, const PatchDev* pt, const 
 template <typename R>
 hipError_t launch_march(int d, int stage, void* pool, const PatchDev* pt, const WorkItem* wk, int nblk, const DevParams& prm,
                         const Coef<R>& cf, int cur, const StepConst* sc, int P, int W, int zlo,
-                        unsigned long long* nprot, hipStream_t st) {
+                        unsigned long long* nprot, SharedHalo sh, hipStream_t st) {
     if (nblk <= 0) return hipSuccess;
     // W > 512: the corrector with the one-zone-ahead loads (FP32), W - 512 pencils a block
     // (stage 3, the corrector from stored records, issues them ahead always in FP32)
@@ -2060,18 +2496,25 @@ hipError_t launch_march(int d, int stage, void* pool, const PatchDev* pt, const 
     if (d < 1 || d > 2 || W < 1 || W > 256) return hipErrorInvalidValue;
     const bool mm = cf.beta_l == R(1);
     const bool pr = cf.rho_prot > R(0) || cf.p_prot > R(0);
+#define WMB_MA2(DD, SS, MM, PR, PF, SH)                                                                             \
+    hipLaunchKernelGGL((march_kernel<R, DD, SS, MM, PR, PF, SH>), dim3(nblk), dim3(W), 0, st, (R*)pool, pt, wk, prm, cf, \
+                       cur, sc, P, zlo, nprot, sh.nbr)
 #define WMB_MA1(DD, SS, MM, PR)                                                                                     \
     do {                                                                                                            \
-        if (pf)                                                                                                     \
-            hipLaunchKernelGGL((march_kernel<R, DD, SS, MM, PR, true>), dim3(nblk), dim3(W), 0, st, (R*)pool, pt, wk, \
-                               prm, cf, cur, sc, P, zlo, nprot);                                                    \
-        else                                                                                                        \
-            hipLaunchKernelGGL((march_kernel<R, DD, SS, MM, PR, false>), dim3(nblk), dim3(W), 0, st, (R*)pool, pt,    \
-                               wk, prm, cf, cur, sc, P, zlo, nprot);                                                \
+        if constexpr ((SS) == 1) {                                                                                  \
+            if (sh.nbr) WMB_MA2(DD, SS, MM, PR, false, true);                                                       \
+            else WMB_MA2(DD, SS, MM, PR, false, false);                                                             \
+        } else {                                                                                                    \
+            if (sh.nbr) return hipErrorInvalidValue;                                                                \
+            if (pf) WMB_MA2(DD, SS, MM, PR, true, false);                                                           \
+            else WMB_MA2(DD, SS, MM, PR, false, false);                                                             \
+        }                                                                                                           \
     } while (0)
 #define WMB_MA3(MM, PR)                                                                                             \
-    hipLaunchKernelGGL((march_kernel<R, 2, 3, MM, PR, false>), dim3(nblk), dim3(W), 0, st, (R*)pool, pt, wk, prm,   \
-                       cf, cur, sc, P, zlo, nprot)
+    do {                                                                                                            \
+        if (sh.nbr) WMB_MA2(2, 3, MM, PR, false, true);                                                             \
+        else WMB_MA2(2, 3, MM, PR, false, false);                                                                   \
+    } while (0)
 #define WMB_MA(DD, SS)                                                                                              \
     do {                                                                                                            \
         if (mm && !pr) WMB_MA1(DD, SS, true, false);                                                                \
@@ -2093,6 +2536,7 @@ hipError_t launch_march(int d, int stage, void* pool, const PatchDev* pt, const 
         if (d == 1) WMB_MA(1, 2);
         else WMB_MA(2, 2);
     }
+#undef WMB_MA2
 #undef WMB_MA1
 #undef WMB_MA3
 #undef WMB_MA
@@ -2103,20 +2547,26 @@ hipError_t launch_march(int d, int stage, void* pool, const PatchDev* pt, const 
 template <typename R>
 hipError_t launch_corr_xy(void* pool, const PatchDev* pt, const WorkItem* wk, int nblk, const DevParams& prm,
                           const Coef<R>& cf, int cur, const StepConst* sc, int P, int RT, unsigned long long* nprot,
-                          hipStream_t st) {
+                          SharedHalo sh, hipStream_t st) {
     if (nblk <= 0) return hipSuccess;
     // FP64 blocks stay within 512 threads (the kernel's launch bound), which the LDS bound implies
     if (P < 1 || RT < 4 || P * RT > 1024 || sizeof(R) * 16 * (size_t)P * RT > 64 * 1024) return hipErrorInvalidValue;
     const size_t shmem = sizeof(R) * 16 * (size_t)P * RT;
     const bool mm = cf.beta_l == R(1);
     const bool pr = cf.rho_prot > R(0) || cf.p_prot > R(0);
+#define WMB_XY2(MM, PR, SH)                                                                                         \
+    hipLaunchKernelGGL((corr_xy_kernel<R, MM, PR, SH>), dim3(nblk), dim3(P, RT), shmem, st, (R*)pool, pt, wk, prm, cf, \
+                       cur, sc, nprot, sh.nbr)
 #define WMB_XY(MM, PR)                                                                                              \
-    hipLaunchKernelGGL((corr_xy_kernel<R, MM, PR>), dim3(nblk), dim3(P, RT), shmem, st, (R*)pool, pt, wk, prm, cf, \
-                       cur, sc, nprot)
+    do {                                                                                                            \
+        if (sh.nbr) WMB_XY2(MM, PR, true);                                                                          \
+        else WMB_XY2(MM, PR, false);                                                                                \
+    } while (0)
     if (mm && !pr) WMB_XY(true, false);
     else if (mm) WMB_XY(true, true);
     else if (!pr) WMB_XY(false, false);
     else WMB_XY(false, true);
+#undef WMB_XY2
 #undef WMB_XY
     return hipGetLastError();
 }
@@ -2138,21 +2588,21 @@ hipError_t launch_diag(const void* pool, const PatchDev* pt, const WorkItem* wk,
     template hipError_t launch_dt_reduce<R>(void*, const PatchDev*, const WorkItem*, int, const DevParams&, int,         \
                                             unsigned long long*, hipStream_t);                                           \
     template hipError_t launch_ct_half<R>(void*, const PatchDev*, const WorkItem*, int, const Coef<R>&, int, int,        \
-                                          const StepConst*, hipStream_t);                                                \
+                                          const StepConst*, SharedHalo, hipStream_t);                                    \
     template hipError_t launch_update<R>(void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, \
                                          int, const StepConst*, unsigned long long*, unsigned long long*, int, int,     \
-                                         unsigned int*, hipStream_t);                                                    \
+                                         unsigned int*, SharedHalo, int, StepConst*, hipStream_t);                       \
     template hipError_t launch_sweep<R>(int, int, void*, const PatchDev*, const WorkItem*, int, const DevParams&,        \
                                         const Coef<R>&, int, const StepConst*, int, int, int, unsigned long long*,       \
-                                        hipStream_t);                                                                    \
+                                        SharedHalo, hipStream_t);                                                        \
     template hipError_t launch_march<R>(int, int, void*, const PatchDev*, const WorkItem*, int, const DevParams&,        \
                                         const Coef<R>&, int, const StepConst*, int, int, int, unsigned long long*,       \
-                                        hipStream_t);                                                                    \
+                                        SharedHalo, hipStream_t);                                                        \
     template hipError_t launch_corr_xy<R>(void*, const PatchDev*, const WorkItem*, int, const DevParams&,           \
                                           const Coef<R>&, int, const StepConst*, int, int, unsigned long long*,         \
-                                          hipStream_t);                                                                  \
-    template int ct_half_resident<R>();                                                                                 \
-    template int update_resident<R>(int);                                                                               \
+                                          SharedHalo, hipStream_t);                                                      \
+    template int ct_half_resident<R>(bool);                                                                               \
+    template int update_resident<R>(int, bool);                                                                            \
     template hipError_t launch_diag<R>(const void*, const PatchDev*, const WorkItem*, int, const DevParams&, int,        \
                                        double*, const unsigned long long*, double, double, double*, hipStream_t);
 WMB_INST(float)

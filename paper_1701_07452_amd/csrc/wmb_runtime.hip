@@ -22,13 +22,13 @@ template <typename R> hipError_t launch_dt_reduce(void*, const PatchDev*, const 
 hipError_t launch_dt_finalize(unsigned long long*, StepConst*, const DevParams&, hipStream_t);
 hipError_t launch_set_dt(StepConst*, double, const DevParams&, hipStream_t);
 hipError_t launch_set_patch(PatchDev*, int, const PatchDev&, hipStream_t);
-template <typename R> hipError_t launch_ct_half(void*, const PatchDev*, const WorkItem*, int, const Coef<R>&, int, int, const StepConst*, hipStream_t);
-template <typename R> hipError_t launch_update(void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, unsigned long long*, unsigned long long*, int, int, unsigned int*, hipStream_t);
-template <typename R> hipError_t launch_sweep(int, int, void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, int, int, int, unsigned long long*, hipStream_t);
-template <typename R> hipError_t launch_corr_xy(void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, int, int, unsigned long long*, hipStream_t);
-template <typename R> hipError_t launch_march(int, int, void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, int, int, int, unsigned long long*, hipStream_t);
-template <typename R> int ct_half_resident();
-template <typename R> int update_resident(int);
+template <typename R> hipError_t launch_ct_half(void*, const PatchDev*, const WorkItem*, int, const Coef<R>&, int, int, const StepConst*, SharedHalo, hipStream_t);
+template <typename R> hipError_t launch_update(void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, unsigned long long*, unsigned long long*, int, int, unsigned int*, SharedHalo, int, StepConst*, hipStream_t);
+template <typename R> hipError_t launch_sweep(int, int, void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, int, int, int, unsigned long long*, SharedHalo, hipStream_t);
+template <typename R> hipError_t launch_corr_xy(void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, int, int, unsigned long long*, SharedHalo, hipStream_t);
+template <typename R> hipError_t launch_march(int, int, void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, int, int, int, unsigned long long*, SharedHalo, hipStream_t);
+template <typename R> int ct_half_resident(bool);
+template <typename R> int update_resident(int, bool);
 template <typename R> hipError_t launch_diag(const void*, const PatchDev*, const WorkItem*, int, const DevParams&, int, double*, const unsigned long long*, double, double, double*, hipStream_t);
 }  // namespace wmb
 
@@ -57,7 +57,16 @@ struct SweepGroup {
     int RT = 0;
     DevList wxy;
     std::vector<DevList> wxyg;
+    // shared-halo steps (see shared_now): pencils of n + 3 zones [-2, n] over
+    // the patch's own rows and columns.  The corrector from q^n takes the
+    // pencil form (Ws); the z corrector from records any shape (W3).
+    int Ws = 0, W3 = 0;
+    DevList wls, wl3;
+    int RTs = 0;
+    DevList wxys;
+    int Ps() const { return n + 3; }
 };
+constexpr int ZLO_S = -2;
 
 // What the device signal-speed maximum (smax) holds relative to the current state.
 enum SmaxState { SMAX_ZERO = 0, SMAX_CLEAN = 1, SMAX_DIRTY = 2 };
@@ -98,6 +107,13 @@ struct wmb_ctx {
     int ngroups = 1;
     std::vector<int> pgroup;  // patch -> step group
     std::vector<DevList> wl_cth_g, wl_upd_g;  // per step group (sized for ngroups)
+    // shared-halo steps: the neighbour table (nullptr: this batch cannot),
+    // the tile lists over the patches' own zones, and what they leave undone
+    unsigned* d_nbr = nullptr;
+    DevList wl_cth_s, wl_upd_s;
+    bool all_in = true;          // every patch present and active (as of the last plan)
+    bool xg_lazy = false;        // the last step was a shared one: the x-ghosts are written when asked for
+    bool stages_shared = false;  // and its intermediates cover the patches' own zones only
     bool serial = false;  // scratch groups: the groups' steps run one after another on the main stream
     hipStream_t gstream[4] = {};  // group streams 1..3 (group 0 runs on the main stream), borrowed
     hipEvent_t ev_g[4] = {};
@@ -122,8 +138,9 @@ struct wmb_ctx {
     double* d_diag_out = nullptr;  // the 12 diagnostics outputs
     double* noalloc_rec = nullptr; // this device's copy of the static records (wmb_diagnostics_noalloc)
     long long nzones = 0;          // interior zones of the batch
-    hipGraphExec_t gexec[2] = {nullptr, nullptr};
-    hipGraph_t graph[2] = {nullptr, nullptr};
+    // captured steps: by the state copy they start from, + 2 for shared-halo steps
+    hipGraphExec_t gexec[4] = {};
+    hipGraph_t graph[4] = {};
     std::string err;
     std::vector<void*> owned;  // library-owned device allocations
     hipEvent_t* marks = nullptr;  // when set, an event is recorded after every kernel class
@@ -278,6 +295,30 @@ std::vector<WorkItem> xcd_order(const std::vector<WorkItem>& items, const std::v
     for (int u : byload)
         for (int i = start[u]; i < start[u + 1]; i++) out[NXCD * pos[xcd[u]]++ + xcd[u]] = items[byunit[i]];
     return out;
+}
+
+// The order of shared-halo lists whose blocks read across x: the first items
+// of all patches, then the second ones and so on, dealt in whole x-rows.  A
+// block reads two or three zones a row from its x-neighbours, in cache lines
+// of their own, which are the lines the neighbours' blocks read whole; with
+// the same planes of an x-row in flight on one XCD its L2 holds them already.
+// Measured at 512 x 32^3 FP32, x-rows patch by patch / patches dealt alone /
+// in turn: the fused corrector 1.34 / 1.25 / 1.19 ms, the Step-1 x sweep 0.41
+// / 0.39 / 0.36, the update 1.12 / 1.24 / 1.11, the step 4.21 / 4.24 / 4.03.
+std::vector<WorkItem> in_turn(const std::vector<WorkItem>& items, const std::vector<int>& rows) {
+    std::vector<int> nth(items.size()), count;
+    int most = 0;
+    for (size_t i = 0; i < items.size(); i++) {
+        if (items[i].patch >= (int)count.size()) count.resize(items[i].patch + 1, 0);
+        nth[i] = count[items[i].patch]++;
+        most = std::max(most, nth[i] + 1);
+    }
+    std::vector<int> at(most + 1, 0);
+    for (int t : nth) at[t + 1]++;
+    for (int t = 0; t < most; t++) at[t + 1] += at[t];
+    std::vector<WorkItem> out(items.size());
+    for (size_t i = 0; i < items.size(); i++) out[at[nth[i]]++] = items[i];
+    return xcd_order(out, &rows);
 }
 
 template <typename T>
@@ -468,14 +509,39 @@ void mark(wmb_ctx* c) {
     if (c->marks) c->nmark++;
 }
 
+// Shared-halo steps.  Where every patch of the batch is stepped together and
+// none ends at a domain boundary, the halo of a patch is other patches' own
+// zones: each face, edge and predictor state is formed once, by the patch
+// that owns it, and read from there, instead of being formed again by every
+// patch whose ghost region holds it (a 32^3 patch forms 1.6 times its own
+// Step-1 faces, a 16^3 one 2.5 times), and a step needs no ghost exchange.
+// The same arithmetic on the same values, so results are bitwise those of
+// the halo scheme, which serves frozen and absent patches, domain boundaries,
+// uneven batches, patch groups and kept stages, and pools of 2^32 words and
+// more.
+//   Without ghosts the intermediates also lie in whole cache lines
+// (scratch_stride): with the halo scheme's layout (rows of 40 words from 16 B
+// into a line at 32^3, stored by parts of lines) the shared sweeps took 0.57 /
+// 0.48 / 0.47 ms at 512 x 32^3 FP32 and 50-65% of the vector issue, without
+// ghosts 0.36 / 0.34 / 0.33 ms and 91-97%.  Measured, halo / shared, ms a step:
+// 512 x 32^3 FP32 6.18 / 3.92, FP64 12.3 / 9.17, 512 x 16^3 FP32 1.20 / 0.60,
+// 64 x 64^3 FP32 5.25 / 3.66.
+bool shared_now(const wmb_ctx* c) {
+    return c->d_nbr && c->all_in && c->ngroups == 1 && !c->serial && !c->keep_edges;
+}
+SharedHalo shared_arg(const wmb_ctx* c, bool sh) { return SharedHalo{sh ? c->d_nbr : nullptr}; }
+
+// one sweep group's launch in its form, over list L (sh: the group's own
+// shared list instead)
 template <typename R>
 hipError_t launch_group(wmb_ctx* c, int d, int stage, const SweepGroup& G, const DevList& L, int cur,
-                        unsigned long long* nprot, hipStream_t st) {
-    if (G.W < 0)
-        return launch_march<R>(d, stage, c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), cur, c->d_sc, G.P, -G.W,
-                               G.zlo, nprot, st);
-    return launch_sweep<R>(d, stage, c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), cur, c->d_sc, G.P, G.W, G.zlo,
-                           nprot, st);
+                        unsigned long long* nprot, hipStream_t st, bool sh) {
+    const int W = sh ? (stage == 3 ? G.W3 : G.Ws) : G.W, P = sh ? G.Ps() : G.P, zlo = sh ? ZLO_S : G.zlo;
+    if (W < 0)
+        return launch_march<R>(d, stage, c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), cur, c->d_sc, P, -W, zlo,
+                               nprot, shared_arg(c, sh), st);
+    return launch_sweep<R>(d, stage, c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), cur, c->d_sc, P, W, zlo, nprot,
+                           shared_arg(c, sh), st);
 }
 
 // with the fused x/y corrector on, the z predictor records it stores are
@@ -485,9 +551,10 @@ bool zrec(const wmb_ctx* c) { return c->xy_rows > 0; }
 // the z corrector sweeps of one group's list: from the stored records after
 // the fused x/y corrector, else from q^n and the Step-1 fluxes
 template <typename R>
-hipError_t launch_corr_z(wmb_ctx* c, int g, int cur, unsigned long long* nprot, hipStream_t st) {
+hipError_t launch_corr_z(wmb_ctx* c, int g, int cur, unsigned long long* nprot, hipStream_t st, bool sh) {
     for (auto& G : c->sweeps[2][1]) {
-        hipError_t r = launch_group<R>(c, 2, zrec(c) ? 3 : 2, G, g < 0 ? G.wl : G.wlg[g], cur, nprot, st);
+        const DevList& L = sh ? (zrec(c) ? G.wl3 : G.wls) : (g < 0 ? G.wl : G.wlg[g]);
+        hipError_t r = launch_group<R>(c, 2, zrec(c) ? 3 : 2, G, L, cur, nprot, st, sh);
         if (r != hipSuccess) return r;
     }
     return hipSuccess;
@@ -496,15 +563,15 @@ hipError_t launch_corr_z(wmb_ctx* c, int g, int cur, unsigned long long* nprot, 
 // the corrector's x sweeps of one group's list (wl: all patches; g >= 0: step
 // group g), as the fused x/y kernel when xy_rows > 0
 template <typename R>
-hipError_t launch_corr_x(wmb_ctx* c, int g, int cur, unsigned long long* nprot, hipStream_t st) {
+hipError_t launch_corr_x(wmb_ctx* c, int g, int cur, unsigned long long* nprot, hipStream_t st, bool sh) {
     for (auto& G : c->sweeps[0][1]) {
         hipError_t r;
         if (c->xy_rows > 0) {
-            const DevList& L = g < 0 ? G.wxy : G.wxyg[g];
-            r = launch_corr_xy<R>(c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), cur, c->d_sc, G.P, G.RT, nprot,
-                                  st);
+            const DevList& L = sh ? G.wxys : (g < 0 ? G.wxy : G.wxyg[g]);
+            r = launch_corr_xy<R>(c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), cur, c->d_sc, sh ? G.Ps() : G.P,
+                                  sh ? G.RTs : G.RT, nprot, shared_arg(c, sh), st);
         } else {
-            r = launch_group<R>(c, 0, 2, G, g < 0 ? G.wl : G.wlg[g], cur, nprot, st);
+            r = launch_group<R>(c, 0, 2, G, sh ? G.wls : (g < 0 ? G.wl : G.wlg[g]), cur, nprot, st, sh);
         }
         if (r != hipSuccess) return r;
     }
@@ -528,7 +595,7 @@ int run_fill(wmb_ctx* c, int mask) {
     const int nw[3] = {c->wl_fill[0].n, c->wl_fill[1].n, c->wl_fill[2].n};
     hipError_t e = launch_fill<R>(c->pool, c->d_patch, wl, nw, c->p.ghost, c->cur, mask, c->stream);
     if (e != hipSuccess) return fail(c, WMB_EHIP, std::string("fill_ghosts: ") + hipGetErrorString(e));
-    if (mask & FILL_X) c->xg_valid = true;
+    if (mask & FILL_X) c->xg_valid = true, c->xg_lazy = false;
     mark(c);
     return WMB_OK;
 }
@@ -551,11 +618,6 @@ int run_finalize(wmb_ctx* c) {
     return WMB_OK;
 }
 
-// one sweep group's launch in its form
-template <typename R>
-hipError_t launch_group(wmb_ctx* c, int d, int stage, const SweepGroup& G, const DevList& L, int cur,
-                        unsigned long long* nprot, hipStream_t st);
-
 // One step.  split (the captured graph): the y/z ghost exchange was forked
 // onto the side stream (ev_join marks its end).  The three sweeps of a stage
 // are independent (each writes its own flux array), so they run as three
@@ -565,17 +627,25 @@ hipError_t launch_group(wmb_ctx* c, int d, int stage, const SweepGroup& G, const
 // both on the main stream).  The Step-1 x sweep
 // first covers the pencils whose transverse coords are interior, which read
 // only the x-ghosts the previous update wrote, then waits for the exchange
-// and covers the frame.
+// and covers the frame.  Shared-halo steps are captured unsplit.
+void stepped(wmb_ctx* c, bool sh) {  // what a step leaves beside the new state
+    c->edges_kept = c->keep_edges;
+    c->xg_valid = !sh;  // the halo scheme's update wrote the x-ghosts of the new copy
+    c->xg_lazy = sh;
+    c->stages_shared = sh;
+}
+
 template <typename R>
 int run_step(wmb_ctx* c, bool split = false) {
     hipError_t e;
     const int cur = c->cur;
+    const bool sh = shared_now(c);
+    const SharedHalo sa = shared_arg(c, sh);
 #define STEPCK(what)                                                                        \
     if (e != hipSuccess) return fail(c, WMB_EHIP, std::string(what) + ": " + hipGetErrorString(e))
     auto sweeps = [&](int d, int stage, const DevList SweepGroup::*wl, hipStream_t st) -> hipError_t {
         for (auto& G : c->sweeps[d][stage - 1]) {
-            const DevList& L = G.*wl;
-            hipError_t r = launch_group<R>(c, d, stage, G, L, cur, c->d_nfloor + 1, st);
+            hipError_t r = launch_group<R>(c, d, stage, G, sh ? G.wls : G.*wl, cur, c->d_nfloor + 1, st, sh);
             if (r != hipSuccess) return r;
         }
         return hipSuccess;
@@ -608,7 +678,8 @@ int run_step(wmb_ctx* c, bool split = false) {
             mark(c);
         }
     }
-    e = launch_ct_half<R>(c->pool, c->d_patch, c->wl_cth.d, c->wl_cth.n, coef<R>(c), c->p.ghost, cur, c->d_sc, c->stream);
+    const DevList& lc = sh ? c->wl_cth_s : c->wl_cth;
+    e = launch_ct_half<R>(c->pool, c->d_patch, lc.d, lc.n, coef<R>(c), c->p.ghost, cur, c->d_sc, sa, c->stream);
     STEPCK("ct_half");
     mark(c);
     if (split) {
@@ -622,35 +693,35 @@ int run_step(wmb_ctx* c, bool split = false) {
             STEPCK("sweep2");
         }
         if (!zrec(c)) {
-            e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + 1, c->side2);
+            e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + 1, c->side2, sh);
             STEPCK("sweep2");
         }
         CKH(hipEventRecord(c->ev_br[3], c->side));
         CKH(hipEventRecord(c->ev_br[4], c->side2));
-        e = launch_corr_x<R>(c, -1, cur, c->d_nfloor + 1, c->stream);
+        e = launch_corr_x<R>(c, -1, cur, c->d_nfloor + 1, c->stream, sh);
         STEPCK("sweep2");
         if (zrec(c)) {
-            e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + 1, c->stream);
+            e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + 1, c->stream, sh);
             STEPCK("sweep2");
         }
         CKH(hipStreamWaitEvent(c->stream, c->ev_br[3], 0));
         CKH(hipStreamWaitEvent(c->stream, c->ev_br[4], 0));
     } else {
         for (int d = 0; d < 3; d++) {
-            if (d == 0) e = launch_corr_x<R>(c, -1, cur, c->d_nfloor + 1, c->stream);
-            else if (d == 2) e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + 1, c->stream);
+            if (d == 0) e = launch_corr_x<R>(c, -1, cur, c->d_nfloor + 1, c->stream, sh);
+            else if (d == 2) e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + 1, c->stream, sh);
             else if (!c->xy_rows) e = sweeps(d, 2, &SweepGroup::wl, c->stream);
             STEPCK("sweep2");
             mark(c);
         }
     }
-    e = launch_update<R>(c->pool, c->d_patch, c->wl_upd.d, c->wl_upd.n, c->dp, coef<R>(c), cur, c->d_sc, c->d_nfloor,
-                         c->d_smax, c->keep_edges ? 1 : 0, c->upd_zones, c->upd_queue ? c->d_queue : nullptr,
-                         c->stream);
+    const DevList& lu = sh ? c->wl_upd_s : c->wl_upd;
+    e = launch_update<R>(c->pool, c->d_patch, lu.d, lu.n, c->dp, coef<R>(c), cur, c->d_sc, c->d_nfloor, c->d_smax,
+                         c->keep_edges ? 1 : 0, c->upd_zones, c->upd_queue ? c->d_queue : nullptr, sa,
+                         zrec(c) ? F_FL1 + 14 : F_FL2 + 14, c->d_sc + 1, c->stream);
     STEPCK("update");
     mark(c);
-    c->edges_kept = c->keep_edges;
-    c->xg_valid = true;  // the update wrote the x-ghosts of the new copy
+    stepped(c, sh);
 #undef STEPCK
     c->cur ^= 1;
     // the final update folds the new state's signal speeds into smax
@@ -681,18 +752,18 @@ int run_step_grouped(wmb_ctx* c) {
         for (int stage = 1; stage <= 2 && e == hipSuccess; stage++) {
             for (int d = 0; d < 3 && e == hipSuccess; d++) {
                 if (stage == 2 && d == 0) {
-                    e = launch_corr_x<R>(c, g, cur, c->d_nfloor + 1, st);
+                    e = launch_corr_x<R>(c, g, cur, c->d_nfloor + 1, st, false);
                 } else if (stage == 2 && d == 2) {
-                    e = launch_corr_z<R>(c, g, cur, c->d_nfloor + 1, st);
+                    e = launch_corr_z<R>(c, g, cur, c->d_nfloor + 1, st, false);
                 } else if (!(stage == 2 && d == 1 && c->xy_rows)) {
                     for (auto& SG : c->sweeps[d][stage - 1])
-                        if (e == hipSuccess) e = launch_group<R>(c, d, stage, SG, SG.wlg[g], cur, c->d_nfloor + 1, st);
+                        if (e == hipSuccess) e = launch_group<R>(c, d, stage, SG, SG.wlg[g], cur, c->d_nfloor + 1, st, false);
                 }
                 if (!par) mark(c);
             }
             if (stage == 1 && e == hipSuccess) {
                 e = launch_ct_half<R>(c->pool, c->d_patch, c->wl_cth_g[g].d, c->wl_cth_g[g].n, coef<R>(c), c->p.ghost,
-                                      cur, c->d_sc, st);
+                                      cur, c->d_sc, SharedHalo{nullptr}, st);
                 if (!par) mark(c);
             }
         }
@@ -700,15 +771,15 @@ int run_step_grouped(wmb_ctx* c) {
         if (e == hipSuccess)
             e = launch_update<R>(c->pool, c->d_patch, wu.d, wu.n, c->dp, coef<R>(c), cur, c->d_sc, c->d_nfloor, c->d_smax,
                                  c->keep_edges ? 1 : 0, c->upd_zones,
-                                 c->upd_queue ? c->d_queue + 16 * (par ? g : 0) : nullptr, st);
+                                 c->upd_queue ? c->d_queue + 16 * (par ? g : 0) : nullptr, SharedHalo{nullptr}, 0,
+                                 nullptr, st);
         if (!par) mark(c);
         if (e != hipSuccess) return fail(c, WMB_EHIP, std::string("grouped step: ") + hipGetErrorString(e));
         if (g > 0 && par) CKH(hipEventRecord(c->ev_g[g], st));
     }
     if (par)
         for (int g = 1; g < c->ngroups; g++) CKH(hipStreamWaitEvent(c->stream, c->ev_g[g], 0));
-    c->edges_kept = c->keep_edges;
-    c->xg_valid = true;
+    stepped(c, false);
     c->cur ^= 1;
     c->smax_state = (c->smax_state == SMAX_ZERO) ? SMAX_CLEAN : SMAX_DIRTY;
     return WMB_OK;
@@ -836,7 +907,7 @@ bool in_plan(const wmb_ctx* c, int p) { return c->hpatch[p].present && c->hpatch
 
 std::vector<WorkItem> tile_items(const wmb_ctx* c, int lo, int hi, int zlo, int zhi, int txmax_allowed, int maxz,
                                  const std::vector<int>* group, int cap, int sgroup = -1, int ermax = 0,
-                                 int edmax = 0) {
+                                 int edmax = 0, bool turn = false) {
     std::vector<WorkItem> items;
     struct Cut {
         int ex, ey, mx, my;
@@ -877,20 +948,29 @@ std::vector<WorkItem> tile_items(const wmb_ctx* c, int lo, int hi, int zlo, int 
             }
         }
     }
+    if (turn) return in_turn(items, *group);
     return xcd_order(items, group, true);
 }
 
 // blocks of Steps 3-4 and of Steps 8-11 (tile planes of Z zones) the chip holds at once
-int cth_cap(const wmb_ctx* c) { return c->esize == 4 ? ct_half_resident<float>() : ct_half_resident<double>(); }
-int upd_cap(const wmb_ctx* c, int Z) { return c->esize == 4 ? update_resident<float>(Z) : update_resident<double>(Z); }
-
-// The Steps 3-4 tiles, at most tx zones wide along x and 256 a plane
-std::vector<WorkItem> cth_items(const wmb_ctx* c, int tx, int sgroup = -1) {
-    return tile_items(c, -2, 2, -2, 2, tx, 256, nullptr, cth_cap(c), sgroup);
+int cth_cap(const wmb_ctx* c, bool sh) {
+    return c->esize == 4 ? ct_half_resident<float>(sh) : ct_half_resident<double>(sh);
+}
+int upd_cap(const wmb_ctx* c, int Z, bool sh) {
+    return c->esize == 4 ? update_resident<float>(Z, sh) : update_resident<double>(Z, sh);
 }
 
-int build_cth_list(wmb_ctx* c, int tx, DevList& out, int sgroup = -1) {
-    std::vector<WorkItem> items = cth_items(c, tx, sgroup);
+// The Steps 3-4 tiles, at most tx zones wide along x and 256 a plane
+std::vector<WorkItem> cth_items(const wmb_ctx* c, int tx, int sgroup = -1, bool sh = false) {
+    if (sh) {
+        const std::vector<int> rows = x_rows(c);
+        return tile_items(c, 0, -1, 0, -1, tx, 256, &rows, cth_cap(c, true), -1, 0, 0, true);
+    }
+    return tile_items(c, -2, 2, -2, 2, tx, 256, nullptr, cth_cap(c, false), sgroup);
+}
+
+int build_cth_list(wmb_ctx* c, int tx, DevList& out, int sgroup = -1, bool sh = false) {
+    std::vector<WorkItem> items = cth_items(c, tx, sgroup, sh);
     out.n = (int)items.size();
     return upload(c, &out.d, items);
 }
@@ -900,12 +980,14 @@ int build_cth_list(wmb_ctx* c, int tx, DevList& out, int sgroup = -1) {
 // tiles instead of 24 x 16), up to 32 otherwise, with ty capped so that the
 // E^r and edge planes fit the kernel's LDS.
 int upd_txmax(int Z) { return Z > 256 ? 48 : 32; }
-std::vector<WorkItem> upd_items(const wmb_ctx* c, int Z, const std::vector<int>* rows, int sgroup = -1) {
+std::vector<WorkItem> upd_items(const wmb_ctx* c, int Z, const std::vector<int>* rows, int sgroup = -1,
+                                bool sh = false) {
     const int es = (int)c->esize;
-    return tile_items(c, 0, -1, 0, -1, upd_txmax(Z), Z, rows, upd_cap(c, Z), sgroup, upd_er_plane(es), upd_ed_plane(es));
+    return tile_items(c, 0, -1, 0, -1, upd_txmax(Z), Z, rows, upd_cap(c, Z, sh), sgroup, upd_er_plane(es),
+                      upd_ed_plane(es), sh);
 }
-int build_upd_list(wmb_ctx* c, int Z, const std::vector<int>* rows, DevList& out, int sgroup = -1) {
-    std::vector<WorkItem> items = upd_items(c, Z, rows, sgroup);
+int build_upd_list(wmb_ctx* c, int Z, const std::vector<int>* rows, DevList& out, int sgroup = -1, bool sh = false) {
+    std::vector<WorkItem> items = upd_items(c, Z, rows, sgroup, sh);
     out.n = (int)items.size();
     return upload(c, &out.d, items);
 }
@@ -949,13 +1031,15 @@ int choose_upd_zones(const wmb_ctx* c) {
 // measured faster for them.  With a grouped schedule, the lists of every
 // group as well.
 int build_ct_update_lists(wmb_ctx* c) {
-    for (DevList* L : {&c->wl_cth, &c->wl_upd}) {
+    for (DevList* L : {&c->wl_cth, &c->wl_upd, &c->wl_cth_s, &c->wl_upd_s}) {
         release(c, L->d);
         *L = DevList{};
     }
     const std::vector<int> rows = x_rows(c);
     int rc = build_cth_list(c, c->cth_tx, c->wl_cth);
     if (!rc) rc = build_upd_list(c, c->upd_zones, &rows, c->wl_upd);
+    if (!rc && c->d_nbr && c->all_in) rc = build_cth_list(c, c->cth_tx, c->wl_cth_s, -1, true);
+    if (!rc && c->d_nbr && c->all_in) rc = build_upd_list(c, c->upd_zones, &rows, c->wl_upd_s, -1, true);
     if (c->ngroups > 1 && c->wl_cth_g.size() < (size_t)c->ngroups) {
         c->wl_cth_g.resize(c->ngroups);
         c->wl_upd_g.resize(c->ngroups);
@@ -1000,9 +1084,13 @@ int build_fill_lists(wmb_ctx* c) {
 
 // Default shape of the sweeps along d with pencils of P zones, npen pencils in
 // the batch (stage 0: Step 1, 1: the corrector, which along z in FP32 reads
-// the stored records).
+// the stored records; march: whether the marching form may be taken).
 //   Marching form: one wave holds 64 pencils, so it needs waves for every
-// SIMD.  In FP32 the z corrector from records takes it from 2048 waves on
+// SIMD.  In shared-halo steps, whose stores fill whole lines, it takes the y
+// and z sweeps from 2048 waves on (two a SIMD; Step 1 along y 0.28 against
+// 0.34 ms at 512 x 32^3 FP32, 0.14 against 0.16 at 64 x 48^3, FP64 0.80 against
+// 0.81; blocks of 256 pencils 49 us and of 64 57 us at 512 x 16^3).  In the
+// halo scheme's FP32 the z corrector from records takes it from 2048 waves on
 // (two a SIMD: 146 against 169 us at 64 x 48^3, 385 against 434 at 512 x
 // 32^3, but 133 against 63 on 36 uneven patches of 870 waves), the Step-1
 // sweeps from 4096 waves of pencils of 60 zones on (483 against 506 us at 64
@@ -1016,9 +1104,10 @@ int build_fill_lists(wmb_ctx* c) {
 // pencils 0.64, of 10 0.69.  Along y and z a wave reads W consecutive zones
 // a row, so a larger W wins at equal residency (FP64 y corrector 1.94 ms at
 // 12, 2.17 at 6).  Fewer blocks than CUs halve the gain.
-int choose_W(int d, int P, size_t es, int stage, long long npen, bool prot) {
+int choose_W(int d, int P, size_t es, int stage, long long npen, bool prot, bool march, bool sh) {
     const long long waves = npen / 64;
-    if (d != 0 && es == 4) {
+    if (d != 0 && march && sh && waves >= 2048) return es == 4 ? -256 : -64;
+    if (d != 0 && es == 4 && march && !sh) {
         if (d == 2 && stage == 1 ? waves >= 2048 : (waves >= 4096 && P >= 60)) return d == 2 && stage == 1 ? -256 : -64;
     }
     const int simd = es == 4 ? (prot ? 7 : 8) : 4;  // waves a SIMD the registers allow
@@ -1048,7 +1137,7 @@ enum SweepPart { PART_ALL, PART_INTERIOR, PART_FRAME };
 // rectangle a block
 // *bad is set when a pencil rectangle does not fit the packed fields
 std::vector<WorkItem> sweep_items(const wmb_ctx* c, int d, int n, int tlo, int thi, int W, SweepPart part = PART_ALL,
-                                  int group = -1, bool* bad = nullptr) {
+                                  int group = -1, bool* bad = nullptr, bool sh = false) {
     const int FA = (d == 0) ? 1 : 0;
     const int SA = (d == 0) ? 2 : (d == 1 ? 2 : 1);
     struct Rect {
@@ -1082,10 +1171,49 @@ std::vector<WorkItem> sweep_items(const wmb_ctx* c, int d, int n, int tlo, int t
                 items.push_back(WorkItem{p, p0, code, (p0 + W - 1 < npen - 1) ? p0 + W - 1 : npen - 1});
         }
     }
+    if (sh && d == 0) return in_turn(items, x_rows(c));
     return xcd_order(items);
 }
 
-// (Re)build a group's work lists for W pencils a block.
+int choose_W(int d, int P, size_t es, int stage, long long npen, bool prot, bool march, bool sh);
+
+// pencils of a group's patches over the transverse range [lo, n+hi]^2
+long long group_pencils(const wmb_ctx* c, int d, int n, int lo, int hi) {
+    long long np = 0;
+    for (int p = 0; p < c->npatch; p++)
+        if (c->desc[p].n[d] == n)
+            np += (long long)(c->desc[p].n[(d + 1) % 3] + hi - lo + 1) * (c->desc[p].n[(d + 2) % 3] + hi - lo + 1);
+    return np;
+}
+bool prot_on(const wmb_ctx* c) { return c->p.rho_protect > 0.0 || c->p.p_protect > 0.0; }
+
+// The group's lists for shared-halo steps: W pencils a block (Step 1 in
+// either form, the corrector from q^n in the pencil form), W3 for the z
+// corrector from records (either form; 0: no list of its own).
+int set_group_Ws(wmb_ctx* c, int d, int stage, SweepGroup& G, int W, int W3) {
+    if (!c->d_nbr || !c->all_in) return WMB_OK;  // built when the batch can share (replan)
+    if (W < 0 && stage == 1)
+        W = choose_W(d, G.Ps(), c->esize, stage, group_pencils(c, d, G.n, 0, -1), prot_on(c), false, true);
+    if (W3 < -512) W3 += 512;
+    auto put = [&](DevList& L, int w) -> int {
+        std::vector<WorkItem> items = sweep_items(c, d, G.n, G.tlo, G.thi, w < 0 ? (-w) % 512 : w, PART_INTERIOR, -1,
+                                                  nullptr, true);
+        WorkItem* nd = nullptr;
+        int rc = upload(c, &nd, items);
+        if (rc) return rc;
+        release(c, L.d);
+        L.d = nd;
+        L.n = (int)items.size();
+        return WMB_OK;
+    };
+    int rc = put(G.wls, W);
+    if (!rc && d == 2 && stage == 1) rc = put(G.wl3, W3);
+    if (rc) return rc;
+    G.Ws = W;
+    G.W3 = W3;
+    return WMB_OK;
+}
+
 // (Re)build a group's work lists for W pencils a block; the lists they
 // replace are freed.
 int set_group_W(wmb_ctx* c, int d, int stage, SweepGroup& G, int W) {
@@ -1115,60 +1243,101 @@ int set_group_W(wmb_ctx* c, int d, int stage, SweepGroup& G, int W) {
     if (!rc && d == 0 && stage == 0) rc = rebuild(G.wl_fr, PART_FRAME);
     if (rc) return rc;
     G.W = W;
-    return WMB_OK;
+    return set_group_Ws(c, d, stage, G, W, W);
 }
 
 // The fused x/y corrector (xy_rows > 0): for the patches whose x edge is n,
 // one item a z-plane k in [-3, n_z + 2] (beyond [-1, n_z] the z predictor
 // records only) and band of y-face rows, the rows [-1, n_y + 2) cut into
-// near-equal bands of at most rb rows.  Planes outermost, so that
+// near-equal bands of at most rb rows (sh: the patch's own planes and rows).  Planes outermost, so that
 // consecutive blocks of a patch share the z-flux plane between them.
-std::vector<WorkItem> xy_items(const wmb_ctx* c, int n, int rb, int group = -1) {
+std::vector<WorkItem> xy_items(const wmb_ctx* c, int n, int rb, int group = -1, bool sh = false) {
     std::vector<WorkItem> items;
     for (int p = 0; p < c->npatch; p++) {
         if (c->desc[p].n[0] != n || !in_plan(c, p)) continue;
         if (group >= 0 && c->pgroup[p] != group) continue;
         const int* e = c->desc[p].n;
-        const int E = e[1] + 3, nb = (E + rb - 1) / rb;
-        for (int k = -3; k <= e[2] + 2; k++)
+        const int E = e[1] + (sh ? 0 : 3), lo = sh ? 0 : -1, nb = (E + rb - 1) / rb;
+        for (int k = sh ? 0 : -3; k <= e[2] + (sh ? -1 : 2); k++)
             for (int b = 0; b < nb; b++) {
-                const int y0 = -1 + E * b / nb, y1 = -1 + E * (b + 1) / nb;
+                const int y0 = lo + E * b / nb, y1 = lo + E * (b + 1) / nb;
                 items.push_back(WorkItem{p, k + XY_BIAS, (y0 + XY_BIAS) | ((y1 + XY_BIAS) << 16), 0});
             }
     }
+    if (sh) return in_turn(items, x_rows(c));
     return xcd_order(items);
 }
 
 // rows of the fused corrector's block for x edge n: the largest band of any
 // patch of that edge (frozen or absent ones too, so that the launch shape
 // does not change when the plan does) plus the limiter's three halo rows
-int xy_rt(const wmb_ctx* c, int n, int rb) {
+int xy_rt(const wmb_ctx* c, int n, int rb, bool sh = false) {
     int rt = 0;
     for (int p = 0; p < c->npatch; p++) {
         if (c->desc[p].n[0] != n) continue;
-        const int E = c->desc[p].n[1] + 3, nb = (E + rb - 1) / rb;
+        const int E = c->desc[p].n[1] + (sh ? 0 : 3), nb = (E + rb - 1) / rb;
         rt = std::max(rt, (E + nb - 1) / nb + 3);
     }
     return rt;
 }
 
+// whether a block of P zones by RT rows fits the fused corrector (1024
+// threads, 64 KiB of LDS)
+bool xy_fits(const wmb_ctx* c, int P, int RT) {
+    const long long t = (long long)P * RT;
+    return t <= 1024 && (long long)c->esize * 16 * t <= 64 * 1024;
+}
+
 // whether bands of at most rb rows fit the fused corrector's blocks for
-// every x edge (1024 threads, 64 KiB of LDS)
+// every x edge
 bool xy_ok(const wmb_ctx* c, int rb) {
     if (rb < 1 || rb > 64) return false;
     for (const auto& G : c->sweeps[0][1]) {
-        const long long t = (long long)G.P * xy_rt(c, G.n, rb);
-        if (t > 1024 || (long long)c->esize * 16 * t > 64 * 1024) return false;
+        if (!xy_fits(c, G.P, xy_rt(c, G.n, rb))) return false;
     }
     return true;
 }
 
+// The most rows a band of the fused corrector by default: the bands that keep
+// the most face rows resident.  A block's waves are dealt to the 4 SIMDs (6
+// waves each at the kernel's 80 VGPRs, 3 at 144 in FP64), so a block takes room for whole rounds
+// of 4 waves, and at equal room smaller blocks wait less at their barriers.
+// Measured in shared-halo steps: 512 x 32^3 1.21 ms with 11-row bands (3
+// blocks of 490 threads a CU), 1.42 with 8 (3 of 385); before the layout
+// without ghosts 64 x 48^3 0.62 ms with 12 rows, 0.72 with 8; 64 x 64^3 1.38
+// with 8, 1.78 with 11.
+int choose_xy(const wmb_ctx* c, bool sh) {
+    int best = 0;
+    double bt = 0.0;
+    for (int rb = 3; rb <= 24; rb++) {
+        if (!xy_ok(c, rb)) continue;
+        double time = 0.0;  // rows of zones over the rows a CU holds
+        for (const auto& d : c->desc) {
+            const int P = d.n[0] + (sh ? 3 : 6), E = d.n[1] + (sh ? 0 : 3), nb = (E + rb - 1) / rb;
+            const int RT = (E + nb - 1) / nb + 3, t = P * RT, ps = (t + 255) / 256;
+            const int res = std::min((c->esize == 4 ? 6 : 3) / ps, (int)(160 * 1024 / (c->esize * 16 * t)));
+            if (t > 1024 || res < 1) {
+                time = -1.0;
+                break;
+            }
+            const double rows = (double)E / nb;
+            time += (double)d.n[2] * E * P / (res * rows * t / (256.0 * ps) * (1.0 - t / 4096.0));
+        }
+        if (time > 0.0 && (best == 0 || time < bt * 0.999)) bt = time, best = rb;
+    }
+    return best;
+}
+
 // Switch the fused x/y corrector off (rb = 0) or on with bands of at most rb
-// rows: (re)build its lists, freeing the ones they replace.
-int set_xy(wmb_ctx* c, int rb) {
+// rows (rs in shared-halo steps; 0: rb too): (re)build its lists, freeing the
+// ones they replace.
+int set_xy(wmb_ctx* c, int rb, int rs = 0) {
+    if (rs <= 0) rs = rb;
     for (auto& G : c->sweeps[0][1]) {
         release(c, G.wxy.d);
         G.wxy = DevList{};
+        release(c, G.wxys.d);
+        G.wxys = DevList{};
         for (auto& L : G.wxyg) {
             release(c, L.d);
             L = DevList{};
@@ -1186,13 +1355,67 @@ int set_xy(wmb_ctx* c, int rb) {
             if (!gi.empty() && (rc = upload(c, &G.wxyg[g].d, gi))) return rc;
         }
         G.RT = xy_rt(c, G.n, rb);
+        if (!c->d_nbr || !c->all_in) continue;
+        // (the patch's own rows may cut into fewer, longer bands than the halo
+        // scheme's, past what a block holds: then shorter ones)
+        int r = rs;
+        while (r > 1 && !xy_fits(c, G.Ps(), xy_rt(c, G.n, r, true))) r--;
+        std::vector<WorkItem> si = xy_items(c, G.n, r, -1, true);
+        G.wxys.n = (int)si.size();
+        if ((rc = upload(c, &G.wxys.d, si))) return rc;
+        G.RTs = xy_rt(c, G.n, r, true);
     }
     c->xy_rows = rb > 0 ? rb : 0;
     return WMB_OK;
 }
 
+// The neighbour table of the shared-halo steps, for a batch that can run
+// them: patches of the same extents (a field then lies at the same offset
+// from every patch's zone), no domain boundary, zones named by 32-bit words
+// of the pool and fields by 32-bit offsets in a patch's region, and no scratch
+// groups (whose patches share the intermediates).
+// Interior edges are at least the ghost width, so the three zones that a step
+// reads beyond a patch lie in its 26 neighbours.
+int build_neighbours(wmb_ctx* c) {
+    c->all_in = true;
+    c->d_nbr = nullptr;
+    const int* n = c->desc[0].n;
+    const uint64_t region = state_bytes(c->desc[0], c->p.ghost, c->esize) + scratch_bytes(c->desc[0], c->p.ghost, c->esize);
+    if (c->p.scratch_groups > 1 || region > 0xFFFFFFFFull || c->npatch * (region / c->esize) > 0xFFFFFFFFull) return WMB_OK;
+    for (const auto& d : c->desc) {
+        for (int a = 0; a < 3; a++)
+            if (d.n[a] != n[a]) return WMB_OK;
+        for (int t = 0; t < 27; t++)
+            if (d.nbr[t] < 0) return WMB_OK;
+    }
+    const int g = c->p.ghost;
+    // (the intermediates without ghosts fit where those with ghosts do)
+    if (scratch_stride(n[0], n[1], n[2]) > (uint64_t)c->hpatch[0].vol) return WMB_OK;
+    std::vector<unsigned> T((size_t)NBR_ROW * c->npatch, 0u);
+    for (int p = 0; p < c->npatch; p++)
+        for (int z = 0; z < 3; z++) {
+            unsigned* row = T.data() + (size_t)NBR_ROW * p;
+            long long first = -1, last = 0, sfirst = -1;
+            for (int t = 9 * z; t < 9 * z + 9; t++) {
+                const PatchDev& Q = c->hpatch[c->desc[p].nbr[t]];
+                // zone i of this frame is zone i - side n of the neighbour's
+                const long long o[3] = {-(t % 3 - 1LL) * n[0], -(t / 3 % 3 - 1LL) * n[1], -(t / 9 - 1LL) * n[2]};
+                row[t] = (unsigned)(Q.base + o[0] + g + (o[1] + g + (o[2] + g) * Q.N[1]) * Q.N[0]);
+                row[NBR_SCR + t] = (unsigned)(Q.sbase + o[0] + (o[1] + o[2] * n[1]) * n[0]);
+                if (first < 0 || Q.base < first) first = Q.base, sfirst = Q.sbase;
+                last = std::max(last, Q.base);
+            }
+            // every field of the nine through one descriptor: offsets below
+            // 4 GiB (the field's own goes into the scalar offset beside the zone's)
+            if ((uint64_t)(last - first) * c->esize + region > 0xFFFFFFFFull) return WMB_OK;
+            row[27 + z] = (unsigned)first;
+            row[NBR_SCR + 27 + z] = (unsigned)sfirst;
+        }
+    return upload(c, &c->d_nbr, T);
+}
+
 int build_sweeps(wmb_ctx* c) {
-    const bool prot = c->p.rho_protect > 0.0 || c->p.p_protect > 0.0;
+    const bool prot = prot_on(c);
     for (int d = 0; d < 3; d++) {
         for (int stage = 0; stage < 2; stage++) {
             const int zlo = stage == 0 ? -4 : -3;
@@ -1213,12 +1436,11 @@ int build_sweeps(wmb_ctx* c) {
                 G.tlo = tlo;
                 G.thi = thi;
                 G.n = n;
-                long long npen = 0;
-                for (int p = 0; p < c->npatch; p++)
-                    if (c->desc[p].n[d] == n)
-                        npen += (long long)(c->desc[p].n[(d + 1) % 3] + thi - tlo + 1) *
-                                (c->desc[p].n[(d + 2) % 3] + thi - tlo + 1);
-                int rc = set_group_W(c, d, stage, G, choose_W(d, G.P, c->esize, stage, npen, prot));
+                const long long np = group_pencils(c, d, n, tlo, thi), nps = group_pencils(c, d, n, 0, -1);
+                int rc = set_group_W(c, d, stage, G, choose_W(d, G.P, c->esize, stage, np, prot, true, false));
+                const int Ws = choose_W(d, G.Ps(), c->esize, stage, nps, prot, stage == 0, true);
+                const int W3 = choose_W(d, G.Ps(), c->esize, stage, nps, prot, true, true);
+                if (!rc) rc = set_group_Ws(c, d, stage, G, Ws, W3);
                 if (rc) return rc;
                 c->sweeps[d][stage].push_back(G);
             }
@@ -1233,8 +1455,9 @@ void free_graphs(wmb_ctx* c) {
     // whole device is idle keeps the memory its kernels used from ever being
     // freed (measured on ROCm 7: a pool freed after wmb_destroy stayed
     // allocated unless the device was synchronised first)
-    if (c->gexec[0] || c->gexec[1]) (void)hipDeviceSynchronize();  // teardown: nothing to report
-    for (int i = 0; i < 2; i++) {
+    if (c->gexec[0] || c->gexec[1] || c->gexec[2] || c->gexec[3])
+        (void)hipDeviceSynchronize();  // teardown: nothing to report
+    for (int i = 0; i < 4; i++) {
         if (c->gexec[i]) (void)hipGraphExecDestroy(c->gexec[i]);  // teardown: nothing to report
         if (c->graph[i]) (void)hipGraphDestroy(c->graph[i]);
         c->gexec[i] = nullptr;
@@ -1256,6 +1479,8 @@ void free_graphs(wmb_ctx* c) {
 int replan(wmb_ctx* c) {
     c->plan_dirty = false;
     CKH(hipStreamSynchronize(c->stream));  // no launch in flight reads the lists
+    c->all_in = true;
+    for (int p = 0; p < c->npatch; p++) c->all_in = c->all_in && in_plan(c, p);
     bool regrid = false;
     auto put = [&](DevList& L, std::vector<WorkItem> items) -> int {
         if (L.d && items.size() <= (size_t)L.n) {
@@ -1293,20 +1518,37 @@ int replan(wmb_ctx* c) {
         rc = put(c->wl_cth_g[g], cth_items(c, c->cth_tx, g));
         if (!rc) rc = put(c->wl_upd_g[g], upd_items(c, c->upd_zones, &rows, g));
     }
+    // the shared-halo lists cover every patch; those that a retune left out
+    // while a patch was frozen or absent are built now
+    if (!rc && c->d_nbr && c->all_in) {
+        const bool tiles = !c->wl_cth_s.d || !c->wl_upd_s.d;
+        if (tiles) rc = build_ct_update_lists(c), regrid = true;
+        for (int d = 0; d < 3 && !rc; d++)
+            for (int stage = 0; stage < 2 && !rc; stage++)
+                for (auto& G : c->sweeps[d][stage])
+                    if (!rc && !G.wls.d) rc = set_group_Ws(c, d, stage, G, G.W, G.W), regrid = true;
+        bool xy = false;
+        for (auto& G : c->sweeps[0][1]) xy = xy || (c->xy_rows > 0 && !G.wxys.d);
+        if (!rc && xy) rc = set_xy(c, c->xy_rows), regrid = true;
+    }
     if (regrid) free_graphs(c);
     return rc;
 }
 
 
-// One graph per state copy: fill ghosts, dt = cfl / smax, step (whose final
+// One graph per state copy (of the scheme that the next step runs): fill ghosts, dt = cfl / smax, step (whose final
 // update refills smax for the next replay).  Replays require smax to hold the
 // current state's maximum at their start.
 int capture_graphs(wmb_ctx* c) {
     // nothing runs during capture: the host-side state flags are restored
     const int saved_state = c->smax_state;
     const bool saved_xg = c->xg_valid, saved_kept = c->edges_kept;
-    const int cur_start = c->cur;
+    const bool saved_lazy = c->xg_lazy, saved_stages = c->stages_shared;
+    const bool sh = shared_now(c);
+    const int cur_start = c->cur, mode = sh ? 2 : 0;
     auto restore = [&]() {
+        c->xg_lazy = saved_lazy;
+        c->stages_shared = saved_stages;
         c->cur = cur_start;
         c->smax_state = saved_state;
         c->xg_valid = saved_xg;
@@ -1317,9 +1559,13 @@ int capture_graphs(wmb_ctx* c) {
         CKH(hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
         // grouped schedule: the exchange first, on the main stream; else the
         // exchange on its own branch beside the interior x sweep
-        int rc = c->ngroups > 1 ? dispatch_fill(c, FILL_YZ) : fork_fill_yz(c);
+        // (shared-halo steps: no exchange)
+        int rc = sh ? WMB_OK : (c->ngroups > 1 ? dispatch_fill(c, FILL_YZ) : fork_fill_yz(c));
         if (!rc) rc = run_finalize(c);
-        if (!rc) rc = dispatch_step(c, true);
+        // shared-halo steps are one chain: with the sweeps at 91-97% of the
+        // vector issue, branches gain nothing (512 x 32^3 FP32 4.03 ms either
+        // way) and cost small batches their joins
+        if (!rc) rc = dispatch_step(c, !sh);
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(c->stream, &g);
         if (rc || e != hipSuccess) {
@@ -1327,8 +1573,8 @@ int capture_graphs(wmb_ctx* c) {
             restore();
             return rc ? rc : fail(c, WMB_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
         }
-        c->graph[cur0] = g;
-        e = hipGraphInstantiate(&c->gexec[cur0], g, nullptr, nullptr, 0);
+        c->graph[mode + cur0] = g;
+        e = hipGraphInstantiate(&c->gexec[mode + cur0], g, nullptr, nullptr, 0);
         if (e != hipSuccess) {
             restore();
             return fail(c, WMB_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e));
@@ -1435,6 +1681,42 @@ int get_state_t(wmb_ctx* c, int ip, double* q, double* b, bool stored) {
     return WMB_OK;
 }
 
+// A shared-halo step leaves intermediates over the patches' own zones only.
+// Form those of the last step again, over the ranges of the halo scheme, from
+// the state copy it started from (still in place) and its step constants;
+// the counters go to the sinks.
+template <typename R>
+int restage(wmb_ctx* c) {
+    const int cur0 = c->cur;
+    const bool xg0 = c->xg_valid, xl0 = c->xg_lazy;
+    StepConst* sc0 = c->d_sc;
+    c->cur ^= 1;
+    int rc = run_fill<R>(c, FILL_ALL);
+    c->d_sc = sc0 + 1;
+    hipError_t e = hipSuccess;
+    for (int d = 0; d < 3; d++)
+        for (auto& G : c->sweeps[d][0])
+            if (!rc && e == hipSuccess)
+                e = launch_group<R>(c, d, 1, G, G.wl, c->cur, c->d_nfloor + 2, c->stream, false);
+    if (!rc && e == hipSuccess)
+        e = launch_ct_half<R>(c->pool, c->d_patch, c->wl_cth.d, c->wl_cth.n, coef<R>(c), c->p.ghost, c->cur, c->d_sc,
+                              SharedHalo{nullptr}, c->stream);
+    if (!rc && e == hipSuccess) e = launch_corr_x<R>(c, -1, c->cur, c->d_nfloor + 2, c->stream, false);
+    if (!c->xy_rows)
+        for (auto& G : c->sweeps[1][1])
+            if (!rc && e == hipSuccess)
+                e = launch_group<R>(c, 1, 2, G, G.wl, c->cur, c->d_nfloor + 2, c->stream, false);
+    if (!rc && e == hipSuccess) e = launch_corr_z<R>(c, -1, c->cur, c->d_nfloor + 2, c->stream, false);
+    c->d_sc = sc0;
+    c->cur = cur0;
+    c->xg_valid = xg0;
+    c->xg_lazy = xl0;
+    if (rc) return rc;
+    if (e != hipSuccess) return fail(c, WMB_EHIP, std::string("stages: ") + hipGetErrorString(e));
+    c->stages_shared = false;
+    return WMB_OK;
+}
+
 template <typename R>
 int debug_stage_t(wmb_ctx* c, int ip, int stage, double* out) {
     const PatchDev& P = c->hpatch[ip];
@@ -1529,6 +1811,10 @@ int autotune_t(wmb_ctx* c, int reps) {
     CKT(hipEventCreate(&e0));
     CKT(hipEventCreate(&e1));
     const size_t es = sizeof(R);
+    // the scheme that the steps run: its lists are the ones timed
+    const bool sh = shared_now(c);
+    const SharedHalo sa = shared_arg(c, sh);
+    const SweepPart part = sh ? PART_INTERIOR : PART_ALL;
     // the separate sweeps are timed first; the fused x/y corrector after them
     if (c->xy_rows > 0) {
         int rc0 = set_xy(c, 0);
@@ -1540,10 +1826,12 @@ int autotune_t(wmb_ctx* c, int reps) {
             hipError_t e = hipSuccess;
             for (int d = 0; d < 3 && e == hipSuccess; d++)
                 for (auto& G : c->sweeps[d][0])
-                    e = launch_group<R>(c, d, 1, G, G.wl, c->cur, c->d_nfloor + 2, c->stream);
+                    if (e == hipSuccess)
+                        e = launch_group<R>(c, d, 1, G, sh ? G.wls : G.wl, c->cur, c->d_nfloor + 2, c->stream, sh);
+            const DevList& lc = sh ? c->wl_cth_s : c->wl_cth;
             if (e == hipSuccess)
-                e = launch_ct_half<R>(c->pool, c->d_patch, c->wl_cth.d, c->wl_cth.n, coef<R>(c), c->p.ghost, c->cur,
-                                      c->d_sc, c->stream);
+                e = launch_ct_half<R>(c->pool, c->d_patch, lc.d, lc.n, coef<R>(c), c->p.ghost, c->cur, c->d_sc, sa,
+                                      c->stream);
             if (e != hipSuccess) return cleanup(fail(c, WMB_EHIP, std::string("autotune: ") + hipGetErrorString(e)));
         }
         for (int d = 0; d < 3; d++) {
@@ -1551,19 +1839,22 @@ int autotune_t(wmb_ctx* c, int reps) {
                 std::vector<int> cand;
                 // pencil counts around the 64-lane wave: 5, 10 and 20 pencils
                 // of 38 zones fill whole waves to 99%
-                const int opts_x[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24};
+                const int opts_x[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24};
                 // negative: the marching form (beyond -512: loads one zone ahead)
-                const int opts_t[] = {2, 4, 8, 16, 32, -64, -128, -256, -576, -640, -768};
+                const int opts_t[] = {2, 4, 6, 7, 8, 12, 14, 16, 32, -64, -128, -256, -576, -640, -768};
                 if (d == 0)
                     for (int W : opts_x) cand.push_back(W);
                 else
                     for (int W : opts_t) cand.push_back(W);
                 float best = 1e30f, bestp = 1e30f, bestm = 1e30f;
-                int bestW = G.W;
+                int bestW = sh ? G.Ws : G.W;
+                const int P = sh ? G.Ps() : G.P;
                 std::vector<std::pair<float, int>> timed;  // (ms, shape) of every candidate
                 for (int W : cand) {
-                    if (!shape_ok(d, G.P, es, W, stage + 1) || (W > 0 && G.P * W < 64)) continue;
-                    std::vector<WorkItem> items = sweep_items(c, d, G.n, G.tlo, G.thi, W < 0 ? (-W) % 512 : W);
+                    if (!shape_ok(d, G.P, es, W, stage + 1) || (W > 0 && P * W < 64)) continue;
+                    if (sh && stage == 1 && W < 0) continue;  // the corrector from q^n: pencil form
+                    std::vector<WorkItem> items = sweep_items(c, d, G.n, G.tlo, G.thi, W < 0 ? (-W) % 512 : W, part, -1,
+                                                              nullptr, sh);
                     if (items.empty()) continue;
                     CKT(hipMalloc(&dl, sizeof(WorkItem) * items.size()));
                     CKT(hipMemcpy(dl, items.data(), sizeof(WorkItem) * items.size(), hipMemcpyHostToDevice));
@@ -1572,9 +1863,9 @@ int autotune_t(wmb_ctx* c, int reps) {
                     for (int r = 0; r <= reps && e == hipSuccess; r++) {
                         CKT(hipEventRecord(e0, c->stream));
                         SweepGroup T = G;
-                        T.W = W;
+                        T.W = T.Ws = W;
                         e = launch_group<R>(c, d, stage + 1, T, DevList{dl, (int)items.size()}, c->cur, c->d_nfloor + 2,
-                                            c->stream);
+                                            c->stream, sh);
                         CKT(hipEventRecord(e1, c->stream));
                         CKT(hipEventSynchronize(e1));
                         float t = 0.f;
@@ -1596,7 +1887,7 @@ int autotune_t(wmb_ctx* c, int reps) {
                 std::sort(timed.begin(), timed.end());
                 G.Wx[0] = timed.size() > 1 ? timed[1].second : 0;
                 G.Wx[1] = timed.size() > 2 ? timed[2].second : 0;
-                if (bestW != G.W) {
+                if (bestW != G.W || (sh && bestW != G.Ws)) {
                     int rc2 = set_group_W(c, d, stage, G, bestW);
                     if (rc2) return cleanup(rc2);
                 }
@@ -1617,7 +1908,7 @@ int autotune_t(wmb_ctx* c, int reps) {
     auto time_stage = [&](float* ms) -> int {
         unsigned long long *smax0 = c->d_smax, *nfl0 = c->d_nfloor;
         const int cur0 = c->cur, ss0 = c->smax_state;
-        const bool xg0 = c->xg_valid, ek0 = c->edges_kept;
+        const bool xg0 = c->xg_valid, ek0 = c->edges_kept, xl0 = c->xg_lazy, sg0 = c->stages_shared;
         c->d_smax = smax0 + 2;
         c->d_nfloor = nfl0 + 2;
         hipGraph_t gr = nullptr;
@@ -1625,8 +1916,8 @@ int autotune_t(wmb_ctx* c, int reps) {
         int rc4 = WMB_OK;
         hipError_t e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed);
         if (e == hipSuccess) {
-            e = hipEventRecord(c->ev_join, c->stream);  // the exchange is done
-            if (e == hipSuccess) rc4 = run_step<R>(c, true);
+            if (!sh) e = hipEventRecord(c->ev_join, c->stream);  // the exchange is done
+            if (e == hipSuccess) rc4 = run_step<R>(c, !sh);
             hipError_t e2 = hipStreamEndCapture(c->stream, &gr);
             if (e == hipSuccess) e = e2;
         }
@@ -1636,6 +1927,8 @@ int autotune_t(wmb_ctx* c, int reps) {
         c->smax_state = ss0;
         c->xg_valid = xg0;
         c->edges_kept = ek0;
+        c->xg_lazy = xl0;
+        c->stages_shared = sg0;
         if (!rc4 && e == hipSuccess) e = hipGraphInstantiate(&ge, gr, nullptr, nullptr, 0);
         float tot = 1e30f;
         for (int r = 0; r <= reps && !rc4 && e == hipSuccess; r++) {
@@ -1711,7 +2004,7 @@ int autotune_t(wmb_ctx* c, int reps) {
                     if (!rc2) rc2 = set_group_W(c, d, stage, G, choice == 1 ? G.Wp : G.Wm);
         if (rc2) return cleanup(rc2);
     }
-    // The fused x/y corrector: bands of 6, 9, 12 or 18 rows, each with the z
+    // The fused x/y corrector: bands of 4 to 18 rows, each with the z
     // corrector (then reading the stored records) as marching sweeps of 256
     // or 64 pencils a block or pencil sweeps of 16, against the separate
     // sweeps as chosen above; whole steps replayed as a graph.
@@ -1723,7 +2016,7 @@ int autotune_t(wmb_ctx* c, int reps) {
         std::vector<int> zw, best_zw;
         for (auto& G : c->sweeps[2][1]) zw.push_back(G.W);
         best_zw = zw;
-        for (int rb : {6, 9, 12, 18}) {
+        for (int rb : {4, 6, 8, 9, 11, 13, 16, 18}) {
             if (!xy_ok(c, rb)) continue;
             if ((rc2 = set_xy(c, rb))) return cleanup(rc2);
             for (int W : {-256, -64, 16}) {
@@ -1756,8 +2049,7 @@ int autotune_t(wmb_ctx* c, int reps) {
         auto time_tiles = [&](int kind, int v, float* ms) -> int {
             DevList L;
             // kind 0: Steps 3-4; 1: Steps 8-11, one block a tile; 2: the same on the queues
-            int rc3 = kind == 0 ? build_cth_list(c, v, L)
-                                : build_upd_list(c, v, &rows, L);
+            int rc3 = kind == 0 ? build_cth_list(c, v, L, -1, sh) : build_upd_list(c, v, &rows, L, -1, sh);
             if (rc3) return cleanup(rc3);
             tl = L.d;  // released by cleanup on an error exit
             hipError_t e = hipSuccess;
@@ -1765,10 +2057,10 @@ int autotune_t(wmb_ctx* c, int reps) {
             for (int r = 0; r <= reps && e == hipSuccess; r++) {
                 CKT(hipEventRecord(e0, c->stream));
                 e = kind == 0 ? launch_ct_half<R>(c->pool, c->d_patch, L.d, L.n, coef<R>(c), c->p.ghost, c->cur, c->d_sc,
-                                                  c->stream)
+                                                  sa, c->stream)
                               : launch_update<R>(c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), c->cur, c->d_sc,
                                                  c->d_nfloor + 2, c->d_smax + 2, 0, v, kind == 2 ? c->d_queue : nullptr,
-                                                 c->stream);
+                                                 sa, zrec(c) ? F_FL1 + 14 : F_FL2 + 14, c->d_sc + 1, c->stream);
                 CKT(hipEventRecord(e1, c->stream));
                 CKT(hipEventSynchronize(e1));
                 float t = 0.f;
@@ -1827,7 +2119,7 @@ std::string tune_key(const wmb_ctx* c) {
         ext.push_back(std::to_string(d.n[0]) + "x" + std::to_string(d.n[1]) + "x" + std::to_string(d.n[2]));
     std::sort(ext.begin(), ext.end());
     std::string key = arch + "|" + std::to_string(c->esize) + "|" + std::to_string(c->p.ghost) + "|" +
-                      (c->p.limiter_beta == 1.0 ? "mm" : "sweby") + "|" +
+                      (c->p.limiter_beta == 1.0 ? "mm" : "sweby") + "|" + (shared_now(c) ? "shared" : "halo") + "|" +
                       ((c->p.rho_protect > 0.0 || c->p.p_protect > 0.0) ? "prot" : "plain");
     for (size_t i = 0; i < ext.size();) {
         size_t j = i;
@@ -2034,17 +2326,19 @@ int wmb_init_patches(wmb_ctx* c, int32_t npatch, const wmb_patch_desc* d, void* 
     if ((rc = build_fill_lists(c))) return rc;
     if ((rc = build_box_list(c, BOX_INTERIOR, c->wl_int))) return rc;
     if ((rc = build_diag_list(c))) return rc;
+    if ((rc = build_neighbours(c))) return rc;
     c->cth_tx = 40;
     c->upd_zones = choose_upd_zones(c);
     if ((rc = build_ct_update_lists(c))) return rc;
     c->nfrozen = 0;
     if ((rc = build_sweeps(c))) return rc;
-    // FP32: the fused corrector with 9-row bands (6 where those blocks do not
-    // fit), the fastest measured at 256^3; FP64 keeps the separate sweeps
+    // the fused corrector in FP32, and in FP64 shared-halo steps (512 x 32^3,
+    // bands of 4 rows: 3.62 against 3.88 ms for the three sweeps; 5.4 + 0.8
+    // against 5.7 ms in the halo scheme, which keeps the sweeps)
     c->xy_rows = 0;
-    if (c->esize == 4) {
-        const int rb = xy_ok(c, 9) ? 9 : (xy_ok(c, 6) ? 6 : 0);
-        if (rb && (rc = set_xy(c, rb))) return rc;
+    if (c->esize == 4 || c->d_nbr) {
+        const int rb = choose_xy(c, false);
+        if (rb && (rc = set_xy(c, rb, c->d_nbr ? choose_xy(c, true) : 0))) return rc;
     }
     if (c->p.scratch_groups > 1) {
         c->serial = true;
@@ -2053,7 +2347,7 @@ int wmb_init_patches(wmb_ctx* c, int32_t npatch, const wmb_patch_desc* d, void* 
     // the signal-speed maxima of the current and the previous state, and a
     // sink for tuning runs
     if ((rc = dev_alloc(c, &c->d_smax, 3))) return rc;
-    if ((rc = dev_alloc(c, &c->d_sc, 1))) return rc;
+    if ((rc = dev_alloc(c, &c->d_sc, 2))) return rc;  // this step's constants; the last shared step's
     // counters: floor activations, protected faces, and two sinks for tuning runs
     if ((rc = dev_alloc(c, &c->d_nfloor, 4))) return rc;
     if ((rc = dev_alloc(c, &c->d_queue, 64))) return rc;
@@ -2063,7 +2357,7 @@ int wmb_init_patches(wmb_ctx* c, int32_t npatch, const wmb_patch_desc* d, void* 
     for (int p = 0; p < npatch; p++) c->nzones += (long long)d[p].n[0] * d[p].n[1] * d[p].n[2];
     if ((rc = bind_scratch(c))) return rc;
     CKH(hipMemsetAsync(c->d_smax, 0, 3 * sizeof(unsigned long long), c->stream));
-    CKH(hipMemsetAsync(c->d_sc, 0, sizeof(StepConst), c->stream));
+    CKH(hipMemsetAsync(c->d_sc, 0, 2 * sizeof(StepConst), c->stream));
     CKH(hipMemsetAsync(c->d_nfloor, 0, 4 * sizeof(unsigned long long), c->stream));
     CKH(hipMemsetAsync(c->d_queue, 0, 64 * sizeof(unsigned int), c->stream));
     CKH(hipStreamSynchronize(c->stream));
@@ -2096,6 +2390,10 @@ int wmb_get_stored(wmb_ctx* c, int32_t patch, double* q, double* b) {
     if (!c) return WMB_EINVAL;
     if (!c->inited) return fail(c, WMB_EORDER, "wmb_init_patches first");
     if (patch < 0 || patch >= c->npatch) return fail(c, WMB_EINVAL, "bad patch");
+    if (c->xg_lazy) {  // the x-ghosts a step leaves, which a shared-halo step did not write
+        int rc = dispatch_fill(c, FILL_X);
+        if (rc) return rc;
+    }
     return c->esize == 4 ? get_state_t<float>(c, patch, q, b, true) : get_state_t<double>(c, patch, q, b, true);
 }
 
@@ -2147,7 +2445,9 @@ int wmb_run_steps(wmb_ctx* c, int32_t nsteps) {
         int rc = replan(c);
         if (rc) return rc;
     }
-    if (!c->gexec[0]) {
+    const bool sh = shared_now(c);
+    const int mode = sh ? 2 : 0;
+    if (!c->gexec[mode]) {
         int rc = capture_graphs(c);
         if (rc) {
             free_graphs(c);
@@ -2155,14 +2455,14 @@ int wmb_run_steps(wmb_ctx* c, int32_t nsteps) {
         }
     }
     int rc = ensure_smax(c);
-    if (!rc && !c->xg_valid) rc = dispatch_fill(c, FILL_X);  // the graphs start at the y pass
+    if (!rc && !sh && !c->xg_valid) rc = dispatch_fill(c, FILL_X);  // the halo graphs start at the y pass
     if (rc) return rc;
     for (int s = 0; s < nsteps; s++) {
-        CKH(hipGraphLaunch(c->gexec[c->cur], c->stream));
+        CKH(hipGraphLaunch(c->gexec[mode + c->cur], c->stream));
         c->cur ^= 1;
     }
     c->smax_state = SMAX_CLEAN;
-    c->xg_valid = true;
+    stepped(c, sh);
     return WMB_OK;
 }
 
@@ -2190,6 +2490,10 @@ int wmb_debug_stage(wmb_ctx* c, int32_t patch, int32_t stage, double* out) {
     if (!c || !out) return WMB_EINVAL;
     if (!c->inited) return fail(c, WMB_EORDER, "wmb_init_patches first");
     if (patch < 0 || patch >= c->npatch) return fail(c, WMB_EINVAL, "bad patch");
+    if (c->stages_shared) {
+        int rc = c->esize == 4 ? restage<float>(c) : restage<double>(c);
+        if (rc) return rc;
+    }
     return c->esize == 4 ? debug_stage_t<float>(c, patch, stage, out) : debug_stage_t<double>(c, patch, stage, out);
 }
 
@@ -2314,6 +2618,10 @@ int wmb_set_schedule(wmb_ctx* c, int32_t groups) {
 // into the other one.
 int freeze_sync(wmb_ctx* c, int patch) {
     const PatchDev& P = c->hpatch[patch];
+    if (c->stages_shared) {  // the copy below overwrites what the last step's stages come from
+        int rs = c->esize == 4 ? restage<float>(c) : restage<double>(c);
+        if (rs) return rs;
+    }
     int rc = dispatch_fill(c, FILL_ALL);
     if (rc) return rc;
     const size_t bytes = (size_t)11 * P.vol * c->esize;
@@ -2424,7 +2732,8 @@ int wmb_profile_step(wmb_ctx* c, double* ms, int32_t nclass) {
     if (nclass < WMB_NCLASS) return fail(c, WMB_EINVAL, "ms must hold WMB_NCLASS entries");
     int rc = c->plan_dirty ? replan(c) : WMB_OK;
     if (!rc) rc = ensure_smax(c);
-    if (!rc && !c->xg_valid) rc = dispatch_fill(c, FILL_X);  // as before a graph replay
+    const bool sh = shared_now(c);
+    if (!rc && !sh && !c->xg_valid) rc = dispatch_fill(c, FILL_X);  // as before a graph replay
     if (rc) return rc;
     // one event after every kernel class; with serial groups after every
     // class of every group (the fill and dt once), summed per class
@@ -2436,7 +2745,8 @@ int wmb_profile_step(wmb_ctx* c, double* ms, int32_t nclass) {
     c->marks = ev.data() + 1;
     c->mark_cap = nev;
     c->nmark = 0;
-    rc = dispatch_fill(c, FILL_YZ);
+    if (sh) mark(c);  // no exchange
+    else rc = dispatch_fill(c, FILL_YZ);
     if (!rc) rc = run_finalize(c);
     if (!rc) rc = dispatch_step(c);
     c->marks = nullptr;

@@ -1,0 +1,133 @@
+"""GPU: steps with shared halos (every face formed once, by the patch that owns
+it, and read from there) against the halo scheme (every patch forms what its
+ghosts hold), which `wmb_keep_stages` selects: the same arithmetic on the same
+values, so states, counters, stages and ghosts are bitwise equal."""
+import numpy as np
+import pytest
+
+from paper_1701_07452_amd import inputs as I
+from tests.test_gpu_parity import as_f32, gpu_sim, wmb  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+# patch extents, patches along each axis, ghost width, parameters, tuning
+PLAIN = {}
+SHARED = {
+    "one_patch": ((9, 7, 12), (1, 1, 1), 4, PLAIN, None),               # its own neighbour on every side
+    "smallest": ((4, 4, 4), (3, 2, 2), 4, PLAIN, None),                 # a halo reaches past half the neighbour
+    "odd": ((33, 5, 9), (2, 3, 1), 5, dict(limiter_beta=1.5), None),    # rows that are no whole lines, thin in y
+    "whole_lines": ((32, 16, 8), (1, 2, 3), 4, PLAIN, None),
+    "separate": ((16, 12, 10), (2, 1, 2), 4, PLAIN, {(6, 0, 0): 0}),    # the corrector as three sweeps
+    "fused": ((16, 12, 10), (2, 1, 2), 4, PLAIN, {(6, 0, 0): 4}),
+    "marching": ((8, 40, 24), (2, 1, 1), 4, PLAIN, "march"),
+    "protected": ((12, 10, 16), (2, 2, 1), 4, dict(rho_protect=0.6, p_protect=0.9), None),
+    "protected_march": ((6, 20, 20), (2, 1, 2), 4, dict(rho_protect=0.6, p_protect=0.9, limiter_beta=2.0), "march"),
+}
+
+
+def _setup(case, prec):
+    n, nb, g, kw, tun = SHARED[case]
+    G = I.uniform_grid(tuple(a * b for a, b in zip(n, nb)), n)
+    N = G.shape
+    dx = (1.0 / max(N),) * 3
+    q, b = I.random_smooth(N, 31, dx=dx, amp=0.4)
+    if prec == 1:
+        q, b = as_f32(q), as_f32(b)
+    if tun == "march":
+        tun = {(st, ax, n[ax]): -64 for st in (1, 2) for ax in (1, 2)}
+    return G, q, b, dict(kw, ghost=g, dx=dx), tun
+
+
+def _sim(W, case, prec, shared, tun="case"):
+    G, q, b, kw, t = _setup(case, prec)
+    sim = gpu_sim(W, G, q, b, prec, **kw)
+    if not shared:
+        sim.keep_stages(True)
+    if t:
+        sim.set_tuning(t)
+    return G, sim
+
+
+def _state(G, sim):
+    return I.gather(G, [sim.get_state(i) for i in range(G.npatch)])
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("case", sorted(SHARED))
+def test_shared_equals_halo(wmb, case, prec):
+    """Five graph-replayed steps, with eager steps and reads between them."""
+    out = []
+    for shared in (True, False):
+        G, sim = _sim(wmb, case, prec, shared)
+        sim.run_steps(2)
+        tot = sim.diagnostics()
+        sim.fill_ghosts()
+        dt = sim.compute_dt()
+        sim.advance(0.0)
+        sim.run_steps(2)
+        out.append((_state(G, sim), tot, dt, sim.protected_faces(), sim.diagnostics()))
+        sim.close()
+    for a, c in zip(out[0][0], out[1][0]):
+        assert np.array_equal(a, c), float(np.abs(a - c).max())
+    assert out[0][2] == out[1][2] and out[0][3] == out[1][3]
+    if "protected" in case:
+        assert out[0][3] > 0
+    for k in (1, 4):  # totals, max div b (normalised, raw), floor activations
+        assert np.array_equal(out[0][k][0], out[1][k][0]) and out[0][k][1:] == out[1][k][1:]
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("case", ["odd", "separate", "fused"])
+def test_stages_and_ghosts_after_shared_steps(wmb, case, prec):
+    """wmb_debug_stage after a shared step (with a new dt formed since) gives
+    the halo scheme's stages on the ranges a step needs, and wmb_get_stored
+    the x-ghosts of interior rows that its update writes."""
+    out = []
+    for shared in (True, False):
+        G, sim = _sim(wmb, case, prec, shared)
+        g = int(sim.params.ghost)
+        sim.run_steps(3)
+        sim.compute_dt()
+        got = []
+        for ip in range(G.npatch):
+            n = G.descs[ip][0]
+            rows = (slice(None), slice(g, g + n[2]), slice(g, g + n[1]))
+            qs, bs = sim.get_stored(ip)
+            got += [qs[rows], bs[rows]]
+            box = tuple(slice(g, g + n[2 - a]) for a in range(3))
+            for st, lo, hi, tlo, thi in ((1, -2, 2, -3, 2), (5, -1, 1, -1, 0)):
+                f = sim.debug_stage(ip, st)
+                for d in range(3):
+                    sl = tuple(slice(g + (lo if a == d else tlo), g + n[a] + (hi if a == d else thi) + 1) for a in (2, 1, 0))
+                    got.append(f[d][(slice(None),) + sl])
+            got.append(sim.debug_stage(ip, 3)[(slice(None),) + box])
+        sim.run_steps(1)  # the stages formed again leave the next step as it was
+        got += list(_state(G, sim))
+        out.append(got)
+        sim.close()
+    for i, (a, c) in enumerate(zip(*out)):
+        assert np.array_equal(a, c), (i, float(np.abs(a - c).max()))
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_shared_and_frozen_in_turn(wmb, prec):
+    """Steps before a freeze (shared), with a patch frozen and with a slot
+    removed (halo scheme), and after both are back (shared again), with a
+    retune while frozen."""
+    out = []
+    for shared in (True, False):
+        G, sim = _sim(wmb, "fused", prec, shared)
+        sim.run_steps(1)
+        sim.set_active(1, False)
+        sim.run_steps(2)
+        sim.set_tuning({(6, 0, 0): 3, (1, 0, 16): 2})
+        sim.set_active(1, True)
+        sim.run_steps(2)
+        sim.set_present(2, False)
+        sim.run_steps(1)
+        sim.set_present(2, True)
+        sim.run_steps(2)
+        out.append(_state(G, sim))
+        sim.close()
+    for a, c in zip(*out):
+        assert np.array_equal(a, c), float(np.abs(a - c).max())
