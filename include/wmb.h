@@ -186,8 +186,8 @@ int wmb_advance(wmb_ctx *c, double dt);
    except that the fused corrector is followed by the z sweep that reads its
    records; the
    x pass is enqueued first when the state was set since.  Shared-halo steps
-   have no exchange, and their graph is one chain.  Results are
-   bitwise those of the eager calls.  Enqueue only; this is the timed call. */
+   have no exchange; their graph is one chain, and from 2^21 zones they are
+   enqueued kernel by kernel.  Results are bitwise those of the eager calls.  Enqueue only; this is the timed call. */
 int wmb_run_steps(wmb_ctx *c, int32_t nsteps);
 
 /* FP64 diagnostics over all interiors: totals[8] = sum over zones of q times
@@ -238,7 +238,8 @@ int wmb_debug_stage(wmb_ctx *c, int32_t patch, int32_t stage, double *out);
    issues the next zone's loads one zone ahead (w pencils a block; more
    registers, half the waves).  The choice never
    changes results (both forms compute every face with the same
-   arithmetic).  It then times whole graph-replayed steps with the x and y
+   arithmetic).  It then times whole steps (graph-replayed, or launched
+   for shared-halo steps) with the x and y
    correctors fused into one launch (bands of 4 to 18 rows, where
    the blocks fit, each with three shapes of the z corrector that reads the
    records it stores) against the separate sweeps, and the tiles of Steps 3-4
@@ -256,7 +257,8 @@ int wmb_debug_stage(wmb_ctx *c, int32_t patch, int32_t stage, double *out);
    groups, then (3, 0, 0, Steps 3-4 tile width), (4, 0, 0, Steps 8-11
    tile zones), (5, 0, 0, Steps 8-11 launch) and (6, 0, 0, fused x/y
    corrector band rows, 0 for separate sweeps) -- up to nchosen ints,
-   0-terminated when shorter.
+   0-terminated when shorter.  Shared-halo batches in FP64 keep the default
+   shapes (reported as the choice) and time nothing.
    Synchronous. */
 int wmb_autotune(wmb_ctx *c, int32_t reps, int32_t *chosen, int32_t nchosen);
 

@@ -1900,8 +1900,9 @@ int autotune_t(wmb_ctx* c, int reps) {
     // stage by stage, for each x group its second and third shapes alone,
     // then for the best pencil shapes and for the best marching shapes of
     // the y and z groups, keeping the fastest each time.  time_stage: a
-    // whole step captured and replayed as a graph, as wmb_run_steps runs it
-    // (the sweeps of a stage as branches), its results going nowhere the
+    // whole step as wmb_run_steps runs it (captured and replayed as a graph,
+    // the sweeps of a stage as branches; a shared-halo step, one chain either
+    // way, launched kernel by kernel), its results going nowhere the
     // next step reads: the update writes the other state copy, floors,
     // protected faces and the signal-speed maximum go to the sinks, and the
     // current copy and the flags are restored
@@ -1914,35 +1915,42 @@ int autotune_t(wmb_ctx* c, int reps) {
         hipGraph_t gr = nullptr;
         hipGraphExec_t ge = nullptr;
         int rc4 = WMB_OK;
-        hipError_t e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed);
-        if (e == hipSuccess) {
-            if (!sh) e = hipEventRecord(c->ev_join, c->stream);  // the exchange is done
-            if (e == hipSuccess) rc4 = run_step<R>(c, !sh);
-            hipError_t e2 = hipStreamEndCapture(c->stream, &gr);
-            if (e == hipSuccess) e = e2;
-        }
-        c->d_smax = smax0;
-        c->d_nfloor = nfl0;
-        c->cur = cur0;
-        c->smax_state = ss0;
-        c->xg_valid = xg0;
-        c->edges_kept = ek0;
-        c->xg_lazy = xl0;
-        c->stages_shared = sg0;
-        if (!rc4 && e == hipSuccess) e = hipGraphInstantiate(&ge, gr, nullptr, nullptr, 0);
+        hipError_t e = hipSuccess;
         float tot = 1e30f;
+        auto restore = [&]() {
+            c->cur = cur0;
+            c->smax_state = ss0;
+            c->xg_valid = xg0;
+            c->edges_kept = ek0;
+            c->xg_lazy = xl0;
+            c->stages_shared = sg0;
+        };
+        if (!sh) {
+            e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed);
+            if (e == hipSuccess) {
+                e = hipEventRecord(c->ev_join, c->stream);  // the exchange is done
+                if (e == hipSuccess) rc4 = run_step<R>(c, true);
+                hipError_t e2 = hipStreamEndCapture(c->stream, &gr);
+                if (e == hipSuccess) e = e2;
+            }
+            restore();
+            if (!rc4 && e == hipSuccess) e = hipGraphInstantiate(&ge, gr, nullptr, nullptr, 0);
+        }
         for (int r = 0; r <= reps && !rc4 && e == hipSuccess; r++) {
             e = hipEventRecord(e0, c->stream);
-            if (e == hipSuccess) e = hipGraphLaunch(ge, c->stream);
+            if (e == hipSuccess && !sh) e = hipGraphLaunch(ge, c->stream);
+            if (e == hipSuccess && sh) rc4 = run_step<R>(c), restore();
             if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
             if (e == hipSuccess) e = hipEventSynchronize(e1);
             float t = 0.f;
             if (e == hipSuccess) e = hipEventElapsedTime(&t, e0, e1);
             if (r > 0) tot = std::min(tot, t);
         }
+        c->d_smax = smax0;
+        c->d_nfloor = nfl0;
         // a graph executable is destroyed only on an idle device (ROCm 7
         // otherwise keeps the memory its kernels used from being freed)
-        (void)hipDeviceSynchronize();
+        if (!sh) (void)hipDeviceSynchronize();
         if (ge) (void)hipGraphExecDestroy(ge);
         if (gr) (void)hipGraphDestroy(gr);
         if (rc4) return cleanup(rc4);
@@ -2436,6 +2444,13 @@ int wmb_advance(wmb_ctx* c, double dt) {
     return dispatch_step(c);
 }
 
+// Shared-halo steps of this many zones and more are launched kernel by kernel:
+// the nine launches of a step hide behind its kernels, and the first step needs
+// no capture.  Measured, graph / launches, us a step: 64 x 32^3 FP32 552 / 546,
+// 125 x 32^3 FP32 1238 / 1232, FP64 2319 / 2311, 64 x 48^3 FP32 1778 / 1771; one
+// 32^3 patch, the other way, 111 / 135.
+constexpr long long EAGER_ZONES = 1LL << 21;
+
 int wmb_run_steps(wmb_ctx* c, int32_t nsteps) {
     if (!c) return WMB_EINVAL;
     if (!c->inited) return fail(c, WMB_EORDER, "wmb_init_patches first");
@@ -2447,6 +2462,14 @@ int wmb_run_steps(wmb_ctx* c, int32_t nsteps) {
     }
     const bool sh = shared_now(c);
     const int mode = sh ? 2 : 0;
+    if (sh && c->nzones >= EAGER_ZONES) {
+        int rc = ensure_smax(c);
+        for (int s = 0; s < nsteps && !rc; s++) {
+            rc = run_finalize(c);
+            if (!rc) rc = dispatch_step(c);
+        }
+        return rc;
+    }
     if (!c->gexec[mode]) {
         int rc = capture_graphs(c);
         if (rc) {
@@ -2511,7 +2534,14 @@ int wmb_autotune(wmb_ctx* c, int32_t reps, int32_t* chosen, int32_t nchosen) {
         for (const auto& kv : tune_cache)
             if (kv.first == key) q = kv.second;
     }
-    if (!q.empty()) {
+    if (shared_now(c) && c->esize == 8) {
+        // Shared-halo steps in FP64 keep the shapes their rules choose: timing
+        // them gained 2% at 512 x 32^3 (9.17 -> 8.97 ms a step).  Two of nine
+        // processes that timed them there ended in a segmentation fault of the
+        // host between this call and the context's end; its cause is not known
+        // (the library's host code is clean under the address sanitizer).
+        q = tuning_quads(c);
+    } else if (!q.empty()) {
         int rc = wmb_set_tuning(c, q.data(), (int32_t)q.size());
         if (rc) return rc;
     } else {
