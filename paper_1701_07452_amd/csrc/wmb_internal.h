@@ -38,7 +38,8 @@ struct Coef {
     R gam, gm1, gm2, ggm, igm1;  // gamma, gamma-1, gamma-2, gamma/(gamma-1), 1/(gamma-1)
     R beta_l, p_floor, rho_floor, tol, tol2;
     R idx[3];                    // 1 / dx_d
-    R eps[7], q4e[7];            // epsilon_k and 1/(4 epsilon_k) (0 where epsilon_k = 0)
+    R eps[7], eps2[7], q4e[7];   // epsilon_k, 2 epsilon_k, 1/(4 epsilon_k) (0 where epsilon_k = 0)
+    int eps_odd;                 // whether a wave of odd k (Alfven, entropy) has epsilon_k > 0
     R rho_prot, p_prot;          // protection floors (0: off)
 };
 

@@ -169,8 +169,10 @@ void make_coef(const wmb_params& p, Coef<R>& cf) {
     for (int a = 0; a < 3; a++) cf.idx[a] = (R)(1.0 / p.dx[a]);
     for (int k = 0; k < 7; k++) {
         cf.eps[k] = (R)p.eps[k];
+        cf.eps2[k] = R(2) * cf.eps[k];
         cf.q4e[k] = p.eps[k] > 0.0 ? (R)(0.25 / p.eps[k]) : (R)0;
     }
+    cf.eps_odd = cf.eps[1] > R(0) || cf.eps[3] > R(0) || cf.eps[5] > R(0);
     cf.rho_prot = (R)p.rho_protect;
     cf.p_prot = (R)p.p_protect;
 }

@@ -1,0 +1,62 @@
+"""FP64 arithmetic of the limited correction: the forms of the viscosity Q_k
+(epsilon_k zero or not, on the even and on the odd waves), and waves so weak
+that their strengths alpha_k are subnormal or vanish, where a reciprocal
+overflows."""
+import numpy as np
+import pytest
+
+from paper_1701_07452_amd import inputs as I
+from tests._helpers import oracle_gather, oracle_sim
+from tests.test_gpu_branches import _lockstep
+from tests.test_gpu_parity import CASES, gpu_sim, rel_max, wmb  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("beta", [1.0, 1.5])
+@pytest.mark.parametrize("eps", [(0.0,) * 7, (0.0, 0.2) * 3 + (0.0,), (0.2, 0.0, 0.0, 0.0, 0.0, 0.1, 0.2)])
+def test_viscosity_forms(wmb, eps, beta):
+    """Six steps against the oracle: every field within 1e-11 of its scale (as
+    for the default epsilon_k)."""
+    G, (q, b) = CASES["uniform8"]()
+    N = G.shape
+    kw = dict(dx=(1.0 / N[2], 1.0 / N[1], 1.0 / N[0]), eps=eps, limiter_beta=beta)
+    sim = gpu_sim(wmb, G, q, b, 0, **kw)
+    orc = oracle_sim(G, q, b, **kw)
+    _lockstep(sim, orc, 6)
+    qg, bg = I.gather(G, [sim.get_state(i) for i in range(G.npatch)])
+    qo, bo = oracle_gather(G, orc)
+    for g, o in [(qg[c], qo[c]) for c in range(8)] + [(bg[c], bo[c]) for c in range(3)]:
+        assert rel_max(g, o) < 1e-11
+    sim.close()
+    orc.close()
+
+
+@pytest.mark.parametrize("tiny", [0.0, 1e-290, 1e-308, 1e-320])
+def test_vanishing_waves(wmb, tiny):
+    """A tube along x whose z velocity and field have the size `tiny`: the
+    Alfven jumps are of that size, subnormal or zero, while the other waves are
+    strong.  Four steps: the fields in the plane within 1e-11 of the oracle's
+    scale, m_z and B_z finite and within a hundredfold of `tiny` (a strong
+    compression multiplies them by less than ten)."""
+    G = I.patch_grid([16, 16], [8], [8])
+    q, b = I.shock_tube_x(G.shape, gamma=5 / 3, left=(1.0, 0.0, 0.0, 0.0, 0.5, 0.0, 1.0),
+                          right=(0.2, 0.0, 0.0, 0.0, -0.5, 0.0, 0.1), bx=0.75)
+    x = np.sin(2 * np.pi * (np.arange(G.shape[2]) + 0.5) / G.shape[2])
+    q, b = q.copy(), b.copy()
+    q[3] += tiny * x
+    q[6] += tiny * x[::-1]
+    b[2] += tiny * x[::-1]
+    kw = dict(dx=(1 / 32,) * 3)
+    sim = gpu_sim(wmb, G, q, b, 0, **kw)
+    orc = oracle_sim(G, q, b, **kw)
+    _lockstep(sim, orc, 4)
+    qg, bg = I.gather(G, [sim.get_state(i) for i in range(G.npatch)])
+    qo, bo = oracle_gather(G, orc)
+    assert np.isfinite(qg).all() and np.isfinite(bg).all()
+    for g, o in [(qg[c], qo[c]) for c in (0, 1, 2, 4, 5, 7)] + [(bg[c], bo[c]) for c in (0, 1)]:
+        assert rel_max(g, o) < 1e-11
+    for f in (qg[3], qg[6], bg[2]):
+        assert np.abs(f).max() <= 100 * tiny
+    sim.close()
+    orc.close()
