@@ -29,6 +29,11 @@ template <typename R> hipError_t launch_corr_xy(void*, const PatchDev*, const Wo
 template <typename R> hipError_t launch_march(int, int, void*, const PatchDev*, const WorkItem*, int, const DevParams&, const Coef<R>&, int, const StepConst*, int, int, int, unsigned long long*, SharedHalo, hipStream_t);
 template <typename R> int ct_half_resident(bool);
 template <typename R> int update_resident(int, bool);
+// values [first, first + count) of the patch's interior, (8 q, 3 b) x z x y x x in
+// double, to out (host memory the device can write)
+template <typename R>
+hipError_t launch_pack(const void* state, const PatchDev& P, int ghost, long long first, int count, double* out,
+                       hipStream_t st);
 template <typename R> hipError_t launch_diag(const void*, const PatchDev*, const WorkItem*, int, const DevParams&, int, double*, const unsigned long long*, double, double, double*, hipStream_t);
 }  // namespace wmb
 
@@ -138,6 +143,9 @@ struct wmb_ctx {
     double* d_diag_out = nullptr;  // the 12 diagnostics outputs
     double* noalloc_rec = nullptr; // this device's copy of the static records (wmb_diagnostics_noalloc)
     long long nzones = 0;          // interior zones of the batch
+    double* stage = nullptr;       // pinned host memory of the read-back, two slots (made by the first one)
+    hipEvent_t ev_stage[2] = {nullptr, nullptr};
+    std::vector<char> img;         // host image of a patch's state (wmb_set_state)
     // captured steps: by the state copy they start from, + 2 for shared-halo steps
     hipGraphExec_t gexec[4] = {};
     hipGraph_t graph[4] = {};
@@ -1631,12 +1639,15 @@ int set_state_t(wmb_ctx* c, int ip, const double* q, const double* b) {
     }
     // the 11 arrays of a state copy are contiguous in the patch region: one
     // host image (ghosts NaN until the next exchange), one copy
-    std::vector<R> img((size_t)11 * P.vol, (R)NAN);
+    const size_t values = (size_t)11 * P.vol;
+    if (c->img.size() < sizeof(R) * values) c->img.resize(sizeof(R) * values);
+    R* img = reinterpret_cast<R*>(c->img.data());
+    std::fill(img, img + values, (R)NAN);
     R* base = (R*)c->pool + P.base + (long long)(c->cur ? F_ST1 : F_ST0) * P.vol;
     if (c->smax_state != SMAX_ZERO) c->smax_state = SMAX_DIRTY;
     for (int f = 0; f < 11; f++) {
         const double* src = f < 8 ? q + f * n3 : b + (f - 8) * n3;
-        R* buf = img.data() + (size_t)f * P.vol;
+        R* buf = img + (size_t)f * P.vol;
         to_device_layout<R>(src, buf, P, g, n3);
         const int a = f - 8;
         if (a >= 0 && P.nb[2 * a + 1] < 0) {
@@ -1655,8 +1666,57 @@ int set_state_t(wmb_ctx* c, int ip, const double* q, const double* b) {
                 }
         }
     }
-    CKH(hipMemcpyAsync(base, img.data(), sizeof(R) * img.size(), hipMemcpyHostToDevice, c->stream));
+    CKH(hipMemcpyAsync(base, img, sizeof(R) * values, hipMemcpyHostToDevice, c->stream));
     CKH(hipStreamSynchronize(c->stream));
+    return WMB_OK;
+}
+
+// Read back a patch's interior through pinned memory: the device packs a slot
+// (widened, without ghosts) while the host copies the other one out.  A 32^3
+// FP64 patch takes 0.15 ms; through a pageable copy of its ghosted box into a
+// fresh image, and a strided copy out of that, it took 0.52 ms.
+constexpr int STAGE_VALUES = 1 << 17;  // doubles a slot
+
+// false: no pinned memory
+bool have_stage(wmb_ctx* c) {
+    if (c->stage) return true;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, sizeof(double) * 2 * STAGE_VALUES, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();  // the caller copies without it
+        return false;
+    }
+    for (auto& e : c->ev_stage)
+        if (!e && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipHostFree(p);
+            return false;
+        }
+    c->stage = static_cast<double*>(p);
+    return true;
+}
+
+template <typename R>
+int read_interior(wmb_ctx* c, int ip, double* q, double* b) {
+    const PatchDev& P = c->hpatch[ip];
+    const long long n3 = (long long)P.n[0] * P.n[1] * P.n[2];
+    const R* base = (const R*)c->pool + P.base + (long long)(c->cur ? F_ST1 : F_ST0) * P.vol;
+    const long long lo = q ? 0 : 8 * n3, hi = b ? 11 * n3 : 8 * n3, parts = (hi - lo + STAGE_VALUES - 1) / STAGE_VALUES;
+    auto pack = [&](long long s) -> hipError_t {
+        const long long first = lo + s * STAGE_VALUES;
+        hipError_t e = launch_pack<R>(base, P, c->p.ghost, first, (int)std::min<long long>(STAGE_VALUES, hi - first),
+                                      c->stage + (s & 1) * STAGE_VALUES, c->stream);
+        return e == hipSuccess ? hipEventRecord(c->ev_stage[s & 1], c->stream) : e;
+    };
+    for (long long s = 0; s < std::min(2LL, parts); s++) CKH(pack(s));
+    for (long long s = 0; s < parts; s++) {
+        CKH(hipEventSynchronize(c->ev_stage[s & 1]));
+        const long long first = lo + s * STAGE_VALUES, last = std::min<long long>(first + STAGE_VALUES, hi);
+        const double* src = c->stage + (s & 1) * STAGE_VALUES;
+        const long long cut = std::min(std::max(first, 8 * n3), last);  // q's values, then b's
+        if (cut > first) std::memcpy(q + first, src, sizeof(double) * (cut - first));
+        if (last > cut) std::memcpy(b + (cut - 8 * n3), src + (cut - first), sizeof(double) * (last - cut));
+        if (s + 2 < parts) CKH(pack(s + 2));
+    }
     return WMB_OK;
 }
 
@@ -1665,6 +1725,7 @@ int get_state_t(wmb_ctx* c, int ip, double* q, double* b, bool stored) {
     const PatchDev& P = c->hpatch[ip];
     const int g = c->p.ghost;
     const size_t n3 = (size_t)P.n[0] * P.n[1] * P.n[2];
+    if (!stored && (q || b) && have_stage(c)) return read_interior<R>(c, ip, q, b);
     std::vector<R> img((size_t)11 * P.vol);
     const R* base = (const R*)c->pool + P.base + (long long)(c->cur ? F_ST1 : F_ST0) * P.vol;
     CKH(hipMemcpyAsync(img.data(), base, sizeof(R) * img.size(), hipMemcpyDeviceToHost, c->stream));
@@ -2801,6 +2862,9 @@ int wmb_destroy(wmb_ctx* c) {
     if (c->stream) (void)hipStreamSynchronize(c->stream);  // teardown: nothing to report
     free_graphs(c);
     for (void* p : c->owned) (void)hipFree(p);
+    if (c->stage) (void)hipHostFree(c->stage);
+    for (hipEvent_t e : c->ev_stage)
+        if (e) (void)hipEventDestroy(e);
     for (hipStream_t sd : {c->side, c->side2}) return_stream(c->device, sd);
     for (int g = 1; g < 4; g++) {
         return_stream(c->device, c->gstream[g]);

@@ -210,8 +210,8 @@ class Sim:
 
     def get_state(self, ip):
         nx, ny, nz = self.n[ip]
-        q = np.zeros((8, nz, ny, nx))
-        b = np.zeros((3, nz, ny, nx))
+        q = np.empty((8, nz, ny, nx))
+        b = np.empty((3, nz, ny, nx))
         self._check(self.lib.wmb_get_state(self.h, ip, _dp(q), _dp(b)))
         return q, b
 
