@@ -113,6 +113,10 @@ __host__ __device__ constexpr unsigned scratch_stride(int nx, int ny, int nz) {
 // [y0, y1) (plane k and rows may be -1).
 constexpr int XY_BIAS = 16;
 
+// The counters: floor activations, then the protected faces in PROT_SLOTS
+// parts, each on a cache line of its own.
+constexpr int PROT_SLOTS = 64, COUNT_PAD = 16, COUNTERS = (1 + PROT_SLOTS) * COUNT_PAD;
+
 // Diagnostics record of one work item (doubles): 9 compensated sums as (hi, lo)
 // pairs (q times the zone volume, |B|^2), the max |div b|, one pad word.
 constexpr int DIAG_REC = 20;

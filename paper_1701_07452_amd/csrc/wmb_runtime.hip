@@ -655,7 +655,7 @@ int run_step(wmb_ctx* c, bool split = false) {
     if (e != hipSuccess) return fail(c, WMB_EHIP, std::string(what) + ": " + hipGetErrorString(e))
     auto sweeps = [&](int d, int stage, const DevList SweepGroup::*wl, hipStream_t st) -> hipError_t {
         for (auto& G : c->sweeps[d][stage - 1]) {
-            hipError_t r = launch_group<R>(c, d, stage, G, sh ? G.wls : G.*wl, cur, c->d_nfloor + 1, st, sh);
+            hipError_t r = launch_group<R>(c, d, stage, G, sh ? G.wls : G.*wl, cur, c->d_nfloor + COUNT_PAD, st, sh);
             if (r != hipSuccess) return r;
         }
         return hipSuccess;
@@ -703,23 +703,23 @@ int run_step(wmb_ctx* c, bool split = false) {
             STEPCK("sweep2");
         }
         if (!zrec(c)) {
-            e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + 1, c->side2, sh);
+            e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + COUNT_PAD, c->side2, sh);
             STEPCK("sweep2");
         }
         CKH(hipEventRecord(c->ev_br[3], c->side));
         CKH(hipEventRecord(c->ev_br[4], c->side2));
-        e = launch_corr_x<R>(c, -1, cur, c->d_nfloor + 1, c->stream, sh);
+        e = launch_corr_x<R>(c, -1, cur, c->d_nfloor + COUNT_PAD, c->stream, sh);
         STEPCK("sweep2");
         if (zrec(c)) {
-            e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + 1, c->stream, sh);
+            e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + COUNT_PAD, c->stream, sh);
             STEPCK("sweep2");
         }
         CKH(hipStreamWaitEvent(c->stream, c->ev_br[3], 0));
         CKH(hipStreamWaitEvent(c->stream, c->ev_br[4], 0));
     } else {
         for (int d = 0; d < 3; d++) {
-            if (d == 0) e = launch_corr_x<R>(c, -1, cur, c->d_nfloor + 1, c->stream, sh);
-            else if (d == 2) e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + 1, c->stream, sh);
+            if (d == 0) e = launch_corr_x<R>(c, -1, cur, c->d_nfloor + COUNT_PAD, c->stream, sh);
+            else if (d == 2) e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + COUNT_PAD, c->stream, sh);
             else if (!c->xy_rows) e = sweeps(d, 2, &SweepGroup::wl, c->stream);
             STEPCK("sweep2");
             mark(c);
@@ -762,12 +762,12 @@ int run_step_grouped(wmb_ctx* c) {
         for (int stage = 1; stage <= 2 && e == hipSuccess; stage++) {
             for (int d = 0; d < 3 && e == hipSuccess; d++) {
                 if (stage == 2 && d == 0) {
-                    e = launch_corr_x<R>(c, g, cur, c->d_nfloor + 1, st, false);
+                    e = launch_corr_x<R>(c, g, cur, c->d_nfloor + COUNT_PAD, st, false);
                 } else if (stage == 2 && d == 2) {
-                    e = launch_corr_z<R>(c, g, cur, c->d_nfloor + 1, st, false);
+                    e = launch_corr_z<R>(c, g, cur, c->d_nfloor + COUNT_PAD, st, false);
                 } else if (!(stage == 2 && d == 1 && c->xy_rows)) {
                     for (auto& SG : c->sweeps[d][stage - 1])
-                        if (e == hipSuccess) e = launch_group<R>(c, d, stage, SG, SG.wlg[g], cur, c->d_nfloor + 1, st, false);
+                        if (e == hipSuccess) e = launch_group<R>(c, d, stage, SG, SG.wlg[g], cur, c->d_nfloor + COUNT_PAD, st, false);
                 }
                 if (!par) mark(c);
             }
@@ -1760,16 +1760,16 @@ int restage(wmb_ctx* c) {
     for (int d = 0; d < 3; d++)
         for (auto& G : c->sweeps[d][0])
             if (!rc && e == hipSuccess)
-                e = launch_group<R>(c, d, 1, G, G.wl, c->cur, c->d_nfloor + 2, c->stream, false);
+                e = launch_group<R>(c, d, 1, G, G.wl, c->cur, c->d_nfloor + COUNTERS + COUNT_PAD, c->stream, false);
     if (!rc && e == hipSuccess)
         e = launch_ct_half<R>(c->pool, c->d_patch, c->wl_cth.d, c->wl_cth.n, coef<R>(c), c->p.ghost, c->cur, c->d_sc,
                               SharedHalo{nullptr}, c->stream);
-    if (!rc && e == hipSuccess) e = launch_corr_x<R>(c, -1, c->cur, c->d_nfloor + 2, c->stream, false);
+    if (!rc && e == hipSuccess) e = launch_corr_x<R>(c, -1, c->cur, c->d_nfloor + COUNTERS + COUNT_PAD, c->stream, false);
     if (!c->xy_rows)
         for (auto& G : c->sweeps[1][1])
             if (!rc && e == hipSuccess)
-                e = launch_group<R>(c, 1, 2, G, G.wl, c->cur, c->d_nfloor + 2, c->stream, false);
-    if (!rc && e == hipSuccess) e = launch_corr_z<R>(c, -1, c->cur, c->d_nfloor + 2, c->stream, false);
+                e = launch_group<R>(c, 1, 2, G, G.wl, c->cur, c->d_nfloor + COUNTERS + COUNT_PAD, c->stream, false);
+    if (!rc && e == hipSuccess) e = launch_corr_z<R>(c, -1, c->cur, c->d_nfloor + COUNTERS + COUNT_PAD, c->stream, false);
     c->d_sc = sc0;
     c->cur = cur0;
     c->xg_valid = xg0;
@@ -1890,7 +1890,7 @@ int autotune_t(wmb_ctx* c, int reps) {
             for (int d = 0; d < 3 && e == hipSuccess; d++)
                 for (auto& G : c->sweeps[d][0])
                     if (e == hipSuccess)
-                        e = launch_group<R>(c, d, 1, G, sh ? G.wls : G.wl, c->cur, c->d_nfloor + 2, c->stream, sh);
+                        e = launch_group<R>(c, d, 1, G, sh ? G.wls : G.wl, c->cur, c->d_nfloor + COUNTERS + COUNT_PAD, c->stream, sh);
             const DevList& lc = sh ? c->wl_cth_s : c->wl_cth;
             if (e == hipSuccess)
                 e = launch_ct_half<R>(c->pool, c->d_patch, lc.d, lc.n, coef<R>(c), c->p.ghost, c->cur, c->d_sc, sa,
@@ -1927,7 +1927,7 @@ int autotune_t(wmb_ctx* c, int reps) {
                         CKT(hipEventRecord(e0, c->stream));
                         SweepGroup T = G;
                         T.W = T.Ws = W;
-                        e = launch_group<R>(c, d, stage + 1, T, DevList{dl, (int)items.size()}, c->cur, c->d_nfloor + 2,
+                        e = launch_group<R>(c, d, stage + 1, T, DevList{dl, (int)items.size()}, c->cur, c->d_nfloor + COUNTERS + COUNT_PAD,
                                             c->stream, sh);
                         CKT(hipEventRecord(e1, c->stream));
                         CKT(hipEventSynchronize(e1));
@@ -1974,7 +1974,7 @@ int autotune_t(wmb_ctx* c, int reps) {
         const int cur0 = c->cur, ss0 = c->smax_state;
         const bool xg0 = c->xg_valid, ek0 = c->edges_kept, xl0 = c->xg_lazy, sg0 = c->stages_shared;
         c->d_smax = smax0 + 2;
-        c->d_nfloor = nfl0 + 2;
+        c->d_nfloor = nfl0 + COUNTERS;
         hipGraph_t gr = nullptr;
         hipGraphExec_t ge = nullptr;
         int rc4 = WMB_OK;
@@ -2130,7 +2130,7 @@ int autotune_t(wmb_ctx* c, int reps) {
                 e = kind == 0 ? launch_ct_half<R>(c->pool, c->d_patch, L.d, L.n, coef<R>(c), c->p.ghost, c->cur, c->d_sc,
                                                   sa, c->stream)
                               : launch_update<R>(c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), c->cur, c->d_sc,
-                                                 c->d_nfloor + 2, c->d_smax + 2, 0, v, kind == 2 ? c->d_queue : nullptr,
+                                                 c->d_nfloor + COUNTERS, c->d_smax + 2, 0, v, kind == 2 ? c->d_queue : nullptr,
                                                  sa, zrec(c) ? F_FL1 + 14 : F_FL2 + 14, c->d_sc + 1, c->stream);
                 CKT(hipEventRecord(e1, c->stream));
                 CKT(hipEventSynchronize(e1));
@@ -2419,8 +2419,8 @@ int wmb_init_patches(wmb_ctx* c, int32_t npatch, const wmb_patch_desc* d, void* 
     // sink for tuning runs
     if ((rc = dev_alloc(c, &c->d_smax, 3))) return rc;
     if ((rc = dev_alloc(c, &c->d_sc, 2))) return rc;  // this step's constants; the last shared step's
-    // counters: floor activations, protected faces, and two sinks for tuning runs
-    if ((rc = dev_alloc(c, &c->d_nfloor, 4))) return rc;
+    // counters: floor activations, protected faces, and sinks of the same layout for tuning runs
+    if ((rc = dev_alloc(c, &c->d_nfloor, 2 * COUNTERS))) return rc;
     if ((rc = dev_alloc(c, &c->d_queue, 64))) return rc;
     if ((rc = dev_alloc(c, &c->d_partial, (size_t)c->wl_diag.n * DIAG_REC))) return rc;
     if ((rc = dev_alloc(c, &c->d_diag_out, 12))) return rc;
@@ -2429,7 +2429,7 @@ int wmb_init_patches(wmb_ctx* c, int32_t npatch, const wmb_patch_desc* d, void* 
     if ((rc = bind_scratch(c))) return rc;
     CKH(hipMemsetAsync(c->d_smax, 0, 3 * sizeof(unsigned long long), c->stream));
     CKH(hipMemsetAsync(c->d_sc, 0, 2 * sizeof(StepConst), c->stream));
-    CKH(hipMemsetAsync(c->d_nfloor, 0, 4 * sizeof(unsigned long long), c->stream));
+    CKH(hipMemsetAsync(c->d_nfloor, 0, 2 * COUNTERS * sizeof(unsigned long long), c->stream));
     CKH(hipMemsetAsync(c->d_queue, 0, 64 * sizeof(unsigned int), c->stream));
     CKH(hipStreamSynchronize(c->stream));
     c->cur = 0;
