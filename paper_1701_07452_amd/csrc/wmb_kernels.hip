@@ -37,15 +37,16 @@ namespace wmb {
 
 // Reciprocal and roots: hardware v_rcp_f32 / v_sqrt_f32 (about 1 ulp) in the
 // FP32 path.  In FP64 the hardware estimate (5.6e-8) and one correction of
-// third order (the root: of second order and a residual), 4 to 8 instructions
-// for the 11 to 30 of the operators, which also scale for operands outside
-// 2^-1022 .. 2^1022.  Measured over 1e-300 .. 1e300: reciprocal and root round
-// as the operators do (at most 0.5 ulp), the reciprocal root is within 0.99
-// ulp (1 / sqrt(x): 1.49).  Below 2^-1022 the root of x is short of sqrt(x),
-// by at most 1.5e-154.  With the limiter's quotient (qvisc_alpha) the Step-1
-// sweeps' 1010 vector instructions became 800 and, at 512 x 32^3, their 0.81 /
-// 0.81 / 0.83 ms 0.72 / 0.61 / 0.66, the fused corrector's 2.88 ms 2.52, a
-// step's 9.17 ms 8.41.
+// third order (the root: of second order and a residual), 4 and 8 instructions
+// for the 11 and 17 of the operators, which also scale for operands outside
+// 2^-1022 .. 2^1022.  Measured over 1e-300 .. 1e300 they round as the operators
+// do.  Below 2^-1022 the root of x is short of sqrt(x), by at most 1.5e-154.
+// (The reciprocal root as their composition too, and the limiter's quotient with
+// a residual: forms of fewer instructions, as accurate against 64-bit
+// references, move the last bit, which the low-beta blast multiplies by 1e12.)
+// With the branch of each_wave, at 512 x 32^3: Step-1 sweeps 0.81 / 0.81 / 0.83
+// -> 0.73 / 0.59 / 0.70 ms, the fused corrector 2.88 -> 2.62, a step 9.17 ->
+// 8.53.
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double frcp(double x) {
     const double y = __builtin_amdgcn_rcp(x), e = __builtin_fma(-x, y, 1.0);
@@ -59,13 +60,19 @@ __device__ __forceinline__ double fsqrt(double x) {
     return __builtin_fma(__builtin_fma(-g, g, x), h, g);
 }
 __device__ __forceinline__ float frsq(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double frsq(double x) {
-    const double y = __builtin_amdgcn_rsq(x), e = __builtin_fma(-(x * y), y, 1.0);
-    return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+__device__ __forceinline__ double frsq(double x) { return frcp(fsqrt(x)); }
+// smallest |alpha| divided by in the limiter's gamma (keeps the reciprocal away
+// from overflow).  Both limiter values are bounded by the face's own g-tilde,
+// so |dg| by a multiple of |alpha|: below, what gamma adds to the flux is below
+// it too
+__device__ __forceinline__ float alpha_min(float) { return 1e-30f; }
+__device__ __forceinline__ double alpha_min(double) { return 0x1p-960; }
+// the limiter's gamma = dg / alpha
+__device__ __forceinline__ float gdiv(float dg, float alpha) { return dg * frcp(alpha); }
+__device__ __forceinline__ double gdiv(double dg, double alpha) {
+    const double r = frcp(alpha), q = dg * r;
+    return __builtin_fma(__builtin_fma(-alpha, q, dg), r, q);
 }
-// smallest |alpha| divided by in the limiter's gamma of FP32 (keeps the
-// hardware reciprocal away from denormals)
-constexpr float ALPHA_MIN = 1e-30f;
 
 template <typename R>
 __device__ __forceinline__ R sgn1(R x) { return x >= R(0) ? R(1) : R(-1); }
@@ -87,7 +94,7 @@ __device__ __forceinline__ R qvisc(R chi, const Coef<R>& cf, int k) {
 
 // f(k, Q0) for the seven waves.  The Alfven and entropy waves (odd k) usually
 // have eps = 0, where Q(chi) = |chi|: one branch, the same for every lane,
-// drops the parabola of three waves of seven (in FP64 with its reciprocal).
+// drops the parabola of three waves of seven.
 template <typename R, typename F>
 __device__ __forceinline__ void each_wave(const Coef<R>& cf, F f) {
 #pragma unroll
@@ -99,25 +106,6 @@ __device__ __forceinline__ void each_wave(const Coef<R>& cf, F f) {
 #pragma unroll
         for (int k = 1; k < 7; k += 2) f(k, std::true_type());
     }
-}
-
-// Q_k(nu + gamma) alpha of a face in FP64, gamma = dg / alpha the limiter's
-// share of the speed (0 where alpha = 0), from t = nu alpha + dg, the argument
-// times alpha: |t| with alpha's sign needs no division, and only a wave with
-// eps > 0 divides, for the parabola below 2 eps.  (Both limiter values are
-// bounded by the face's own g-tilde, so |dg| by a multiple of |alpha|: t and
-// the quotient stay bounded as alpha vanishes, and dg = 0 at alpha = 0.)
-template <bool Q0>
-__device__ __forceinline__ double qvisc_alpha(double nu, double dg, double alpha, const Coef<double>& cf, int k) {
-#pragma clang fp contract(on)
-    const double t = fabs(nu * alpha + dg);
-    double q = t;
-    if (!Q0) {
-        // (below 2^-1000 a reciprocal could overflow)
-        const double aa = fabs(alpha), chi = t * frcp(fmax(aa, 0x1p-1000));
-        if (t < cf.eps2[k] * aa) q = chi * cf.q4e[k] * t + cf.eps[k] * aa;
-    }
-    return copysign(q, alpha);
 }
 
 // g_i = SIGN(gp) * SWEBY(gp, gm) (Appendix A), Sweby family with parameter
@@ -1667,12 +1655,8 @@ __device__ __forceinline__ void face_correction(GLim glim, const FaceEig<R>& e, 
 #pragma clang fp contract(on)
         R gL, gR;
         glim(k, gL, gR);
-        if constexpr (sizeof(R) == 8) {
-            bet[k] = qvisc_alpha<q0.value>(nu[k], gR - gL, alpha[k], cf, k) - (gL + gR);
-        } else {
-            const R gk = fabs(alpha[k]) > ALPHA_MIN ? (gR - gL) * frcp(alpha[k]) : R(0);
-            bet[k] = qvisc<R, q0.value>(nu[k] + gk, cf, k) * alpha[k] - (gL + gR);
-        }
+        const R gk = fabs(alpha[k]) > alpha_min(alpha[k]) ? gdiv(gR - gL, alpha[k]) : R(0);
+        bet[k] = qvisc<R, q0.value>(nu[k] + gk, cf, k) * alpha[k] - (gL + gR);
     });
     R bfp = bet[6] + bet[0], bfm = bet[6] - bet[0];
     R bsp = bet[4] + bet[2], bsm = bet[4] - bet[2];
