@@ -1238,6 +1238,41 @@ struct alignas(8 * sizeof(R)) Rec8 {
     R v[8];
 };
 
+// The records in LDS.  FP64 records are 64 bytes, so the same 16-byte part of
+// consecutive records lies in four of the sixteen bank groups: part c of record
+// i is kept in place c ^ (i / 4 mod 4), which uses all sixteen (bank
+// conflicts took 35% of the sweeps' cycles; 64 x 32^3 FP64 1.091 -> 1.075 ms a
+// step, 512 x 32^3 1% less).
+template <typename R>
+struct RecLds {
+    unsigned char* p;
+    using Part = double __attribute__((ext_vector_type(2)));
+    __device__ __forceinline__ Part* part(int i, int c) const {
+        return reinterpret_cast<Part*>(p + ((i * 64 + ((i << 2) & 0x30)) ^ (c << 4)));
+    }
+    __device__ __forceinline__ Rec8<R> operator[](int i) const {
+        if constexpr (sizeof(R) == 4) {
+            return reinterpret_cast<const Rec8<R>*>(p)[i];
+        } else {
+            Rec8<R> r;
+#pragma unroll
+            for (int c = 0; c < 4; c++) {
+                const Part v = *part(i, c);
+                r.v[2 * c] = v.x, r.v[2 * c + 1] = v.y;
+            }
+            return r;
+        }
+    }
+    __device__ __forceinline__ void put(int i, const Rec8<R>& r) const {
+        if constexpr (sizeof(R) == 4) {
+            reinterpret_cast<Rec8<R>*>(p)[i] = r;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; c++) *part(i, c) = Part{r.v[2 * c], r.v[2 * c + 1]};
+        }
+    }
+};
+
 template <typename R>
 struct FaceEig {
     R rho, sq, vx, vy, vz, b1, b2, X;
@@ -1711,8 +1746,8 @@ __global__ void __launch_bounds__(1024, sizeof(R) == 4 && !PROT ? 8 : 4) sweep_k
                                                      const unsigned* __restrict__ nbr) {
     extern __shared__ unsigned char smem_raw[];
     const int nthr = P * W;
-    Rec8<R>* shp = reinterpret_cast<Rec8<R>*>(smem_raw);  // zone primitives
-    Rec8<R>* shg = shp + nthr;                             // face g-tilde
+    const RecLds<R> shp{smem_raw};  // zone primitives
+    const RecLds<R> shg{smem_raw + nthr * sizeof(Rec8<R>)};                           // face g-tilde
 
     constexpr int FA = (D == 0) ? 1 : 0;                 // fast transverse axis
     constexpr int SA = (D == 0) ? 2 : (D == 1 ? 2 : 1);  // slow transverse axis
@@ -1806,9 +1841,9 @@ __global__ void __launch_bounds__(1024, sizeof(R) == 4 && !PROT ? 8 : 4) sweep_k
                     return a == 3 ? sld(f) : (a == 2 || D == 2 ? sload(z0, rp, us[a], f) : bload(z0, rls, us[a], f));
                 },
                 qs, VB, VW, z);
-            shp[tid] = zone_record<R, D, STAGE>(z, cf, prm, *sc);
+            shp.put(tid, zone_record<R, D, STAGE>(z, cf, prm, *sc));
         } else {
-            shp[tid] = zone_phase<R, D, STAGE>(rs, rw, xo, st, qs, VB, cf, prm, *sc);
+            shp.put(tid, zone_phase<R, D, STAGE>(rs, rw, xo, st, qs, VB, cf, prm, *sc));
         }
     }
     __syncthreads();
@@ -1824,7 +1859,7 @@ __global__ void __launch_bounds__(1024, sizeof(R) == 4 && !PROT ? 8 : 4) sweep_k
         else bf = (STAGE == 1) ? bload(z0, rs, xo, qs + (8 + D) * VB) : bload(z0, rw, xo, (unsigned)(F_BH + D) * VB);
         Rec8<R> gr;
         face_phase<R, PROT>(shp[tid - sstep], shp[tid], bf, lam, cf, e, alpha, nu, gr, prot);
-        shg[tid] = gr;
+        shg.put(tid, gr);
     }
     __syncthreads();
 
@@ -2043,7 +2078,7 @@ __device__ __forceinline__ constexpr int row_a1(int r) { return r < 5 ? r : (r =
 __device__ __forceinline__ constexpr int row_a2(int r) { return r < 5 ? r : (r == 5 ? 5 : 6); }
 
 template <typename R, int D, bool MM, bool PROT, bool SH>
-__device__ __forceinline__ void xy_flux(const Rec8<R>* shp, const Rec8<R>* shg, int tid, int step, R bf,
+__device__ __forceinline__ void xy_flux(const RecLds<R> shp, const RecLds<R> shg, int tid, int step, R bf,
                                         const FaceEig<R>& e, const R alpha[7], const R nu[7], bool prot,
                                         const Coef<R>& cf, R il, __amdgpu_buffer_rsrc_t rw, unsigned xo, unsigned VB,
                                         unsigned long long* nprot, const PatchDev& Pt, int x, int y, int k) {
@@ -2074,8 +2109,8 @@ __global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512, sizeof(R) == 4 ? 
                    unsigned long long* __restrict__ nprot, const unsigned* __restrict__ nbr) {
     extern __shared__ unsigned char smem_raw[];
     const int P = (int)blockDim.x, RT = (int)blockDim.y;
-    Rec8<R>* shp = reinterpret_cast<Rec8<R>*>(smem_raw);  // zone records: x, then y
-    Rec8<R>* shg = shp + P * RT;                          // face g-tilde: x, then y
+    const RecLds<R> shp{smem_raw};  // zone records: x, then y
+    const RecLds<R> shg{smem_raw + P * RT * sizeof(Rec8<R>)};                        // face g-tilde: x, then y
     constexpr unsigned ES = sizeof(R);
 
     const WorkItem wi = work[blockIdx.x];
@@ -2195,7 +2230,7 @@ __global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512, sizeof(R) == 4 ? 
         // the z record first (stored at once), so that its temporaries are
         // dead before the x and y records are formed
         __builtin_amdgcn_sched_barrier(0);
-        if (needX) shp[tid] = zone_record<R, 0, 2>(zx, cf, prm, scv);
+        if (needX) shp.put(tid, zone_record<R, 0, 2>(zx, cf, prm, scv));
         if (needY) ry = zone_record<R, 1, 2>(zy, cf, prm, scv);
     }
     if (!faces) return;  // a z-record plane: no barrier follows for the whole block
@@ -2212,7 +2247,7 @@ __global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512, sizeof(R) == 4 ? 
             bf = SH ? sld((unsigned)F_BH * VW) : bload(z0, rw, xo, (unsigned)F_BH * VB);
             Rec8<R> gr;
             face_phase<R, PROT>(shp[tid - 1], shp[tid], bf, sc_lam(scv, 0, R(0)), cf, e, alpha, nu, gr, prot);
-            shg[tid] = gr;
+            shg.put(tid, gr);
         }
         __syncthreads();
         if (face && tx >= 2 && tx <= P - 2)
@@ -2220,7 +2255,7 @@ __global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512, sizeof(R) == 4 ? 
                                         nprot, Pt, x, y, k);
     }
     __syncthreads();  // the x records and g-tilde are read
-    if (needY) shp[tid] = ry;
+    if (needY) shp.put(tid, ry);
     __syncthreads();
 
     // ---------------- y faces: y between rows ty - 1 and ty ----------------
@@ -2234,7 +2269,7 @@ __global__ void __launch_bounds__(sizeof(R) == 4 ? 1024 : 512, sizeof(R) == 4 ? 
             bf = SH ? sld((unsigned)(F_BH + 1) * VW) : bload(z0, rw, xo, (unsigned)(F_BH + 1) * VB);
             Rec8<R> gr;
             face_phase<R, PROT>(shp[tid - P], shp[tid], bf, sc_lam(scv, 1, R(0)), cf, e, alpha, nu, gr, prot);
-            shg[tid] = gr;
+            shg.put(tid, gr);
         }
         __syncthreads();
         if (face && ty >= 2 && ty <= rows - 2)
