@@ -122,6 +122,7 @@ struct wmb_ctx {
     bool serial = false;  // scratch groups: the groups' steps run one after another on the main stream
     hipStream_t gstream[4] = {};  // group streams 1..3 (group 0 runs on the main stream), borrowed
     hipEvent_t ev_g[4] = {};
+    int xy_rows_s = 0;    // the fused corrector's band rows in shared-halo steps
     int upd_zones = 256;  // zones a tile plane of Steps 8-11 (the update's block size)
     int cth_tx = 40;      // widest tile of Steps 3-4 along x (zones; 256 a tile plane)
     int upd_queue = 0;    // Steps 8-11 launch: 0 one block a tile, 1 persistent blocks on per-XCD queues
@@ -151,6 +152,16 @@ struct wmb_ctx {
     hipGraph_t graph[4] = {};
     std::string err;
     std::vector<void*> owned;  // library-owned device allocations
+    // The small lists of wmb_init_patches: parts of a few device chunks, each filled on
+    // the host and copied once (an allocation and a copy for every list took a
+    // fifth of the call for one patch).  Kept until the context ends.
+    struct Chunk {
+        char* d;
+        size_t used;
+        std::vector<char> h;
+    };
+    std::vector<Chunk> chunks;
+    bool chunked = false;      // wmb_init_patches is running
     hipEvent_t* marks = nullptr;  // when set, an event is recorded after every kernel class
     int mark_cap = 0;             // events at marks
     int nmark = 0;
@@ -333,9 +344,31 @@ std::vector<WorkItem> in_turn(const std::vector<WorkItem>& items, const std::vec
 
 template <typename T>
 int upload(wmb_ctx* c, T** ptr, const std::vector<T>& h) {
+    const size_t bytes = sizeof(T) * h.size();
+    if (c->chunked && bytes <= 32768) {  // (larger ones: their copy alone costs more than the allocation)
+        const size_t room = (bytes + 255) / 256 * 256 + 256;
+        if (c->chunks.empty() || c->chunks.back().used + room > c->chunks.back().h.size()) {
+            const size_t size = std::max(room + 256, (size_t)1 << 18);
+            char* p = nullptr;
+            int rc = dev_alloc(c, &p, size);
+            if (rc) return rc;
+            c->chunks.push_back({p, 256, std::vector<char>(size)});  // (no list at its start, which release() would free)
+        }
+        auto& k = c->chunks.back();
+        if (bytes) std::memcpy(k.h.data() + k.used, h.data(), bytes);
+        *ptr = reinterpret_cast<T*>(k.d + k.used);
+        k.used += room;
+        return WMB_OK;
+    }
     int rc = dev_alloc(c, ptr, h.size());
     if (rc) return rc;
     if (!h.empty()) CKH(hipMemcpy(*ptr, h.data(), sizeof(T) * h.size(), hipMemcpyHostToDevice));
+    return WMB_OK;
+}
+int flush_chunks(wmb_ctx* c) {
+    for (auto& k : c->chunks) CKH(hipMemcpy(k.d, k.h.data(), k.used, hipMemcpyHostToDevice));
+    c->chunks.clear();
+    c->chunked = false;
     return WMB_OK;
 }
 
@@ -1376,6 +1409,7 @@ int set_xy(wmb_ctx* c, int rb, int rs = 0) {
         G.RTs = xy_rt(c, G.n, r, true);
     }
     c->xy_rows = rb > 0 ? rb : 0;
+    c->xy_rows_s = rs > 0 ? rs : 0;
     return WMB_OK;
 }
 
@@ -2203,13 +2237,18 @@ std::string tune_key(const wmb_ctx* c) {
 
 std::vector<int32_t> tuning_quads(const wmb_ctx* c) {
     std::vector<int32_t> q;
+    const bool sh = shared_now(c);
     for (int stage = 0; stage < 2; stage++)
         for (int d = 0; d < 3; d++)
-            for (const auto& G : c->sweeps[d][stage]) q.insert(q.end(), {stage + 1, d, G.n, G.W});
+            for (const auto& G : c->sweeps[d][stage]) {
+                // (the shape the steps run, where wmb_set_tuning takes it)
+                const int W = sh ? (d == 2 && stage == 1 && c->xy_rows > 0 ? G.W3 : G.Ws) : G.W;
+                q.insert(q.end(), {stage + 1, d, G.n, shape_ok(d, G.P, c->esize, W, stage + 1) ? W : G.W});
+            }
     q.insert(q.end(), {3, 0, 0, c->cth_tx});
     q.insert(q.end(), {4, 0, 0, c->upd_zones});
     q.insert(q.end(), {5, 0, 0, c->upd_queue});
-    q.insert(q.end(), {6, 0, 0, c->xy_rows});
+    q.insert(q.end(), {6, 0, 0, sh && c->xy_rows > 0 && xy_ok(c, c->xy_rows_s) ? c->xy_rows_s : c->xy_rows});
     return q;
 }
 
@@ -2393,6 +2432,7 @@ int wmb_init_patches(wmb_ctx* c, int32_t npatch, const wmb_patch_desc* d, void* 
         P.present = 1;
     }
     int rc;
+    c->chunked = true;
     if ((rc = upload(c, &c->d_patch, c->hpatch))) return rc;
     if ((rc = build_fill_lists(c))) return rc;
     if ((rc = build_box_list(c, BOX_INTERIOR, c->wl_int))) return rc;
@@ -2415,6 +2455,7 @@ int wmb_init_patches(wmb_ctx* c, int32_t npatch, const wmb_patch_desc* d, void* 
         c->serial = true;
         if ((rc = apply_groups(c, c->p.scratch_groups))) return rc;
     }
+    if ((rc = flush_chunks(c))) return rc;
     // the signal-speed maxima of the current and the previous state, and a
     // sink for tuning runs
     if ((rc = dev_alloc(c, &c->d_smax, 3))) return rc;
