@@ -2338,11 +2338,13 @@ int apply_groups(wmb_ctx* c, int groups) {
     for (int d = 0; d < 3; d++)
         for (int stage = 0; stage < 2; stage++)
             for (auto& SG : c->sweeps[d][stage]) {
+                const int ws = SG.Ws, w3 = SG.W3;  // the shared-halo shapes stay
                 int rc = set_group_W(c, d, stage, SG, SG.W);
+                if (!rc && ws && (ws != SG.Ws || w3 != SG.W3)) rc = set_group_Ws(c, d, stage, SG, ws, w3);
                 if (rc) return rc;
             }
     if (c->xy_rows > 0) {
-        int rc = set_xy(c, c->xy_rows);
+        int rc = set_xy(c, c->xy_rows, c->xy_rows_s);
         if (rc) return rc;
     }
     return build_ct_update_lists(c);
