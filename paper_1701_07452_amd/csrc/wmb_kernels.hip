@@ -37,10 +37,16 @@ namespace wmb {
 
 // Reciprocal and roots: hardware v_rcp_f32 / v_sqrt_f32 (about 1 ulp) in the
 // FP32 path.  In FP64 the hardware estimate (5.6e-8) and one correction of
-// third order (the root: of second order and a residual), 4 and 8 instructions
-// for the 11 and 17 of the operators, which also scale for operands outside
-// 2^-1022 .. 2^1022.  Measured over 1e-300 .. 1e300 they round as the operators
-// do.  Below 2^-1022 the root of x is short of sqrt(x), by at most 1.5e-154.
+// third order (the root: of second order and a residual), 5 and 8 instructions
+// for the 11 and 17 of the operators.  Measured over all operands: the
+// reciprocal rounds as the operator does (0, infinities and NaN by the fix-up;
+// only below 2^-1024, where the operator overflows, it is NaN), the root of a
+// normal number to within a unit in the last place.  The root of a subnormal x
+// has a residual rounded to 2^-1074, so its error is up to that of x being
+// rounded by half of that.  It has to be that good: frsq of the transverse
+// field's square makes a unit vector, so a root that is short by a factor,
+// however small itself, makes Alfven and slow waves that are too strong by its
+// square (clamped at 2^-1022, fields of 1e-157 blew a sheared flow up).
 // (The reciprocal root as their composition too, and the limiter's quotient with
 // a residual: forms of fewer instructions, as accurate against 64-bit
 // references, move the last bit, which the low-beta blast multiplies by 1e12.)
@@ -50,11 +56,11 @@ namespace wmb {
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double frcp(double x) {
     const double y = __builtin_amdgcn_rcp(x), e = __builtin_fma(-x, y, 1.0);
-    return __builtin_fma(y, __builtin_fma(e, e, e), y);
+    return __builtin_amdgcn_div_fixup(__builtin_fma(y, __builtin_fma(e, e, e), y), x, 1.0);
 }
 __device__ __forceinline__ float fsqrt(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ __forceinline__ double fsqrt(double x) {
-    const double y = __builtin_amdgcn_rsq(fmax(x, 0x1p-1022));  // (finite for x = 0)
+    const double y = __builtin_amdgcn_rsq(fmax(x, 0x1p-1074));  // (finite for x = 0)
     const double g0 = x * y, h = 0.5 * y;
     const double g = __builtin_fma(g0, __builtin_fma(-h, g0, 0.5), g0);
     return __builtin_fma(__builtin_fma(-g, g, x), h, g);

@@ -60,3 +60,38 @@ def test_vanishing_waves(wmb, tiny):
         assert np.abs(f).max() <= 100 * tiny
     sim.close()
     orc.close()
+
+
+@pytest.mark.parametrize("walls", [False, True])
+@pytest.mark.parametrize("field", [1e-152, 1e-155, 1e-157, 1e-160])
+def test_vanishing_field(wmb, field, walls):
+    """A sheared flow in a uniform transverse field so weak that its square is
+    subnormal (B_x = 0): the unit vector along it comes from a root of that
+    square.  Two steps (periodic patches, which share their halos, and walled
+    ones): the flow within 1e-11 of the oracle's scale, but for what the
+    square's rounding to multiples of 2^-1074 does: it moves the unit vector's
+    square by two parts in field^2 / 2^-1074 on each side, and each of the six
+    sweeps of a step its share of the flux, less than the flow's scale.  (The
+    field itself follows the upwind picks of a mass flux that is rounding noise
+    here, as it does at any strength below 1e-8.)"""
+    G = I.patch_grid([16], [8, 8], [8], periodic=(not walls, True, True))
+    x = 2 * np.pi * (np.arange(G.shape[2]) + 0.5) / G.shape[2]
+    q = np.zeros((8,) + G.shape)
+    b = np.zeros((3,) + G.shape)
+    q[0], q[2], q[3] = 1.0, 0.3 * np.sin(x), 0.3 * np.cos(x)
+    q[5], q[6] = field, 0.5 * field
+    b[1], b[2] = field, 0.5 * field
+    q[7] = 1.5 + 0.5 * (q[2] ** 2 + q[3] ** 2)
+    kw = dict(dx=(1 / 16,) * 3)
+    sim = gpu_sim(wmb, G, q, b, 0, **kw)
+    orc = oracle_sim(G, q, b, **kw)
+    _lockstep(sim, orc, 2)
+    qg, bg = I.gather(G, [sim.get_state(i) for i in range(G.npatch)])
+    qo, bo = oracle_gather(G, orc)
+    tol = 1e-11 + 2 * 6 * 2 * 2 * (2.0 ** -1074 / field / field)
+    for c, scale in ((0, 1.0), (1, 0.3), (2, 0.3), (3, 0.3), (7, 1.5)):
+        err = float(np.abs(qg[c] - qo[c]).max())
+        assert err <= tol * scale, (c, err)
+    assert np.isfinite(qg).all() and np.isfinite(bg).all()
+    sim.close()
+    orc.close()
