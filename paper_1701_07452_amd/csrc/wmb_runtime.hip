@@ -946,6 +946,8 @@ std::vector<int> x_rows(const wmb_ctx* c) { return rows_of(c->npatch, c->desc.da
 // The stage work lists (sweeps, Steps 3-4, Steps 8-11) cover the present,
 // active patches; frozen and absent ones are left out when the lists are
 // planned again (replan), so their blocks are not launched at all.
+// The shared-halo lists cover every patch whatever is frozen or absent when
+// they are built: they run only when no patch is.
 bool in_plan(const wmb_ctx* c, int p) { return c->hpatch[p].present && c->hpatch[p].active; }
 
 std::vector<WorkItem> tile_items(const wmb_ctx* c, int lo, int hi, int zlo, int zhi, int txmax_allowed, int maxz,
@@ -975,7 +977,7 @@ std::vector<WorkItem> tile_items(const wmb_ctx* c, int lo, int hi, int zlo, int 
     }
     const int zlen = plan_zlen(tiles, ez, cap);
     for (int p = 0; p < c->npatch; p++) {
-        if (!in_plan(c, p) || (sgroup >= 0 && c->pgroup[p] != sgroup)) continue;
+        if ((!turn && !in_plan(c, p)) || (sgroup >= 0 && c->pgroup[p] != sgroup)) continue;
         const Cut& q = cuts[p];
         const int e = c->desc[p].n[2] + zhi + 1 - zlo, mz = (e + zlen - 1) / zlen;
         for (int bz = 0; bz < mz; bz++) {
@@ -1081,8 +1083,8 @@ int build_ct_update_lists(wmb_ctx* c) {
     const std::vector<int> rows = x_rows(c);
     int rc = build_cth_list(c, c->cth_tx, c->wl_cth);
     if (!rc) rc = build_upd_list(c, c->upd_zones, &rows, c->wl_upd);
-    if (!rc && c->d_nbr && c->all_in) rc = build_cth_list(c, c->cth_tx, c->wl_cth_s, -1, true);
-    if (!rc && c->d_nbr && c->all_in) rc = build_upd_list(c, c->upd_zones, &rows, c->wl_upd_s, -1, true);
+    if (!rc && c->d_nbr) rc = build_cth_list(c, c->cth_tx, c->wl_cth_s, -1, true);
+    if (!rc && c->d_nbr) rc = build_upd_list(c, c->upd_zones, &rows, c->wl_upd_s, -1, true);
     if (c->ngroups > 1 && c->wl_cth_g.size() < (size_t)c->ngroups) {
         c->wl_cth_g.resize(c->ngroups);
         c->wl_upd_g.resize(c->ngroups);
@@ -1188,7 +1190,7 @@ std::vector<WorkItem> sweep_items(const wmb_ctx* c, int d, int n, int tlo, int t
     };
     std::vector<WorkItem> items;
     for (int p = 0; p < c->npatch; p++) {
-        if (c->desc[p].n[d] != n || !in_plan(c, p)) continue;
+        if (c->desc[p].n[d] != n || (!sh && !in_plan(c, p))) continue;
         if (group >= 0 && c->pgroup[p] != group) continue;
         const int nf = c->desc[p].n[FA], ns = c->desc[p].n[SA];
         const int tf = nf + thi - tlo + 1;
@@ -1234,7 +1236,7 @@ bool prot_on(const wmb_ctx* c) { return c->p.rho_protect > 0.0 || c->p.p_protect
 // either form, the corrector from q^n in the pencil form), W3 for the z
 // corrector from records (either form; 0: no list of its own).
 int set_group_Ws(wmb_ctx* c, int d, int stage, SweepGroup& G, int W, int W3) {
-    if (!c->d_nbr || !c->all_in) return WMB_OK;  // built when the batch can share (replan)
+    if (!c->d_nbr) return WMB_OK;
     if (W < 0 && stage == 1)
         W = choose_W(d, G.Ps(), c->esize, stage, group_pencils(c, d, G.n, 0, -1), prot_on(c), false, true);
     if (W3 < -512) W3 += 512;
@@ -1297,7 +1299,7 @@ int set_group_W(wmb_ctx* c, int d, int stage, SweepGroup& G, int W) {
 std::vector<WorkItem> xy_items(const wmb_ctx* c, int n, int rb, int group = -1, bool sh = false) {
     std::vector<WorkItem> items;
     for (int p = 0; p < c->npatch; p++) {
-        if (c->desc[p].n[0] != n || !in_plan(c, p)) continue;
+        if (c->desc[p].n[0] != n || (!sh && !in_plan(c, p))) continue;
         if (group >= 0 && c->pgroup[p] != group) continue;
         const int* e = c->desc[p].n;
         const int E = e[1] + (sh ? 0 : 3), lo = sh ? 0 : -1, nb = (E + rb - 1) / rb;
@@ -1398,7 +1400,7 @@ int set_xy(wmb_ctx* c, int rb, int rs = 0) {
             if (!gi.empty() && (rc = upload(c, &G.wxyg[g].d, gi))) return rc;
         }
         G.RT = xy_rt(c, G.n, rb);
-        if (!c->d_nbr || !c->all_in) continue;
+        if (!c->d_nbr) continue;
         // (the patch's own rows may cut into fewer, longer bands than the halo
         // scheme's, past what a block holds: then shorter ones)
         int r = rs;
@@ -1561,19 +1563,6 @@ int replan(wmb_ctx* c) {
     for (int g = 0; g < c->ngroups && c->ngroups > 1 && !rc; g++) {
         rc = put(c->wl_cth_g[g], cth_items(c, c->cth_tx, g));
         if (!rc) rc = put(c->wl_upd_g[g], upd_items(c, c->upd_zones, &rows, g));
-    }
-    // the shared-halo lists cover every patch; those that a retune left out
-    // while a patch was frozen or absent are built now
-    if (!rc && c->d_nbr && c->all_in) {
-        const bool tiles = !c->wl_cth_s.d || !c->wl_upd_s.d;
-        if (tiles) rc = build_ct_update_lists(c), regrid = true;
-        for (int d = 0; d < 3 && !rc; d++)
-            for (int stage = 0; stage < 2 && !rc; stage++)
-                for (auto& G : c->sweeps[d][stage])
-                    if (!rc && !G.wls.d) rc = set_group_Ws(c, d, stage, G, G.W, G.W), regrid = true;
-        bool xy = false;
-        for (auto& G : c->sweeps[0][1]) xy = xy || (c->xy_rows > 0 && !G.wxys.d);
-        if (!rc && xy) rc = set_xy(c, c->xy_rows), regrid = true;
     }
     if (regrid) free_graphs(c);
     return rc;

@@ -131,3 +131,27 @@ def test_shared_and_frozen_in_turn(wmb, prec):
         sim.close()
     for a, c in zip(*out):
         assert np.array_equal(a, c), float(np.abs(a - c).max())
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("how", ["tuning", "schedule"])
+def test_lists_rebuilt_while_frozen(wmb, how, prec):
+    """Work lists rebuilt between a freeze and the next step (a retune, or
+    another schedule and back): the shared steps after the thaw leave out no
+    patch."""
+    out = []
+    for shared in (True, False):
+        G, sim = _sim(wmb, "fused", prec, shared)
+        sim.run_steps(1)
+        sim.set_active(1, False)
+        if how == "tuning":
+            sim.set_tuning({(6, 0, 0): 3, (1, 0, 16): 2, (1, 1, 12): 4, (2, 2, 10): 4, (3, 0, 0): 13})
+        else:
+            sim.set_schedule(2)
+            sim.set_schedule(1)
+        sim.set_active(1, True)
+        sim.run_steps(3)
+        out.append(_state(G, sim))
+        sim.close()
+    for a, c in zip(*out):
+        assert np.array_equal(a, c), float(np.abs(a - c).max())
