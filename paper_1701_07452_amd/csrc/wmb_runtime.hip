@@ -587,29 +587,31 @@ hipError_t launch_group(wmb_ctx* c, int d, int stage, const SweepGroup& G, const
                            shared_arg(c, sh), st);
 }
 
-// with the fused x/y corrector on, the z predictor records it stores are
+// with the fused x/y corrector on (the schemes have it on apart: in FP64 only
+// shared-halo steps are faster with it), the z predictor records it stores are
 // what the z corrector reads (stage 3), so the z sweep follows it
-bool zrec(const wmb_ctx* c) { return c->xy_rows > 0; }
+bool zrec(const wmb_ctx* c, bool sh) { return (sh ? c->xy_rows_s : c->xy_rows) > 0; }
 
 // the z corrector sweeps of one group's list: from the stored records after
 // the fused x/y corrector, else from q^n and the Step-1 fluxes
 template <typename R>
 hipError_t launch_corr_z(wmb_ctx* c, int g, int cur, unsigned long long* nprot, hipStream_t st, bool sh) {
     for (auto& G : c->sweeps[2][1]) {
-        const DevList& L = sh ? (zrec(c) ? G.wl3 : G.wls) : (g < 0 ? G.wl : G.wlg[g]);
-        hipError_t r = launch_group<R>(c, 2, zrec(c) ? 3 : 2, G, L, cur, nprot, st, sh);
+        const bool zr = zrec(c, sh);
+        const DevList& L = sh ? (zr ? G.wl3 : G.wls) : (g < 0 ? G.wl : G.wlg[g]);
+        hipError_t r = launch_group<R>(c, 2, zr ? 3 : 2, G, L, cur, nprot, st, sh);
         if (r != hipSuccess) return r;
     }
     return hipSuccess;
 }
 
 // the corrector's x sweeps of one group's list (wl: all patches; g >= 0: step
-// group g), as the fused x/y kernel when xy_rows > 0
+// group g), as the fused x/y kernel where the scheme has it on
 template <typename R>
 hipError_t launch_corr_x(wmb_ctx* c, int g, int cur, unsigned long long* nprot, hipStream_t st, bool sh) {
     for (auto& G : c->sweeps[0][1]) {
         hipError_t r;
-        if (c->xy_rows > 0) {
+        if (zrec(c, sh)) {
             const DevList& L = sh ? G.wxys : (g < 0 ? G.wxy : G.wxyg[g]);
             r = launch_corr_xy<R>(c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), cur, c->d_sc, sh ? G.Ps() : G.P,
                                   sh ? G.RTs : G.RT, nprot, shared_arg(c, sh), st);
@@ -731,11 +733,11 @@ int run_step(wmb_ctx* c, bool split = false) {
         CKH(hipStreamWaitEvent(c->side2, c->ev_br[2], 0));
         // with the fused x/y corrector the y branch is empty; when it stores
         // the z records, the z corrector follows it on the main stream
-        if (!c->xy_rows) {
+        if (!zrec(c, sh)) {
             e = sweeps(1, 2, &SweepGroup::wl, c->side);
             STEPCK("sweep2");
         }
-        if (!zrec(c)) {
+        if (!zrec(c, sh)) {
             e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + COUNT_PAD, c->side2, sh);
             STEPCK("sweep2");
         }
@@ -743,7 +745,7 @@ int run_step(wmb_ctx* c, bool split = false) {
         CKH(hipEventRecord(c->ev_br[4], c->side2));
         e = launch_corr_x<R>(c, -1, cur, c->d_nfloor + COUNT_PAD, c->stream, sh);
         STEPCK("sweep2");
-        if (zrec(c)) {
+        if (zrec(c, sh)) {
             e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + COUNT_PAD, c->stream, sh);
             STEPCK("sweep2");
         }
@@ -753,7 +755,7 @@ int run_step(wmb_ctx* c, bool split = false) {
         for (int d = 0; d < 3; d++) {
             if (d == 0) e = launch_corr_x<R>(c, -1, cur, c->d_nfloor + COUNT_PAD, c->stream, sh);
             else if (d == 2) e = launch_corr_z<R>(c, -1, cur, c->d_nfloor + COUNT_PAD, c->stream, sh);
-            else if (!c->xy_rows) e = sweeps(d, 2, &SweepGroup::wl, c->stream);
+            else if (!zrec(c, sh)) e = sweeps(d, 2, &SweepGroup::wl, c->stream);
             STEPCK("sweep2");
             mark(c);
         }
@@ -761,7 +763,7 @@ int run_step(wmb_ctx* c, bool split = false) {
     const DevList& lu = sh ? c->wl_upd_s : c->wl_upd;
     e = launch_update<R>(c->pool, c->d_patch, lu.d, lu.n, c->dp, coef<R>(c), cur, c->d_sc, c->d_nfloor, c->d_smax,
                          c->keep_edges ? 1 : 0, c->upd_zones, c->upd_queue ? c->d_queue : nullptr, sa,
-                         zrec(c) ? F_FL1 + 14 : F_FL2 + 14, c->d_sc + 1, c->stream);
+                         zrec(c, sh) ? F_FL1 + 14 : F_FL2 + 14, c->d_sc + 1, c->stream);
     STEPCK("update");
     mark(c);
     stepped(c, sh);
@@ -1373,16 +1375,13 @@ int choose_xy(const wmb_ctx* c, bool sh) {
     return best;
 }
 
-// Switch the fused x/y corrector off (rb = 0) or on with bands of at most rb
-// rows (rs in shared-halo steps; 0: rb too): (re)build its lists, freeing the
-// ones they replace.
-int set_xy(wmb_ctx* c, int rb, int rs = 0) {
-    if (rs <= 0) rs = rb;
+// Switch the fused x/y corrector of the halo scheme off (rb = 0) or on with
+// bands of at most rb rows: (re)build its lists, freeing the ones they
+// replace.
+int set_xy(wmb_ctx* c, int rb) {
     for (auto& G : c->sweeps[0][1]) {
         release(c, G.wxy.d);
         G.wxy = DevList{};
-        release(c, G.wxys.d);
-        G.wxys = DevList{};
         for (auto& L : G.wxyg) {
             release(c, L.d);
             L = DevList{};
@@ -1400,18 +1399,29 @@ int set_xy(wmb_ctx* c, int rb, int rs = 0) {
             if (!gi.empty() && (rc = upload(c, &G.wxyg[g].d, gi))) return rc;
         }
         G.RT = xy_rt(c, G.n, rb);
-        if (!c->d_nbr) continue;
-        // (the patch's own rows may cut into fewer, longer bands than the halo
-        // scheme's, past what a block holds: then shorter ones)
-        int r = rs;
-        while (r > 1 && !xy_fits(c, G.Ps(), xy_rt(c, G.n, r, true))) r--;
-        std::vector<WorkItem> si = xy_items(c, G.n, r, -1, true);
-        G.wxys.n = (int)si.size();
-        if ((rc = upload(c, &G.wxys.d, si))) return rc;
-        G.RTs = xy_rt(c, G.n, r, true);
     }
     c->xy_rows = rb > 0 ? rb : 0;
-    c->xy_rows_s = rs > 0 ? rs : 0;
+    return WMB_OK;
+}
+
+// The same for shared-halo steps (where the batch can run them).
+int set_xy_s(wmb_ctx* c, int rb) {
+    if (!c->d_nbr) return WMB_OK;
+    for (auto& G : c->sweeps[0][1]) {
+        release(c, G.wxys.d);
+        G.wxys = DevList{};
+        if (rb <= 0) continue;
+        // (the patch's own rows may cut into fewer, longer bands than the halo
+        // scheme's, past what a block holds: then shorter ones)
+        int r = rb;
+        while (r > 1 && !xy_fits(c, G.Ps(), xy_rt(c, G.n, r, true))) r--;
+        std::vector<WorkItem> items = xy_items(c, G.n, r, -1, true);
+        G.wxys.n = (int)items.size();
+        int rc = upload(c, &G.wxys.d, items);
+        if (rc) return rc;
+        G.RTs = xy_rt(c, G.n, r, true);
+    }
+    c->xy_rows_s = rb > 0 ? rb : 0;
     return WMB_OK;
 }
 
@@ -1902,10 +1912,11 @@ int autotune_t(wmb_ctx* c, int reps) {
     const SharedHalo sa = shared_arg(c, sh);
     const SweepPart part = sh ? PART_INTERIOR : PART_ALL;
     // the separate sweeps are timed first; the fused x/y corrector after them
-    if (c->xy_rows > 0) {
-        int rc0 = set_xy(c, 0);
-        if (rc0) return cleanup(rc0);
-    }
+    auto set_rows = [&](int rb) -> int {
+        int rc0 = set_xy(c, rb);
+        return rc0 ? rc0 : set_xy_s(c, rb);
+    };
+    if (int rc0 = set_rows(0)) return cleanup(rc0);
     for (int stage = 0; stage < 2; stage++) {
         if (stage == 1) {
             // intermediates the corrector sweeps read: Step-1 fluxes, edges, b^{n+1/2}
@@ -2112,7 +2123,7 @@ int autotune_t(wmb_ctx* c, int reps) {
         best_zw = zw;
         for (int rb : {4, 6, 8, 9, 11, 13, 16, 18}) {
             if (!xy_ok(c, rb)) continue;
-            if ((rc2 = set_xy(c, rb))) return cleanup(rc2);
+            if ((rc2 = set_rows(rb))) return cleanup(rc2);
             for (int W : {-256, -64, 16}) {
                 std::vector<int> cur_zw;
                 for (auto& G : c->sweeps[2][1]) {
@@ -2125,7 +2136,7 @@ int autotune_t(wmb_ctx* c, int reps) {
                 if (t < best) best = t, best_rb = rb, best_zw = cur_zw;
             }
         }
-        if ((rc2 = set_xy(c, best_rb))) return cleanup(rc2);
+        if ((rc2 = set_rows(best_rb))) return cleanup(rc2);
         size_t i = 0;
         for (auto& G : c->sweeps[2][1]) {
             const int w = best_zw[i++];
@@ -2154,7 +2165,7 @@ int autotune_t(wmb_ctx* c, int reps) {
                                                   sa, c->stream)
                               : launch_update<R>(c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), c->cur, c->d_sc,
                                                  c->d_nfloor + COUNTERS, c->d_smax + 2, 0, v, kind == 2 ? c->d_queue : nullptr,
-                                                 sa, zrec(c) ? F_FL1 + 14 : F_FL2 + 14, c->d_sc + 1, c->stream);
+                                                 sa, zrec(c, sh) ? F_FL1 + 14 : F_FL2 + 14, c->d_sc + 1, c->stream);
                 CKT(hipEventRecord(e1, c->stream));
                 CKT(hipEventSynchronize(e1));
                 float t = 0.f;
@@ -2231,13 +2242,13 @@ std::vector<int32_t> tuning_quads(const wmb_ctx* c) {
         for (int d = 0; d < 3; d++)
             for (const auto& G : c->sweeps[d][stage]) {
                 // (the shape the steps run, where wmb_set_tuning takes it)
-                const int W = sh ? (d == 2 && stage == 1 && c->xy_rows > 0 ? G.W3 : G.Ws) : G.W;
+                const int W = sh ? (d == 2 && stage == 1 && c->xy_rows_s > 0 ? G.W3 : G.Ws) : G.W;
                 q.insert(q.end(), {stage + 1, d, G.n, shape_ok(d, G.P, c->esize, W, stage + 1) ? W : G.W});
             }
     q.insert(q.end(), {3, 0, 0, c->cth_tx});
     q.insert(q.end(), {4, 0, 0, c->upd_zones});
     q.insert(q.end(), {5, 0, 0, c->upd_queue});
-    q.insert(q.end(), {6, 0, 0, sh && c->xy_rows > 0 && xy_ok(c, c->xy_rows_s) ? c->xy_rows_s : c->xy_rows});
+    q.insert(q.end(), {6, 0, 0, sh ? c->xy_rows_s : c->xy_rows});
     return q;
 }
 
@@ -2333,7 +2344,7 @@ int apply_groups(wmb_ctx* c, int groups) {
                 if (rc) return rc;
             }
     if (c->xy_rows > 0) {
-        int rc = set_xy(c, c->xy_rows, c->xy_rows_s);
+        int rc = set_xy(c, c->xy_rows);
         if (rc) return rc;
     }
     return build_ct_update_lists(c);
@@ -2435,13 +2446,13 @@ int wmb_init_patches(wmb_ctx* c, int32_t npatch, const wmb_patch_desc* d, void* 
     c->nfrozen = 0;
     if ((rc = build_sweeps(c))) return rc;
     // the fused corrector in FP32, and in FP64 shared-halo steps (512 x 32^3,
-    // bands of 4 rows: 3.62 against 3.88 ms for the three sweeps; 5.4 + 0.8
-    // against 5.7 ms in the halo scheme, which keeps the sweeps)
-    c->xy_rows = 0;
-    if (c->esize == 4 || c->d_nbr) {
-        const int rb = choose_xy(c, false);
-        if (rb && (rc = set_xy(c, rb, c->d_nbr ? choose_xy(c, true) : 0))) return rc;
-    }
+    // bands of 4 rows: 3.62 against 3.88 ms for the three sweeps).  The halo
+    // scheme in FP64 keeps the sweeps; whole steps with one patch frozen,
+    // sweeps / the best bands, ms: 27 x 48^3 2.05 / 2.14, 64 x 64^3 10.67 /
+    // 10.99, 64 x 32^3 1.66 / 1.64, 512 x 32^3 12.72 / 12.62
+    c->xy_rows = c->xy_rows_s = 0;
+    if (c->esize == 4 && (rc = set_xy(c, choose_xy(c, false)))) return rc;
+    if (c->d_nbr && (rc = set_xy_s(c, choose_xy(c, true)))) return rc;
     if (c->p.scratch_groups > 1) {
         c->serial = true;
         if ((rc = apply_groups(c, c->p.scratch_groups))) return rc;
@@ -2702,6 +2713,7 @@ int wmb_set_tuning(wmb_ctx* c, const int32_t* quads, int32_t n) {
         if (stage == 6) {
             if (W != c->xy_rows) {
                 int rc = set_xy(c, W);
+                if (!rc) rc = set_xy_s(c, W);
                 if (rc) return rc;
             }
             continue;

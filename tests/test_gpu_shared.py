@@ -155,3 +155,23 @@ def test_lists_rebuilt_while_frozen(wmb, how, prec):
         sim.close()
     for a, c in zip(*out):
         assert np.array_equal(a, c), float(np.abs(a - c).max())
+
+
+def test_fp64_halo_scheme_takes_separate_correctors(wmb):
+    """In FP64 the fused x/y corrector serves the shared-halo steps alone (in
+    the halo scheme the three sweeps are faster): a profiled shared step has no
+    y corrector, one with a frozen patch has it beside those along x and z,
+    which each take as long within a factor of four."""
+    n, nb = (24, 24, 24), (3, 3, 3)
+    G = I.uniform_grid(tuple(a * b for a, b in zip(n, nb)), n)
+    q, b = I.random_smooth(G.shape, 5, dx=(1 / 72,) * 3)
+    sim = gpu_sim(wmb, G, q, b, 0, dx=(1 / 72,) * 3)
+    y = []
+    for frozen in (False, True):
+        sim.set_active(0, not frozen)
+        sim.run_steps(1)
+        ms = [sim.profile_step() for _ in range(3)]
+        y.append([min(m[k] for m in ms) for k in ("sweep2_x", "sweep2_y", "sweep2_z")])
+    sim.close()
+    assert y[0][1] < 0.25 * y[0][0]
+    assert 0.25 < y[1][1] / y[1][0] < 4 and 0.25 < y[1][1] / y[1][2] < 4
