@@ -2711,11 +2711,9 @@ int wmb_set_tuning(wmb_ctx* c, const int32_t* quads, int32_t n) {
             continue;
         }
         if (stage == 6) {
-            if (W != c->xy_rows) {
-                int rc = set_xy(c, W);
-                if (!rc) rc = set_xy_s(c, W);
-                if (rc) return rc;
-            }
+            int rc = W != c->xy_rows ? set_xy(c, W) : WMB_OK;
+            if (!rc && W != c->xy_rows_s) rc = set_xy_s(c, W);
+            if (rc) return rc;
             continue;
         }
         if (stage == 3 || stage == 4) {

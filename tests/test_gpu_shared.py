@@ -175,3 +175,25 @@ def test_fp64_halo_scheme_takes_separate_correctors(wmb):
     sim.close()
     assert y[0][1] < 0.25 * y[0][0]
     assert 0.25 < y[1][1] / y[1][0] < 4 and 0.25 < y[1][1] / y[1][2] < 4
+
+
+def test_band_rows_set_are_the_ones_that_run(wmb):
+    """Every entry (6, 0, 0, r) takes effect in shared steps, whichever rows
+    the halo scheme has, and a schedule set and taken back while a patch is
+    frozen keeps them.  (wmb_autotune of a shared FP64 batch reports the
+    shapes that run and times nothing.)"""
+    for r in range(8):
+        G, sim = _sim(wmb, "smallest", 0, True)
+        sim.set_tuning({(6, 0, 0): r})
+        assert sim.autotune()[(6, 0, 0)] == r
+        sim.close()
+    G, sim = _sim(wmb, "smallest", 0, True)
+    before = sim.autotune()
+    sim.set_active(1, False)
+    sim.set_schedule(2)
+    sim.run_steps(1)
+    sim.set_schedule(1)
+    sim.set_active(1, True)
+    sim.run_steps(1)
+    assert sim.autotune() == before
+    sim.close()
