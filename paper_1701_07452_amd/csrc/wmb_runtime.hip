@@ -1261,8 +1261,8 @@ int set_group_Ws(wmb_ctx* c, int d, int stage, SweepGroup& G, int W, int W3) {
     return WMB_OK;
 }
 
-// (Re)build a group's work lists for W pencils a block; the lists they
-// replace are freed.
+// (Re)build a group's halo-scheme work lists for W pencils a block; the lists
+// they replace are freed.
 int set_group_W(wmb_ctx* c, int d, int stage, SweepGroup& G, int W) {
     auto rebuild = [&](DevList& L, SweepPart part) -> int {
         bool bad = false;
@@ -1290,7 +1290,7 @@ int set_group_W(wmb_ctx* c, int d, int stage, SweepGroup& G, int W) {
     if (!rc && d == 0 && stage == 0) rc = rebuild(G.wl_fr, PART_FRAME);
     if (rc) return rc;
     G.W = W;
-    return set_group_Ws(c, d, stage, G, W, W);
+    return WMB_OK;
 }
 
 // The fused x/y corrector (xy_rows > 0): for the patches whose x edge is n,
@@ -1911,11 +1911,17 @@ int autotune_t(wmb_ctx* c, int reps) {
     const bool sh = shared_now(c);
     const SharedHalo sa = shared_arg(c, sh);
     const SweepPart part = sh ? PART_INTERIOR : PART_ALL;
-    // the separate sweeps are timed first; the fused x/y corrector after them
-    auto set_rows = [&](int rb) -> int {
-        int rc0 = set_xy(c, rb);
-        return rc0 ? rc0 : set_xy_s(c, rb);
+    // its shapes only: those of the other scheme stay as they are
+    auto shape = [&](const SweepGroup& G) -> int { return sh ? G.Ws : G.W; };
+    auto set_shape = [&](int d, int stage, SweepGroup& G, int W) -> int {
+        return sh ? set_group_Ws(c, d, stage, G, W, G.W3) : set_group_W(c, d, stage, G, W);
     };
+    auto zshape = [&](const SweepGroup& G) -> int { return sh ? G.W3 : G.W; };  // the z corrector from records
+    auto set_zshape = [&](SweepGroup& G, int W) -> int {
+        return sh ? set_group_Ws(c, 2, 1, G, G.Ws, W) : set_group_W(c, 2, 1, G, W);
+    };
+    auto set_rows = [&](int rb) -> int { return sh ? set_xy_s(c, rb) : set_xy(c, rb); };
+    // the separate sweeps are timed first; the fused x/y corrector after them
     if (int rc0 = set_rows(0)) return cleanup(rc0);
     for (int stage = 0; stage < 2; stage++) {
         if (stage == 1) {
@@ -1944,7 +1950,8 @@ int autotune_t(wmb_ctx* c, int reps) {
                 else
                     for (int W : opts_t) cand.push_back(W);
                 float best = 1e30f, bestp = 1e30f, bestm = 1e30f;
-                int bestW = sh ? G.Ws : G.W;
+                int bestW = shape(G);
+                G.Wp = G.Wm = 0;
                 const int P = sh ? G.Ps() : G.P;
                 std::vector<std::pair<float, int>> timed;  // (ms, shape) of every candidate
                 for (int W : cand) {
@@ -1984,8 +1991,8 @@ int autotune_t(wmb_ctx* c, int reps) {
                 std::sort(timed.begin(), timed.end());
                 G.Wx[0] = timed.size() > 1 ? timed[1].second : 0;
                 G.Wx[1] = timed.size() > 2 ? timed[2].second : 0;
-                if (bestW != G.W || (sh && bestW != G.Ws)) {
-                    int rc2 = set_group_W(c, d, stage, G, bestW);
+                if (bestW != shape(G)) {
+                    int rc2 = set_shape(d, stage, G, bestW);
                     if (rc2) return cleanup(rc2);
                 }
             }
@@ -2062,20 +2069,20 @@ int autotune_t(wmb_ctx* c, int reps) {
         // the x sweeps: the second and third shapes alone, one group at a time
         for (auto& G : c->sweeps[0][stage])
             for (int a = 0; a < 2; a++) {
-                const int W0 = G.W, W1 = G.Wx[a];
+                const int W0 = shape(G), W1 = G.Wx[a];
                 if (W1 == 0 || W1 == W0) continue;
-                if ((rc2 = set_group_W(c, 0, stage, G, W1))) return cleanup(rc2);
+                if ((rc2 = set_shape(0, stage, G, W1))) return cleanup(rc2);
                 float t = 0.f;
                 if ((rc2 = time_stage(&t))) return rc2;
                 if (t < best) {
                     best = t;
-                } else if ((rc2 = set_group_W(c, 0, stage, G, W0))) {
+                } else if ((rc2 = set_shape(0, stage, G, W0))) {
                     return cleanup(rc2);
                 }
             }
         std::vector<int> alone;
         for (int d = 1; d < 3; d++)
-            for (auto& G : c->sweeps[d][stage]) alone.push_back(G.W);
+            for (auto& G : c->sweeps[d][stage]) alone.push_back(shape(G));
         int choice = 0;  // 0: alone, 1: all pencil, 2: all marching
         for (int alt = 1; alt <= 2; alt++) {
             bool differs = false, valid = true;
@@ -2083,12 +2090,12 @@ int autotune_t(wmb_ctx* c, int reps) {
                 for (auto& G : c->sweeps[d][stage]) {
                     const int W = alt == 1 ? G.Wp : G.Wm;
                     valid = valid && W != 0;
-                    differs = differs || W != G.W;
+                    differs = differs || W != shape(G);
                 }
             if (!valid || !differs) continue;
             for (int d = 1; d < 3 && !rc2; d++)
                 for (auto& G : c->sweeps[d][stage])
-                    if (!rc2) rc2 = set_group_W(c, d, stage, G, alt == 1 ? G.Wp : G.Wm);
+                    if (!rc2) rc2 = set_shape(d, stage, G, alt == 1 ? G.Wp : G.Wm);
             if (rc2) return cleanup(rc2);
             float t = 0.f;
             if ((rc2 = time_stage(&t))) return rc2;
@@ -2100,13 +2107,13 @@ int autotune_t(wmb_ctx* c, int reps) {
             size_t k = 0;
             for (int d = 1; d < 3 && !rc2; d++)
                 for (auto& G : c->sweeps[d][stage])
-                    if (!rc2) rc2 = set_group_W(c, d, stage, G, alone[k++]);
+                    if (!rc2) rc2 = set_shape(d, stage, G, alone[k++]);
             if (rc2) return cleanup(rc2);
         }
         if (choice)
             for (int d = 1; d < 3 && !rc2; d++)
                 for (auto& G : c->sweeps[d][stage])
-                    if (!rc2) rc2 = set_group_W(c, d, stage, G, choice == 1 ? G.Wp : G.Wm);
+                    if (!rc2) rc2 = set_shape(d, stage, G, choice == 1 ? G.Wp : G.Wm);
         if (rc2) return cleanup(rc2);
     }
     // The fused x/y corrector: bands of 4 to 18 rows, each with the z
@@ -2119,7 +2126,7 @@ int autotune_t(wmb_ctx* c, int reps) {
         if (rc2) return rc2;
         int best_rb = 0;
         std::vector<int> zw, best_zw;
-        for (auto& G : c->sweeps[2][1]) zw.push_back(G.W);
+        for (auto& G : c->sweeps[2][1]) zw.push_back(zshape(G));
         best_zw = zw;
         for (int rb : {4, 6, 8, 9, 11, 13, 16, 18}) {
             if (!xy_ok(c, rb)) continue;
@@ -2127,8 +2134,8 @@ int autotune_t(wmb_ctx* c, int reps) {
             for (int W : {-256, -64, 16}) {
                 std::vector<int> cur_zw;
                 for (auto& G : c->sweeps[2][1]) {
-                    const int w = shape_ok(2, G.P, es, W, 2) ? W : G.W;
-                    if (w != G.W && (rc2 = set_group_W(c, 2, 1, G, w))) return cleanup(rc2);
+                    const int w = shape_ok(2, G.P, es, W, 2) ? W : zshape(G);
+                    if (w != zshape(G) && (rc2 = set_zshape(G, w))) return cleanup(rc2);
                     cur_zw.push_back(w);
                 }
                 float t = 0.f;
@@ -2140,7 +2147,7 @@ int autotune_t(wmb_ctx* c, int reps) {
         size_t i = 0;
         for (auto& G : c->sweeps[2][1]) {
             const int w = best_zw[i++];
-            if (w != G.W && (rc2 = set_group_W(c, 2, 1, G, w))) return cleanup(rc2);
+            if (w != zshape(G) && (rc2 = set_zshape(G, w))) return cleanup(rc2);
         }
     }
     // The tiles of Steps 3-4 (widest tile along x) and of Steps 8-11 (zones
@@ -2319,6 +2326,43 @@ int bind_scratch(wmb_ctx* c) {
 // C ABI
 // ===========================================================================
 
+// Apply checked tuning entries to the halo scheme's shapes, the shared-halo
+// steps' shapes or both (the tiles of Steps 3-4 and 8-11 are common).
+int apply_tuning(wmb_ctx* c, const int32_t* quads, int32_t n, bool halo, bool shared) {
+    bool tiles = false;
+    for (int k = 0; k + 4 <= n; k += 4) {
+        const int stage = quads[k], d = quads[k + 1], edge = quads[k + 2], W = quads[k + 3];
+        if (stage == 5) {
+            c->upd_queue = W;
+            continue;
+        }
+        if (stage == 6) {
+            int rc = halo && W != c->xy_rows ? set_xy(c, W) : WMB_OK;
+            if (!rc && shared && W != c->xy_rows_s) rc = set_xy_s(c, W);
+            if (rc) return rc;
+            continue;
+        }
+        if (stage == 3 || stage == 4) {
+            int& v = stage == 3 ? c->cth_tx : c->upd_zones;
+            tiles = tiles || v != W;
+            v = W;
+            continue;
+        }
+        for (auto& G : c->sweeps[d][stage - 1]) {
+            if (G.n != edge) continue;
+            int rc = halo ? set_group_W(c, d, stage - 1, G, W) : WMB_OK;
+            if (!rc && shared) rc = set_group_Ws(c, d, stage - 1, G, W, W);
+            if (rc) return rc;
+        }
+    }
+    if (tiles) {
+        int rc = build_ct_update_lists(c);
+        if (rc) return rc;
+    }
+    free_graphs(c);
+    return WMB_OK;
+}
+
 // Patch groups of the step: pgroup from deal_rows, the group lists, and for
 // concurrent groups (not serial) a stream and an event per group
 int apply_groups(wmb_ctx* c, int groups) {
@@ -2338,9 +2382,7 @@ int apply_groups(wmb_ctx* c, int groups) {
     for (int d = 0; d < 3; d++)
         for (int stage = 0; stage < 2; stage++)
             for (auto& SG : c->sweeps[d][stage]) {
-                const int ws = SG.Ws, w3 = SG.W3;  // the shared-halo shapes stay
                 int rc = set_group_W(c, d, stage, SG, SG.W);
-                if (!rc && ws && (ws != SG.Ws || w3 != SG.W3)) rc = set_group_Ws(c, d, stage, SG, ws, w3);
                 if (rc) return rc;
             }
     if (c->xy_rows > 0) {
@@ -2648,7 +2690,8 @@ int wmb_autotune(wmb_ctx* c, int32_t reps, int32_t* chosen, int32_t nchosen) {
         // (the library's host code is clean under the address sanitizer).
         q = tuning_quads(c);
     } else if (!q.empty()) {
-        int rc = wmb_set_tuning(c, q.data(), (int32_t)q.size());
+        const bool sh = shared_now(c);
+        int rc = apply_tuning(c, q.data(), (int32_t)q.size(), !sh, sh);
         if (rc) return rc;
     } else {
         int r = reps < 0 ? -reps : reps;
@@ -2703,37 +2746,7 @@ int wmb_set_tuning(wmb_ctx* c, const int32_t* quads, int32_t n) {
                 return fail(c, WMB_EINVAL, "tuning entry: the marching form serves y and z with at most 256 pencils "
                                            "a block; the pencil form must fit 1024 threads and 64 KiB of LDS");
     }
-    bool tiles = false;
-    for (int k = 0; k + 4 <= n; k += 4) {
-        const int stage = quads[k], d = quads[k + 1], edge = quads[k + 2], W = quads[k + 3];
-        if (stage == 5) {
-            c->upd_queue = W;
-            continue;
-        }
-        if (stage == 6) {
-            int rc = W != c->xy_rows ? set_xy(c, W) : WMB_OK;
-            if (!rc && W != c->xy_rows_s) rc = set_xy_s(c, W);
-            if (rc) return rc;
-            continue;
-        }
-        if (stage == 3 || stage == 4) {
-            int& v = stage == 3 ? c->cth_tx : c->upd_zones;
-            tiles = tiles || v != W;
-            v = W;
-            continue;
-        }
-        for (auto& G : c->sweeps[d][stage - 1]) {
-            if (G.n != edge) continue;
-            int rc = set_group_W(c, d, stage - 1, G, W);
-            if (rc) return rc;
-        }
-    }
-    if (tiles) {
-        int rc = build_ct_update_lists(c);
-        if (rc) return rc;
-    }
-    free_graphs(c);
-    return WMB_OK;
+    return apply_tuning(c, quads, n, true, true);
 }
 
 int wmb_set_schedule(wmb_ctx* c, int32_t groups) {

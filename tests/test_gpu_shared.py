@@ -197,3 +197,22 @@ def test_band_rows_set_are_the_ones_that_run(wmb):
     sim.run_steps(1)
     assert sim.autotune() == before
     sim.close()
+
+
+def test_autotune_keeps_the_other_scheme(wmb):
+    """Shapes timed in the halo scheme (a patch frozen) are not forced on the
+    shared-halo steps, whose sweeps and band rows stay what they were (the tiles
+    of Steps 3-4 and 8-11 are common to both)."""
+    G, sim = _sim(wmb, "whole_lines", 0, True)
+    own = lambda t: {k: v for k, v in t.items() if k[0] in (1, 2, 6)}  # noqa: E731
+    before = own(sim.autotune())
+    sim.set_active(1, False)
+    sim.run_steps(1)
+    timed = own(sim.autotune(-1))
+    sim.set_active(1, True)
+    sim.run_steps(1)
+    assert own(sim.autotune()) == before
+    sim.set_active(1, False)
+    sim.run_steps(1)
+    assert own(sim.autotune()) == timed  # remembered for the halo scheme
+    sim.close()
