@@ -1922,6 +1922,9 @@ int autotune_t(wmb_ctx* c, int reps) {
     };
     auto set_rows = [&](int rb) -> int { return sh ? set_xy_s(c, rb) : set_xy(c, rb); };
     // the separate sweeps are timed first; the fused x/y corrector after them
+    const int rows0 = sh ? c->xy_rows_s : c->xy_rows;
+    std::vector<int> zshape0;
+    for (auto& G : c->sweeps[2][1]) zshape0.push_back(zshape(G));
     if (int rc0 = set_rows(0)) return cleanup(rc0);
     for (int stage = 0; stage < 2; stage++) {
         if (stage == 1) {
@@ -1949,6 +1952,8 @@ int autotune_t(wmb_ctx* c, int reps) {
                     for (int W : opts_x) cand.push_back(W);
                 else
                     for (int W : opts_t) cand.push_back(W);
+                // and the shape it has: tuning is not to end slower than none
+                if (std::find(cand.begin(), cand.end(), shape(G)) == cand.end()) cand.push_back(shape(G));
                 float best = 1e30f, bestp = 1e30f, bestm = 1e30f;
                 int bestW = shape(G);
                 G.Wp = G.Wm = 0;
@@ -2116,10 +2121,11 @@ int autotune_t(wmb_ctx* c, int reps) {
                     if (!rc2) rc2 = set_shape(d, stage, G, choice == 1 ? G.Wp : G.Wm);
         if (rc2) return cleanup(rc2);
     }
-    // The fused x/y corrector: bands of 4 to 18 rows, each with the z
-    // corrector (then reading the stored records) as marching sweeps of 256
-    // or 64 pencils a block or pencil sweeps of 16, against the separate
-    // sweeps as chosen above; whole steps replayed as a graph.
+    // The fused x/y corrector: bands of 4 to 18 rows and of the rows it had,
+    // each with the z corrector (then reading the stored records) as marching
+    // sweeps of 256 or 64 pencils a block, pencil sweeps of 16 or, with the
+    // rows it had, in its own shapes (W = 0), against the separate sweeps as
+    // chosen above; whole steps.
     {
         float best = 0.f;
         int rc2 = time_stage(&best);
@@ -2128,13 +2134,18 @@ int autotune_t(wmb_ctx* c, int reps) {
         std::vector<int> zw, best_zw;
         for (auto& G : c->sweeps[2][1]) zw.push_back(zshape(G));
         best_zw = zw;
-        for (int rb : {4, 6, 8, 9, 11, 13, 16, 18}) {
+        std::vector<int> bands{4, 6, 8, 9, 11, 13, 16, 18};
+        if (rows0 > 0 && std::find(bands.begin(), bands.end(), rows0) == bands.end()) bands.push_back(rows0);
+        for (int rb : bands) {
             if (!xy_ok(c, rb)) continue;
             if ((rc2 = set_rows(rb))) return cleanup(rc2);
-            for (int W : {-256, -64, 16}) {
+            for (int W : {-256, -64, 16, 0}) {
+                if (W == 0 && rb != rows0) continue;
                 std::vector<int> cur_zw;
+                size_t i = 0;
                 for (auto& G : c->sweeps[2][1]) {
-                    const int w = shape_ok(2, G.P, es, W, 2) ? W : zshape(G);
+                    const int own = zshape0[i++];
+                    const int w = W == 0 ? own : (shape_ok(2, G.P, es, W, 2) ? W : zshape(G));
                     if (w != zshape(G) && (rc2 = set_zshape(G, w))) return cleanup(rc2);
                     cur_zw.push_back(w);
                 }
