@@ -119,6 +119,7 @@ struct wmb_ctx {
     bool all_in = true;          // every patch present and active (as of the last plan)
     bool xg_lazy = false;        // the last step was a shared one: the x-ghosts are written when asked for
     bool stages_shared = false;  // and its intermediates cover the patches' own zones only
+    int stage_cur = 0;           // the state copy that the last step started from
     bool serial = false;  // scratch groups: the groups' steps run one after another on the main stream
     hipStream_t gstream[4] = {};  // group streams 1..3 (group 0 runs on the main stream), borrowed
     hipEvent_t ev_g[4] = {};
@@ -673,7 +674,8 @@ int run_finalize(wmb_ctx* c) {
 // first covers the pencils whose transverse coords are interior, which read
 // only the x-ghosts the previous update wrote, then waits for the exchange
 // and covers the frame.  Shared-halo steps are captured unsplit.
-void stepped(wmb_ctx* c, bool sh) {  // what a step leaves beside the new state
+void stepped(wmb_ctx* c, bool sh, int from) {  // what a step from copy `from` leaves beside the new state
+    c->stage_cur = from;
     c->edges_kept = c->keep_edges;
     c->xg_valid = !sh;  // the halo scheme's update wrote the x-ghosts of the new copy
     c->xg_lazy = sh;
@@ -766,7 +768,7 @@ int run_step(wmb_ctx* c, bool split = false) {
                          zrec(c, sh) ? F_FL1 + 14 : F_FL2 + 14, c->d_sc + 1, c->stream);
     STEPCK("update");
     mark(c);
-    stepped(c, sh);
+    stepped(c, sh, cur);
 #undef STEPCK
     c->cur ^= 1;
     // the final update folds the new state's signal speeds into smax
@@ -824,7 +826,7 @@ int run_step_grouped(wmb_ctx* c) {
     }
     if (par)
         for (int g = 1; g < c->ngroups; g++) CKH(hipStreamWaitEvent(c->stream, c->ev_g[g], 0));
-    stepped(c, false);
+    stepped(c, false, cur);
     c->cur ^= 1;
     c->smax_state = (c->smax_state == SMAX_ZERO) ? SMAX_CLEAN : SMAX_DIRTY;
     return WMB_OK;
@@ -1587,11 +1589,13 @@ int capture_graphs(wmb_ctx* c) {
     const int saved_state = c->smax_state;
     const bool saved_xg = c->xg_valid, saved_kept = c->edges_kept;
     const bool saved_lazy = c->xg_lazy, saved_stages = c->stages_shared;
+    const int saved_from = c->stage_cur;
     const bool sh = shared_now(c);
     const int cur_start = c->cur, mode = sh ? 2 : 0;
     auto restore = [&]() {
         c->xg_lazy = saved_lazy;
         c->stages_shared = saved_stages;
+        c->stage_cur = saved_from;
         c->cur = cur_start;
         c->smax_state = saved_state;
         c->xg_valid = saved_xg;
@@ -1780,13 +1784,14 @@ int get_state_t(wmb_ctx* c, int ip, double* q, double* b, bool stored) {
 // A shared-halo step leaves intermediates over the patches' own zones only.
 // Form those of the last step again, over the ranges of the halo scheme, from
 // the state copy it started from (still in place) and its step constants;
-// the counters go to the sinks.
+// the counters go to the sinks.  (After wmb_autotune those of its timed steps,
+// which started from the current copy.)
 template <typename R>
 int restage(wmb_ctx* c) {
     const int cur0 = c->cur;
     const bool xg0 = c->xg_valid, xl0 = c->xg_lazy;
     StepConst* sc0 = c->d_sc;
-    c->cur ^= 1;
+    c->cur = c->stage_cur;
     int rc = run_fill<R>(c, FILL_ALL);
     c->d_sc = sc0 + 1;
     hipError_t e = hipSuccess;
@@ -1910,6 +1915,10 @@ int autotune_t(wmb_ctx* c, int reps) {
     // the scheme that the steps run: its lists are the ones timed
     const bool sh = shared_now(c);
     const SharedHalo sa = shared_arg(c, sh);
+    // from here on the intermediates are those of steps from the current state
+    c->stages_shared = sh;
+    c->stage_cur = c->cur;
+    if (sh) CKT(hipMemcpyAsync(c->d_sc + 1, c->d_sc, sizeof(StepConst), hipMemcpyDeviceToDevice, c->stream));
     const SweepPart part = sh ? PART_INTERIOR : PART_ALL;
     // its shapes only: those of the other scheme stay as they are
     auto shape = [&](const SweepGroup& G) -> int { return sh ? G.Ws : G.W; };
@@ -2644,7 +2653,7 @@ int wmb_run_steps(wmb_ctx* c, int32_t nsteps) {
         c->cur ^= 1;
     }
     c->smax_state = SMAX_CLEAN;
-    stepped(c, sh);
+    stepped(c, sh, c->cur ^ 1);
     return WMB_OK;
 }
 

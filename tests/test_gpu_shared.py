@@ -216,3 +216,25 @@ def test_autotune_keeps_the_other_scheme(wmb):
     sim.run_steps(1)
     assert own(sim.autotune()) == timed  # remembered for the halo scheme
     sim.close()
+
+
+def test_stages_after_autotune(wmb):
+    """wmb_autotune leaves the intermediates of the steps it timed, which start
+    from the current state: its stages are those of the next step (FP32, whose
+    shared shapes are timed; one repetition)."""
+    G, sim = _sim(wmb, "whole_lines", 1, True)
+    g = int(sim.params.ghost)
+    sim.run_steps(2)
+    sim.autotune(-1)
+    got = []
+    for _ in range(2):
+        stages = []
+        for ip in range(G.npatch):
+            n = G.descs[ip][0]
+            own = (slice(None),) + tuple(slice(g, g + n[a]) for a in (2, 1, 0))
+            stages += [sim.debug_stage(ip, 3)[own], sim.debug_stage(ip, 1)[1][own], sim.debug_stage(ip, 5)[2][own]]
+        got.append(stages)
+        sim.run_steps(1)
+    for a, c in zip(*got):
+        assert np.isfinite(a).all() and np.array_equal(a, c), float(np.abs(a - c).max())
+    sim.close()
