@@ -238,3 +238,48 @@ def test_stages_after_autotune(wmb):
     for a, c in zip(*got):
         assert np.isfinite(a).all() and np.array_equal(a, c), float(np.abs(a - c).max())
     sim.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("between", ["nothing", "retune", "schedule", "more"])
+def test_stages_after_freeze(wmb, between, prec):
+    """The stages of a shared step asked for after one patch was frozen and
+    another slot removed, with the work lists rebuilt in between or not, and
+    the steps after."""
+    out = []
+    for shared in (True, False):
+        G, sim = _sim(wmb, "fused", prec, shared)
+        g = int(sim.params.ghost)
+        sim.run_steps(3)
+        q, b = sim.get_state(1)
+        sim.set_active(1, False)
+        sim.set_state(1, q, b)  # copies the frozen patch again
+        sim.set_present(2, False)
+        if between == "retune":
+            sim.set_tuning({(1, 0, 16): 2, (2, 2, 10): 4})
+        elif between == "schedule":
+            sim.set_schedule(2)
+            sim.set_schedule(1)
+        elif between == "more":
+            sim.set_active(3, False)
+            sim.set_active(3, True)
+        got = []
+        for ip in range(G.npatch):
+            n = G.descs[ip][0]
+            box = (slice(None),) + tuple(slice(g, g + n[2 - a]) for a in range(3))
+            for st, lo, hi, tlo, thi in ((1, -2, 2, -3, 2), (5, -1, 1, -1, 0)):
+                f = sim.debug_stage(ip, st)
+                for d in range(3):
+                    sl = tuple(slice(g + (lo if a == d else tlo), g + n[a] + (hi if a == d else thi) + 1) for a in (2, 1, 0))
+                    got.append(f[d][(slice(None),) + sl])
+            got.append(sim.debug_stage(ip, 3)[box])
+        sim.run_steps(2)
+        got += [a for ip in (0, 1, 3) for a in sim.get_state(ip)]
+        sim.set_present(2, True)
+        sim.set_active(1, True)
+        sim.run_steps(2)
+        got += list(_state(G, sim))
+        out.append(got)
+        sim.close()
+    for i, (a, c) in enumerate(zip(*out)):
+        assert np.array_equal(a, c), (i, float(np.abs(a - c).max()))
