@@ -1660,6 +1660,10 @@ void from_device_layout(const R* src, double* dst, const PatchDev& P, int g) {
             }
 }
 
+// The host image of wmb_set_state is kept for the next call up to this size
+// (a 64^3 FP64 patch's takes 33 MB); a patch of 504^3 has one of 12 GB.
+constexpr size_t IMG_KEPT = (size_t)64 << 20;
+
 template <typename R>
 int set_state_t(wmb_ctx* c, int ip, const double* q, const double* b) {
     const PatchDev& P = c->hpatch[ip];
@@ -1710,6 +1714,7 @@ int set_state_t(wmb_ctx* c, int ip, const double* q, const double* b) {
     }
     CKH(hipMemcpyAsync(base, img, sizeof(R) * values, hipMemcpyHostToDevice, c->stream));
     CKH(hipStreamSynchronize(c->stream));
+    if (c->img.size() > IMG_KEPT) std::vector<char>().swap(c->img);
     return WMB_OK;
 }
 
