@@ -283,3 +283,42 @@ def test_stages_after_freeze(wmb, between, prec):
         sim.close()
     for i, (a, c) in enumerate(zip(*out)):
         assert np.array_equal(a, c), (i, float(np.abs(a - c).max()))
+
+
+# what a shared step can be combined with: the Steps 8-11 launch from queues, a
+# dt one step late, other schedules and back, steps launched kernel by kernel
+# (from 2^21 zones on)
+OPTIONS = {
+    "queue": ((16, 12, 10), (2, 1, 2), {}, {(5, 0, 0): 1}),
+    "dt_lag": ((16, 12, 10), (2, 1, 2), dict(dt_lag=1), None),
+    "schedules": ((8, 8, 8), (2, 2, 3), {}, None),
+    "launched": ((64, 64, 64), (2, 2, 2), {}, None),
+}
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("option", sorted(OPTIONS))
+def test_shared_options(wmb, option, prec):
+    """Six steps, bitwise those of the halo scheme."""
+    n, nb, kw, tun = OPTIONS[option]
+    G = I.uniform_grid(tuple(a * b for a, b in zip(n, nb)), n)
+    dx = (1.0 / max(G.shape),) * 3
+    q, b = I.random_smooth(G.shape, 8, dx=dx, amp=0.4)
+    if prec == 1:
+        q, b = as_f32(q), as_f32(b)
+    out = []
+    for shared in (True, False):
+        sim = gpu_sim(wmb, G, q, b, prec, dx=dx, **kw)
+        if not shared:
+            sim.keep_stages(True)
+        if tun:
+            sim.set_tuning(tun)
+        for groups in (1, 3, 1, 2, 4, 1):
+            if option == "schedules":
+                sim.set_schedule(groups)
+            sim.run_steps(1)
+        out.append((_state(G, sim), sim.diagnostics()))
+        sim.close()
+    for a, c in zip(out[0][0], out[1][0]):
+        assert np.array_equal(a, c), float(np.abs(a - c).max())
+    assert np.array_equal(out[0][1][0], out[1][1][0]) and out[0][1][1:] == out[1][1][1:]
