@@ -177,7 +177,8 @@ int wmb_compute_dt(wmb_ctx *c, double *dt_out);
 int wmb_advance(wmb_ctx *c, double dt);
 
 /* nsteps x (fill ghosts, compute dt, advance) with dt kept on the device,
-   replayed from a captured HIP graph (captured on the first call).  The
+   replayed from a captured HIP graph (captured on the first call) or, for
+   shared-halo steps of 2^21 zones and more, enqueued kernel by kernel.  The
    graph's ghost exchange runs the y and z passes only (the step before wrote
    the x-ghosts), on a branch of its own beside the part of the Step-1 x sweep
    whose pencils have interior transverse coordinates (the overlap of
@@ -186,8 +187,7 @@ int wmb_advance(wmb_ctx *c, double dt);
    except that the fused corrector is followed by the z sweep that reads its
    records; the
    x pass is enqueued first when the state was set since.  Shared-halo steps
-   have no exchange; their graph is one chain, and from 2^21 zones they are
-   enqueued kernel by kernel.  Results are bitwise those of the eager calls.  Enqueue only; this is the timed call. */
+   have no exchange, and their graph is one chain.  Results are bitwise those of the eager calls.  Enqueue only; this is the timed call. */
 int wmb_run_steps(wmb_ctx *c, int32_t nsteps);
 
 /* FP64 diagnostics over all interiors: totals[8] = sum over zones of q times
@@ -227,9 +227,10 @@ int wmb_diagnostics_noalloc(wmb_ctx *c, double *dev_out);
    overwritten by Step 9) give WMB_EINVAL.  Synchronous. */
 int wmb_debug_stage(wmb_ctx *c, int32_t patch, int32_t stage, double *out);
 
-/* Search the shape of the directional sweeps for every group of patches
-   with the same edge along the sweep axis, timing each candidate `reps`
-   times on the device, and keep the fastest.  A shape W > 0 is the LDS
+/* Search the shapes of shared-halo steps in FP32: the directional sweeps' for
+   every group of patches with the same edge along the sweep axis, timing each
+   candidate and the shape it has `reps` times on the device, and keep the
+   fastest.  A shape W > 0 is the LDS
    pencil form with W pencils a block (every thread one zone of a pencil);
    W < 0, for the y and z sweeps only, is the marching form with -W pencils
    a block (every thread walks one whole pencil, consecutive lanes on
@@ -238,10 +239,9 @@ int wmb_debug_stage(wmb_ctx *c, int32_t patch, int32_t stage, double *out);
    issues the next zone's loads one zone ahead (w pencils a block; more
    registers, half the waves).  The choice never
    changes results (both forms compute every face with the same
-   arithmetic).  It then times whole steps (graph-replayed, or launched
-   for shared-halo steps) with the x and y
-   correctors fused into one launch (bands of 4 to 18 rows, where
-   the blocks fit, each with three shapes of the z corrector that reads the
+   arithmetic).  It then times whole steps with the x and y
+   correctors fused into one launch (bands of 4 to 18 rows and of the rows it
+   has, where the blocks fit, each with shapes of the z corrector that reads the
    records it stores) against the separate sweeps, and the tiles of Steps 3-4
    (the widest tile along x: 40, 20 or 13 zones, 256 zones a plane) and of
    Steps 8-11 (256 or, in FP32, 512 zones a plane) with either Steps 8-11
@@ -252,17 +252,22 @@ int wmb_debug_stage(wmb_ctx *c, int32_t patch, int32_t stage, double *out);
    architecture, the precision, the ghost width, the limiter and protection
    variants and the patch extents with their counts: a later call with the
    same key (on any context) applies it without timing.  reps < 0 times
-   anyway, with -reps repetitions, and replaces the kept choice.  If chosen
+   anyway, with -reps repetitions, and replaces the kept choice.
+   In FP64 and in the halo scheme (walls, uneven patches, a frozen or removed
+   patch, kept stages, patch groups) nothing is timed, whatever reps: the
+   batch keeps the shapes it has, which are reported.  (Their whole steps were
+   timed as captured graphs, one for each candidate; three processes that did
+   so ended in a segmentation fault on a thread of the HIP runtime.)  Shapes of
+   the scheme that does not run stay as they are.  If chosen
    != NULL it receives quadruples (stage, axis, edge, shape) -- the sweep
    groups, then (3, 0, 0, Steps 3-4 tile width), (4, 0, 0, Steps 8-11
    tile zones), (5, 0, 0, Steps 8-11 launch) and (6, 0, 0, fused x/y
    corrector band rows, 0 for separate sweeps) -- up to nchosen ints,
-   0-terminated when shorter.  Shared-halo batches in FP64 keep the default
-   shapes (reported as the choice) and time nothing.
+   0-terminated when shorter.
    Synchronous. */
 int wmb_autotune(wmb_ctx *c, int32_t reps, int32_t *chosen, int32_t nchosen);
 
-/* Set the shapes of sweep groups directly: quads of (stage 1|2, axis 0..2,
+/* Set the shapes of sweep groups directly (in both schemes): quads of (stage 1|2, axis 0..2,
    edge along the axis, shape), n ints in total (a multiple of 4), as
    returned by wmb_autotune (shape > 0: pencil form with that many pencils a
    block; shape < 0: marching form, y and z only, with -shape pencils a
@@ -271,16 +276,18 @@ int wmb_autotune(wmb_ctx *c, int32_t reps, int32_t *chosen, int32_t nchosen);
    pencil shape exceeds 1024 threads or 64 KiB of LDS, or a marching shape
    is asked for x or beyond 256.  Invalidates the captured graphs.  The
    defaults follow from the patch extents and counts: the pencil form with
-   the width that keeps the most threads resident, and in FP32 the marching
-   form for the y and z sweeps of large batches.  Tile entries: (3, 0, 0, w)
+   the width that keeps the most threads resident, and for the y and z sweeps
+   of large batches the marching form (in FP64 with shared halos only).  Tile entries: (3, 0, 0, w)
    sets the widest Steps 3-4 tile along x to w zones (4..40, default 40);
    (4, 0, 0, z) the zones of a Steps 8-11 tile plane (256, or 512 in FP32;
    the default is the one that leaves fewer threads idle); (5, 0, 0, m) the
    Steps 8-11 launch: m = 0 one block a tile (the default), m = 1 a
    persistent grid whose blocks take the tiles of their XCD's queue from an
    atomic counter; (6, 0, 0, r) the corrector (Steps 5-7): r = 0 three
-   separate sweeps (the FP64 default), r > 0 (the FP32 default: 9, or 6
-   where those blocks do not fit) one fused launch for x and y whose
+   separate sweeps (the default of the halo scheme in FP64), r > 0 (the
+   default elsewhere, apart for the halo scheme and the shared-halo steps: the
+   rows whose blocks keep the most faces resident, 9 and 11 at 32^3 in FP32;
+   an entry sets both) one fused launch for x and y whose
    blocks each take one z-plane of a patch and a band of at most r rows
    along y, build the x, y and z predictor states of their zones from one
    block's loads, form the x and y faces and store the z predictor records

@@ -102,8 +102,9 @@ constexpr int NBR_ROW = 64, NBR_SCR = 32;
 
 // Layout of the intermediates in shared-halo steps: fields of the patch's own
 // n_x n_y n_z zones, without ghosts, so that the rows of a 16-, 32- or 64-zone
-// patch are whole cache lines; the field stride (words) is a multiple of 32
-// words plus three, so that the fields of a zone spread over the memory channels.
+// patch are whole cache lines; the field stride (words) is the field rounded
+// up to 32 words (a line in FP32) and 96 more, so that the fields of a zone spread over the
+// memory channels.
 __host__ __device__ constexpr unsigned scratch_stride(int nx, int ny, int nz) {
     return (((unsigned)nx * ny * nz + 31u) & ~31u) + 96u;
 }

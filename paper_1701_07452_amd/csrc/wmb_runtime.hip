@@ -1927,8 +1927,14 @@ int diagnostics_t(wmb_ctx* c, double totals[8], double* dn, double* dr, int64_t*
 // are bitwise independent of the choice.  Timed on the current state: ghosts
 // are refreshed and dt formed, then every candidate of each sweep group is
 // launched (writing only step intermediates); the fastest W is kept.
-template <typename R>
-int autotune_t(wmb_ctx* c, int reps) {
+//   For shared-halo steps in FP32, the only ones whose timing launches kernels
+// and no more: timing whole steps of the others as they run, as captured
+// graphs, one made, launched and destroyed for each candidate, ended three
+// processes in a segmentation fault on a thread of the runtime (its cause is
+// not known; this library's host code is clean under the address sanitizer).
+// The other scheme's shapes stay as they are.
+int autotune_shared(wmb_ctx* c, int reps) {
+    using R = float;
     int rc = dispatch_fill(c);
     if (!rc) rc = ensure_smax(c);
     if (!rc) rc = run_finalize(c);
@@ -1953,30 +1959,23 @@ int autotune_t(wmb_ctx* c, int reps) {
     CKT(hipEventCreate(&e0));
     CKT(hipEventCreate(&e1));
     const size_t es = sizeof(R);
-    // the scheme that the steps run: its lists are the ones timed
-    const bool sh = shared_now(c);
-    const SharedHalo sa = shared_arg(c, sh);
+    const SharedHalo sa = shared_arg(c, true);
     // from here on the intermediates are those of steps from the current state
-    c->stages_shared = sh;
+    c->stages_shared = true;
     c->stage_cur = c->cur;
     c->stage_saved.clear();
-    if (sh) CKT(hipMemcpyAsync(c->d_sc + 1, c->d_sc, sizeof(StepConst), hipMemcpyDeviceToDevice, c->stream));
-    const SweepPart part = sh ? PART_INTERIOR : PART_ALL;
-    // its shapes only: those of the other scheme stay as they are
-    auto shape = [&](const SweepGroup& G) -> int { return sh ? G.Ws : G.W; };
+    CKT(hipMemcpyAsync(c->d_sc + 1, c->d_sc, sizeof(StepConst), hipMemcpyDeviceToDevice, c->stream));
     auto set_shape = [&](int d, int stage, SweepGroup& G, int W) -> int {
-        return sh ? set_group_Ws(c, d, stage, G, W, G.W3) : set_group_W(c, d, stage, G, W);
+        return set_group_Ws(c, d, stage, G, W, G.W3);
     };
-    auto zshape = [&](const SweepGroup& G) -> int { return sh ? G.W3 : G.W; };  // the z corrector from records
-    auto set_zshape = [&](SweepGroup& G, int W) -> int {
-        return sh ? set_group_Ws(c, 2, 1, G, G.Ws, W) : set_group_W(c, 2, 1, G, W);
+    auto set_zshape = [&](SweepGroup& G, int W) -> int {  // the z corrector from records
+        return set_group_Ws(c, 2, 1, G, G.Ws, W);
     };
-    auto set_rows = [&](int rb) -> int { return sh ? set_xy_s(c, rb) : set_xy(c, rb); };
     // the separate sweeps are timed first; the fused x/y corrector after them
-    const int rows0 = sh ? c->xy_rows_s : c->xy_rows;
+    const int rows0 = c->xy_rows_s;
     std::vector<int> zshape0;
-    for (auto& G : c->sweeps[2][1]) zshape0.push_back(zshape(G));
-    if (int rc0 = set_rows(0)) return cleanup(rc0);
+    for (auto& G : c->sweeps[2][1]) zshape0.push_back(G.W3);
+    if (int rc0 = set_xy_s(c, 0)) return cleanup(rc0);
     for (int stage = 0; stage < 2; stage++) {
         if (stage == 1) {
             // intermediates the corrector sweeps read: Step-1 fluxes, edges, b^{n+1/2}
@@ -1984,11 +1983,10 @@ int autotune_t(wmb_ctx* c, int reps) {
             for (int d = 0; d < 3 && e == hipSuccess; d++)
                 for (auto& G : c->sweeps[d][0])
                     if (e == hipSuccess)
-                        e = launch_group<R>(c, d, 1, G, sh ? G.wls : G.wl, c->cur, c->d_nfloor + COUNTERS + COUNT_PAD, c->stream, sh);
-            const DevList& lc = sh ? c->wl_cth_s : c->wl_cth;
+                        e = launch_group<R>(c, d, 1, G, G.wls, c->cur, c->d_nfloor + COUNTERS + COUNT_PAD, c->stream, true);
             if (e == hipSuccess)
-                e = launch_ct_half<R>(c->pool, c->d_patch, lc.d, lc.n, coef<R>(c), c->p.ghost, c->cur, c->d_sc, sa,
-                                      c->stream);
+                e = launch_ct_half<R>(c->pool, c->d_patch, c->wl_cth_s.d, c->wl_cth_s.n, coef<R>(c), c->p.ghost, c->cur,
+                                      c->d_sc, sa, c->stream);
             if (e != hipSuccess) return cleanup(fail(c, WMB_EHIP, std::string("autotune: ") + hipGetErrorString(e)));
         }
         for (int d = 0; d < 3; d++) {
@@ -2004,17 +2002,17 @@ int autotune_t(wmb_ctx* c, int reps) {
                 else
                     for (int W : opts_t) cand.push_back(W);
                 // and the shape it has: tuning is not to end slower than none
-                if (std::find(cand.begin(), cand.end(), shape(G)) == cand.end()) cand.push_back(shape(G));
+                if (std::find(cand.begin(), cand.end(), G.Ws) == cand.end()) cand.push_back(G.Ws);
                 float best = 1e30f, bestp = 1e30f, bestm = 1e30f;
-                int bestW = shape(G);
+                int bestW = G.Ws;
                 G.Wp = G.Wm = 0;
-                const int P = sh ? G.Ps() : G.P;
+                const int P = G.Ps();
                 std::vector<std::pair<float, int>> timed;  // (ms, shape) of every candidate
                 for (int W : cand) {
                     if (!shape_ok(d, G.P, es, W, stage + 1) || (W > 0 && P * W < 64)) continue;
-                    if (sh && stage == 1 && W < 0) continue;  // the corrector from q^n: pencil form
-                    std::vector<WorkItem> items = sweep_items(c, d, G.n, G.tlo, G.thi, W < 0 ? (-W) % 512 : W, part, -1,
-                                                              nullptr, sh);
+                    if (stage == 1 && W < 0) continue;  // the corrector from q^n: pencil form
+                    std::vector<WorkItem> items = sweep_items(c, d, G.n, G.tlo, G.thi, W < 0 ? (-W) % 512 : W,
+                                                              PART_INTERIOR, -1, nullptr, true);
                     if (items.empty()) continue;
                     CKT(hipMalloc(&dl, sizeof(WorkItem) * items.size()));
                     CKT(hipMemcpy(dl, items.data(), sizeof(WorkItem) * items.size(), hipMemcpyHostToDevice));
@@ -2023,9 +2021,9 @@ int autotune_t(wmb_ctx* c, int reps) {
                     for (int r = 0; r <= reps && e == hipSuccess; r++) {
                         CKT(hipEventRecord(e0, c->stream));
                         SweepGroup T = G;
-                        T.W = T.Ws = W;
+                        T.Ws = W;
                         e = launch_group<R>(c, d, stage + 1, T, DevList{dl, (int)items.size()}, c->cur, c->d_nfloor + COUNTERS + COUNT_PAD,
-                                            c->stream, sh);
+                                            c->stream, true);
                         CKT(hipEventRecord(e1, c->stream));
                         CKT(hipEventSynchronize(e1));
                         float t = 0.f;
@@ -2047,59 +2045,39 @@ int autotune_t(wmb_ctx* c, int reps) {
                 std::sort(timed.begin(), timed.end());
                 G.Wx[0] = timed.size() > 1 ? timed[1].second : 0;
                 G.Wx[1] = timed.size() > 2 ? timed[2].second : 0;
-                if (bestW != shape(G)) {
+                if (bestW != G.Ws) {
                     int rc2 = set_shape(d, stage, G, bestW);
                     if (rc2) return cleanup(rc2);
                 }
             }
         }
     }
-    // The graph runs the three sweeps of a stage concurrently, so the shapes
-    // that are fastest alone need not be the fastest together: time whole
-    // steps replayed from a captured graph for the shapes picked alone, then,
+    // The shapes that are fastest alone need not be the fastest in a step: time
+    // whole steps for the shapes picked alone, then,
     // stage by stage, for each x group its second and third shapes alone,
     // then for the best pencil shapes and for the best marching shapes of
     // the y and z groups, keeping the fastest each time.  time_stage: a
-    // whole step as wmb_run_steps runs it (captured and replayed as a graph,
-    // the sweeps of a stage as branches; a shared-halo step, one chain either
-    // way, launched kernel by kernel), its results going nowhere the
+    // whole step launched kernel by kernel, its results going nowhere the
     // next step reads: the update writes the other state copy, floors,
     // protected faces and the signal-speed maximum go to the sinks, and the
     // current copy and the flags are restored
     auto time_stage = [&](float* ms) -> int {
         unsigned long long *smax0 = c->d_smax, *nfl0 = c->d_nfloor;
         const int cur0 = c->cur, ss0 = c->smax_state;
-        const bool xg0 = c->xg_valid, ek0 = c->edges_kept, xl0 = c->xg_lazy, sg0 = c->stages_shared;
+        const bool xg0 = c->xg_valid, ek0 = c->edges_kept, xl0 = c->xg_lazy;
         c->d_smax = smax0 + 2;
         c->d_nfloor = nfl0 + COUNTERS;
-        hipGraph_t gr = nullptr;
-        hipGraphExec_t ge = nullptr;
         int rc4 = WMB_OK;
         hipError_t e = hipSuccess;
         float tot = 1e30f;
-        auto restore = [&]() {
+        for (int r = 0; r <= reps && !rc4 && e == hipSuccess; r++) {
+            e = hipEventRecord(e0, c->stream);
+            if (e == hipSuccess) rc4 = run_step<R>(c);
             c->cur = cur0;
             c->smax_state = ss0;
             c->xg_valid = xg0;
             c->edges_kept = ek0;
             c->xg_lazy = xl0;
-            c->stages_shared = sg0;
-        };
-        if (!sh) {
-            e = hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed);
-            if (e == hipSuccess) {
-                e = hipEventRecord(c->ev_join, c->stream);  // the exchange is done
-                if (e == hipSuccess) rc4 = run_step<R>(c, true);
-                hipError_t e2 = hipStreamEndCapture(c->stream, &gr);
-                if (e == hipSuccess) e = e2;
-            }
-            restore();
-            if (!rc4 && e == hipSuccess) e = hipGraphInstantiate(&ge, gr, nullptr, nullptr, 0);
-        }
-        for (int r = 0; r <= reps && !rc4 && e == hipSuccess; r++) {
-            e = hipEventRecord(e0, c->stream);
-            if (e == hipSuccess && !sh) e = hipGraphLaunch(ge, c->stream);
-            if (e == hipSuccess && sh) rc4 = run_step<R>(c), restore();
             if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
             if (e == hipSuccess) e = hipEventSynchronize(e1);
             float t = 0.f;
@@ -2108,11 +2086,6 @@ int autotune_t(wmb_ctx* c, int reps) {
         }
         c->d_smax = smax0;
         c->d_nfloor = nfl0;
-        // a graph executable is destroyed only on an idle device (ROCm 7
-        // otherwise keeps the memory its kernels used from being freed)
-        if (!sh) (void)hipDeviceSynchronize();
-        if (ge) (void)hipGraphExecDestroy(ge);
-        if (gr) (void)hipGraphDestroy(gr);
         if (rc4) return cleanup(rc4);
         if (e != hipSuccess) return cleanup(fail(c, WMB_EHIP, std::string("autotune: ") + hipGetErrorString(e)));
         *ms = tot;
@@ -2125,7 +2098,7 @@ int autotune_t(wmb_ctx* c, int reps) {
         // the x sweeps: the second and third shapes alone, one group at a time
         for (auto& G : c->sweeps[0][stage])
             for (int a = 0; a < 2; a++) {
-                const int W0 = shape(G), W1 = G.Wx[a];
+                const int W0 = G.Ws, W1 = G.Wx[a];
                 if (W1 == 0 || W1 == W0) continue;
                 if ((rc2 = set_shape(0, stage, G, W1))) return cleanup(rc2);
                 float t = 0.f;
@@ -2138,7 +2111,7 @@ int autotune_t(wmb_ctx* c, int reps) {
             }
         std::vector<int> alone;
         for (int d = 1; d < 3; d++)
-            for (auto& G : c->sweeps[d][stage]) alone.push_back(shape(G));
+            for (auto& G : c->sweeps[d][stage]) alone.push_back(G.Ws);
         int choice = 0;  // 0: alone, 1: all pencil, 2: all marching
         for (int alt = 1; alt <= 2; alt++) {
             bool differs = false, valid = true;
@@ -2146,7 +2119,7 @@ int autotune_t(wmb_ctx* c, int reps) {
                 for (auto& G : c->sweeps[d][stage]) {
                     const int W = alt == 1 ? G.Wp : G.Wm;
                     valid = valid && W != 0;
-                    differs = differs || W != shape(G);
+                    differs = differs || W != G.Ws;
                 }
             if (!valid || !differs) continue;
             for (int d = 1; d < 3 && !rc2; d++)
@@ -2183,21 +2156,21 @@ int autotune_t(wmb_ctx* c, int reps) {
         if (rc2) return rc2;
         int best_rb = 0;
         std::vector<int> zw, best_zw;
-        for (auto& G : c->sweeps[2][1]) zw.push_back(zshape(G));
+        for (auto& G : c->sweeps[2][1]) zw.push_back(G.W3);
         best_zw = zw;
         std::vector<int> bands{4, 6, 8, 9, 11, 13, 16, 18};
         if (rows0 > 0 && std::find(bands.begin(), bands.end(), rows0) == bands.end()) bands.push_back(rows0);
         for (int rb : bands) {
             if (!xy_ok(c, rb)) continue;
-            if ((rc2 = set_rows(rb))) return cleanup(rc2);
+            if ((rc2 = set_xy_s(c, rb))) return cleanup(rc2);
             for (int W : {-256, -64, 16, 0}) {
                 if (W == 0 && rb != rows0) continue;
                 std::vector<int> cur_zw;
                 size_t i = 0;
                 for (auto& G : c->sweeps[2][1]) {
                     const int own = zshape0[i++];
-                    const int w = W == 0 ? own : (shape_ok(2, G.P, es, W, 2) ? W : zshape(G));
-                    if (w != zshape(G) && (rc2 = set_zshape(G, w))) return cleanup(rc2);
+                    const int w = W == 0 ? own : (shape_ok(2, G.P, es, W, 2) ? W : G.W3);
+                    if (w != G.W3 && (rc2 = set_zshape(G, w))) return cleanup(rc2);
                     cur_zw.push_back(w);
                 }
                 float t = 0.f;
@@ -2205,11 +2178,11 @@ int autotune_t(wmb_ctx* c, int reps) {
                 if (t < best) best = t, best_rb = rb, best_zw = cur_zw;
             }
         }
-        if ((rc2 = set_rows(best_rb))) return cleanup(rc2);
+        if ((rc2 = set_xy_s(c, best_rb))) return cleanup(rc2);
         size_t i = 0;
         for (auto& G : c->sweeps[2][1]) {
             const int w = best_zw[i++];
-            if (w != zshape(G) && (rc2 = set_zshape(G, w))) return cleanup(rc2);
+            if (w != G.W3 && (rc2 = set_zshape(G, w))) return cleanup(rc2);
         }
     }
     // The tiles of Steps 3-4 (widest tile along x) and of Steps 8-11 (zones
@@ -2223,7 +2196,7 @@ int autotune_t(wmb_ctx* c, int reps) {
         auto time_tiles = [&](int kind, int v, float* ms) -> int {
             DevList L;
             // kind 0: Steps 3-4; 1: Steps 8-11, one block a tile; 2: the same on the queues
-            int rc3 = kind == 0 ? build_cth_list(c, v, L, -1, sh) : build_upd_list(c, v, &rows, L, -1, sh);
+            int rc3 = kind == 0 ? build_cth_list(c, v, L, -1, true) : build_upd_list(c, v, &rows, L, -1, true);
             if (rc3) return cleanup(rc3);
             tl = L.d;  // released by cleanup on an error exit
             hipError_t e = hipSuccess;
@@ -2234,7 +2207,7 @@ int autotune_t(wmb_ctx* c, int reps) {
                                                   sa, c->stream)
                               : launch_update<R>(c->pool, c->d_patch, L.d, L.n, c->dp, coef<R>(c), c->cur, c->d_sc,
                                                  c->d_nfloor + COUNTERS, c->d_smax + 2, 0, v, kind == 2 ? c->d_queue : nullptr,
-                                                 sa, zrec(c, sh) ? F_FL1 + 14 : F_FL2 + 14, c->d_sc + 1, c->stream);
+                                                 sa, zrec(c, true) ? F_FL1 + 14 : F_FL2 + 14, c->d_sc + 1, c->stream);
                 CKT(hipEventRecord(e1, c->stream));
                 CKT(hipEventSynchronize(e1));
                 float t = 0.f;
@@ -2748,20 +2721,14 @@ int wmb_autotune(wmb_ctx* c, int32_t reps, int32_t* chosen, int32_t nchosen) {
         for (const auto& kv : tune_cache)
             if (kv.first == key) q = kv.second;
     }
-    if (shared_now(c) && c->esize == 8) {
-        // Shared-halo steps in FP64 keep the shapes their rules choose: timing
-        // them gained 2% at 512 x 32^3 (9.17 -> 8.97 ms a step).  Two of nine
-        // processes that timed them there ended in a segmentation fault of the
-        // host between this call and the context's end; its cause is not known
-        // (the library's host code is clean under the address sanitizer).
-        q = tuning_quads(c);
+    if (!shared_now(c) || c->esize != 4) {
+        q = tuning_quads(c);  // nothing is timed (autotune_shared): the shapes the batch has
     } else if (!q.empty()) {
-        const bool sh = shared_now(c);
-        int rc = apply_tuning(c, q.data(), (int32_t)q.size(), !sh, sh);
+        int rc = apply_tuning(c, q.data(), (int32_t)q.size(), false, true);
         if (rc) return rc;
     } else {
         int r = reps < 0 ? -reps : reps;
-        int rc = c->esize == 4 ? autotune_t<float>(c, r < 1 ? 1 : r) : autotune_t<double>(c, r < 1 ? 1 : r);
+        int rc = autotune_shared(c, r < 1 ? 1 : r);
         if (rc) return rc;
         q = tuning_quads(c);
         std::lock_guard<std::mutex> lk(tune_mu);

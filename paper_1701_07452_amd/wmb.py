@@ -272,7 +272,8 @@ class Sim:
 
     def autotune(self, reps=3):
         """Pick the sweep block shapes, the fused corrector's band rows and the Steps 3-4 / 8-11
-        tiles by timing (or from the per-process cache; reps < 0 forces timing); returns
+        tiles of FP32 shared-halo steps by timing (or from the per-process cache; reps < 0 forces
+        timing); other batches keep the shapes they have.  Returns
         {(stage, axis, edge): shape}, with (3, 0, 0) the Steps 3-4 tile width, (4, 0, 0) the
         Steps 8-11 tile zones, (5, 0, 0) their launch form and (6, 0, 0) the fused corrector's
         band rows (0: three separate corrector sweeps)."""

@@ -200,21 +200,19 @@ def test_band_rows_set_are_the_ones_that_run(wmb):
 
 
 def test_autotune_keeps_the_other_scheme(wmb):
-    """Shapes timed in the halo scheme (a patch frozen) are not forced on the
-    shared-halo steps, whose sweeps and band rows stay what they were (the tiles
-    of Steps 3-4 and 8-11 are common to both)."""
-    G, sim = _sim(wmb, "whole_lines", 0, True)
+    """Shapes timed for shared-halo steps (FP32) are not forced on the halo
+    scheme, which wmb_autotune does not time (the tiles of Steps 3-4 and 8-11
+    are common to both)."""
+    G, sim = _sim(wmb, "whole_lines", 1, True)
     own = lambda t: {k: v for k, v in t.items() if k[0] in (1, 2, 6)}  # noqa: E731
-    before = own(sim.autotune())
-    sim.set_active(1, False)
-    sim.run_steps(1)
+    sim.keep_stages(True)
+    halo = own(sim.autotune())
+    sim.keep_stages(False)
     timed = own(sim.autotune(-1))
-    sim.set_active(1, True)
-    sim.run_steps(1)
-    assert own(sim.autotune()) == before
-    sim.set_active(1, False)
-    sim.run_steps(1)
-    assert own(sim.autotune()) == timed  # remembered for the halo scheme
+    sim.keep_stages(True)
+    assert own(sim.autotune()) == halo and own(sim.autotune(-1)) == halo
+    sim.keep_stages(False)
+    assert own(sim.autotune()) == timed  # remembered for shared steps
     sim.close()
 
 
@@ -287,12 +285,13 @@ def test_stages_after_freeze(wmb, between, prec):
 
 # what a shared step can be combined with: the Steps 8-11 launch from queues, a
 # dt one step late, other schedules and back, steps launched kernel by kernel
-# (from 2^21 zones on)
+# (from 2^21 zones on), timed shapes (FP32)
 OPTIONS = {
     "queue": ((16, 12, 10), (2, 1, 2), {}, {(5, 0, 0): 1}),
     "dt_lag": ((16, 12, 10), (2, 1, 2), dict(dt_lag=1), None),
     "schedules": ((8, 8, 8), (2, 2, 3), {}, None),
     "launched": ((64, 64, 64), (2, 2, 2), {}, None),
+    "tuned": ((24, 20, 16), (2, 2, 2), {}, None),
 }
 
 
@@ -313,6 +312,8 @@ def test_shared_options(wmb, option, prec):
             sim.keep_stages(True)
         if tun:
             sim.set_tuning(tun)
+        if option == "tuned" and shared:
+            sim.autotune(-1)
         for groups in (1, 3, 1, 2, 4, 1):
             if option == "schedules":
                 sim.set_schedule(groups)
