@@ -5,19 +5,21 @@ Headline workload: 3D periodic 256^3 box as 512 patches of 32^3 (ghost width
 4, the stencil minimum), rho = 1, P = 1, B = (0.1, 0, 0), seeded Gaussian
 random velocity with a k^-5/3 spectrum at rms Mach 1, gamma = 5/3, CFL 0.4.
 One step = ghost exchange + FP64 CFL reduction + the full CTU+CT MHDTVD
-update (Steps 1-11) of all patches, replayed from a captured HIP graph, with
+update (Steps 1-11) of all patches, enqueued by wmb_run_steps (a captured HIP
+graph, or kernel by kernel for large shared-halo batches such as this one), with
 the state resident in HBM.  The headline value is the FP32 batch (FP32 sweeps
 and CT, FP64 dt and floors); the FP64 batch of the same workload is reported
 beside it, and so are the uneven 400-patch batch, the 512^3 Orszag-Tang batch
 (patches of 64^3, 50 steps) and the 768^3 high-contrast batch (patches of
 48^3).
 
-Roofline: the algorithmic bytes of one step are those of the patch design
-(16 + 24 ((1 + 2g/n)^3 - 1) words per interior zone-update for cubic patches
-of edge n: the step reads and writes the 8 conserved words of every interior
-zone, the ghost exchange reads and writes those of every ghost zone, and the
-step reads the ghosts), over the step time measured with HIP events on the
-library's stream around the timed graph replays.
+Roofline: the algorithmic bytes of one step are those of the scheme that runs.
+Shared-halo steps, without ghosts or an exchange, read and write the 11 stored
+words of every zone.  In the halo scheme a step takes 16 + 24 ((1 + 2g/n)^3 - 1)
+words per interior zone-update for cubic patches of edge n: it reads and writes
+the 8 conserved words of every interior zone, the ghost exchange reads and
+writes those of every ghost zone, and the step reads the ghosts.  Over the step
+time measured with HIP events on the library's stream around the timed steps.
 
 Prints ONE JSON line.  --gpus > 1 is not supported (one GPU per process; the
 multi-GPU design is documented, not built).
@@ -48,20 +50,44 @@ def log(*a):
 # algorithmic bytes of one step, and their attribution to the kernel classes
 # ---------------------------------------------------------------------------
 
-def alg_words(descs, g):
-    """Algorithmic words of one step over a batch of patches (8 conserved
-    words per zone; the zone-centred field is carried, the face field is not
-    counted separately), attributed to the kernel class that must move them:
+def shared_halos(descs, g, es, groups=1):
+    """Whether the batch steps with shared halos: equal extents, every
+    neighbour there, no patch groups, the pool within 2^32 words and the nine
+    patches around a patch at each z within 4 GiB."""
+    n = descs[0][0]
+    vol = (n[0] + 2 * g) * (n[1] + 2 * g) * (n[2] + 2 * g)
+    region = sum((w * vol * es + 255) // 256 * 256 for w in (22, 51))
+    if groups > 1 or len(descs) * (region // es) > 0xFFFFFFFF:
+        return False
+    if any(tuple(m) != tuple(n) or min(nbr) < 0 for m, nbr in descs):
+        return False
+    if (n[0] * n[1] * n[2] + 31) // 32 * 32 + 96 > vol:
+        return False
+    return all((max(nbr[9 * z:9 * z + 9]) - min(nbr[9 * z:9 * z + 9]) + 1) * region <= 0xFFFFFFFF
+               for _, nbr in descs for z in range(3))
+
+
+def alg_words(descs, g, shared):
+    """Algorithmic words of one step over a batch of patches, attributed to
+    the kernel class that must move them.  Shared-halo steps: the 11 stored
+    words of every zone, read by the three Step-1 sweeps (a third each) and
+    written by the update.  Halo scheme (8 conserved words per zone; the
+    zone-centred field is carried, the face field is not counted separately):
       - the ghost exchange reads and writes 8 words of every ghost zone: the
         x-ghosts of interior rows are written by the update kernel (its push
         to the x-neighbours), the other ghosts by the y/z exchange passes;
       - the step reads q^n over the whole stored box (interior and ghosts):
         charged to the three Step-1 sweeps, a third each;
       - the step writes q^{n+1} over the interior: charged to the update.
-    The total is 16 V_int + 24 (V_stored - V_int) per patch."""
+    The total is 22 V_int, or 16 V_int + 24 (V_stored - V_int), per patch."""
     w = {"fill": 0, "sweep1_x": 0, "sweep1_y": 0, "sweep1_z": 0, "update": 0}
     for n, _ in descs:
         vi = n[0] * n[1] * n[2]
+        if shared:
+            w["update"] += 11 * vi
+            for k in ("sweep1_x", "sweep1_y", "sweep1_z"):
+                w[k] += 11 * vi / 3.0
+            continue
         vs = (n[0] + 2 * g) * (n[1] + 2 * g) * (n[2] + 2 * g)
         gx = 2 * g * n[1] * n[2]
         w["update"] += 16 * gx + 8 * vi
@@ -83,12 +109,13 @@ def profile_record():
     return rec if rec.get("kernels_source_sha256") == cur else None
 
 
-def roofline(descs, g, es, zones, ms_step, kern_ms, prof=None):
+def roofline(descs, g, es, zones, ms_step, kern_ms, prof=None, groups=1):
     """Step-level HBM roofline at the algorithmic bytes, with per-kernel
     shares (each kernel's algorithmic bytes over the step time; the shares sum
     to the step fraction) and the measured traffic and VALU utilisation from
     the committed counter summary when it is current."""
-    words = alg_words(descs, g)
+    shared = shared_halos(descs, g, es, groups)
+    words = alg_words(descs, g, shared)
     step_bytes = sum(words.values()) * es
     t = ms_step * 1e-3
     achieved = step_bytes / t / 1e9
@@ -106,7 +133,7 @@ def roofline(descs, g, es, zones, ms_step, kern_ms, prof=None):
         traffic = sum(v.get("fetch_bytes", 0) + v.get("write_bytes", 0) for v in prof["per_class"].values())
     dom = max(kern_ms, key=kern_ms.get) if kern_ms else None
     return {
-        "kernel": "step (one graph replay: exchange, dt, Steps 1-11 of every patch)",
+        "kernel": "step (%sdt, Steps 1-11 of every patch)" % ("shared halos: " if shared else "exchange, "),
         "bound": "hbm",
         "achieved": round(achieved, 2),
         "peak": HBM_PEAK_GBS,
@@ -126,8 +153,8 @@ def roofline(descs, g, es, zones, ms_step, kern_ms, prof=None):
 # rocprofv3 counter summary (written into profiles/, read back by roofline())
 # ---------------------------------------------------------------------------
 
-TUNING32_PROF = "1x32=12,1y32=16,1z32=16,2x32=2,2y32=16,2z32=-256,6x0=9"
-TUNING64_PROF = "1x32=6,1y32=-256,1z32=-256,2x32=3,2y32=-64,2z32=-64,6x0=0"
+TUNING32_PROF = "1x32=7,1y32=-128,1z32=-256,2x32=12,2y32=16,2z32=-256,6x0=11"
+TUNING64_PROF = "1x32=7,1y32=-64,1z32=-64,2x32=7,2y32=13,2z32=-64,6x0=4"
 COUNTER_ARGS = ("--steps 2 --warmup 1 --prof-steps 0 --no-fp64 --no-cpu-baseline --schedule 1 --calib-copy "
                 "--tuning32 " + TUNING32_PROF)
 SQ_COUNTERS = "SQ_WAVES SQ_INSTS_VALU SQ_ACTIVE_INST_VALU SQ_WAVE_CYCLES SQ_BUSY_CYCLES GRBM_GUI_ACTIVE"
@@ -292,8 +319,8 @@ def summarize_counters(root):
     md.append("| **whole step** | %.3f | %.3f | %.3f | %.2f | | |" % (tot_f / 1e9, tot_w / 1e9, tot_ms,
                                                                        (tot_f + tot_w) / (tot_ms * 1e9)))
     md += ["", "The step moves %.2f GB of measured traffic in %.3f ms of serialised kernel time (%.2f TB/s); "
-           "its algorithmic bytes are 2.609 GB (155.5 B per zone-update)." % ((tot_f + tot_w) / 1e9, tot_ms,
-                                                                             (tot_f + tot_w) / (tot_ms * 1e9))]
+           "its algorithmic bytes are 1.476 GB (22 words, 88 B, per zone-update: shared halos)." % (
+               (tot_f + tot_w) / 1e9, tot_ms, (tot_f + tot_w) / (tot_ms * 1e9))]
     base = PROFILE_JSON[:-len(".json")]
     with open(base + ".md", "w") as fh:
         fh.write("\n".join(md) + "\n")
@@ -316,13 +343,11 @@ def summarize_trace(root, sha):
           "Command (TMPDIR=/tmp, run from /tmp; `<repo>` is the repository root):", "```",
           "rocprofv3 --kernel-trace --stats --output-format csv -d <out>/trace -o run -- \\",
           "  python3 <repo>/bench.py " + TRACE_ARGS, "```",
-          "Kernel source sha256 %s. Per precision the run does 1 warm-up step, 5 graph-replayed timed steps "
+          "Kernel source sha256 %s. Per precision the run does 1 warm-up step, 5 timed steps "
           "and 3 eager profiled steps (`wmb_profile_step`: the same launches, one kernel at a time), plus "
-          "set-up and diagnostics kernels. `Avg` is rocprofv3's `AverageNs` over all calls: in the replayed "
-          "steps the three sweeps of a stage run concurrently and share the GPU, so their average lies above "
-          "the one-at-a-time time. `Eager` is the mean of each kernel's last 3 dispatches (the profiled "
+          "set-up and diagnostics kernels. `Avg` is rocprofv3's `AverageNs` over all calls. `Eager` is the mean of each kernel's last 3 dispatches (the profiled "
           "steps). The last column is `bench.py`'s own HIP-event time for the kernel class in the same run "
-          "(`kernels_ms`; FP32 `%s` ms/step, FP64 `%s` ms/step in the graph)." % (
+          "(`kernels_ms`; FP32 `%s` ms/step, FP64 `%s` ms/step timed)." % (
               sha[:16], "%.3f" % bench["ms_per_step"], "%.3f" % bench["fp64"]["ms_per_step"]), "",
           "| Kernel | Calls | Avg (ms) | Min (ms) | Max (ms) | Eager (ms) | bench.py HIP-event (ms) |",
           "|---|---:|---:|---:|---:|---:|---:|"]
@@ -457,7 +482,7 @@ SCHEDULE = 0  # captured-step schedule: 0 picks 1, 2 or 3 patch groups by timing
 
 
 def pick_schedule(sim, stream, reps=3):
-    """Time `reps` graph replays under 1, 2 and 3 patch groups (warm-up steps:
+    """Time `reps` steps under 1, 2 and 3 patch groups (warm-up steps:
     the state advances) and keep the fastest; returns {groups: ms per step}."""
     import torch
 
@@ -477,7 +502,7 @@ def pick_schedule(sim, stream, reps=3):
 
 
 def run_batch(W, G, q, b, dx, prec, ghost, steps, warmup, prof_steps, tuning=None, freeze=(), divb_at=(), **params):
-    """Time `steps` graph replays after `warmup` ones; per-kernel eager
+    """Time `steps` steps after `warmup` ones; per-kernel eager
     durations from prof_steps profiled steps; optionally the normalised div b
     of a fresh run after each step count in divb_at."""
     import torch
@@ -582,7 +607,8 @@ def main():
     ap.add_argument("--patch-sweep", action="store_true",
                     help="also time the FP32 turbulence box cut into patches of 16, 24, 32, 48 and 64 zones an edge")
     ap.add_argument("--schedule", type=int, default=0,
-                    help="captured-step schedule: 1 (concurrent sweep branches), 2 or 3 patch groups; 0 picks by timing")
+                    help="step schedule: 1 (shared halos where the batch can, else concurrent sweep branches), 2 or 3 patch "
+                         "groups; 0 picks by timing")
     ap.add_argument("--calib-copy", action="store_true",
                     help="run one 1 GiB device-to-device copy first (reference for HBM byte counters)")
     ap.add_argument("--summarize-counters", metavar="DIR", default="",
@@ -639,7 +665,7 @@ def main():
         fp64 = {"value": zones * args.steps / (ms64 / 1e3), "ms_per_step": ms64 / args.steps, "dtype": "f64",
                 "kernels_ms": kern64, **diag64}
         if kern64:
-            fp64["roofline"] = roofline(G.descs, g, 8, zones, ms64 / args.steps, kern64)
+            fp64["roofline"] = roofline(G.descs, g, 8, zones, ms64 / args.steps, kern64, groups=diag64["schedule_groups"])
         log("bench: FP64 %.3f ms/step" % (ms64 / args.steps))
 
     uneven = None
@@ -657,7 +683,7 @@ def main():
                               "turbulence, ghost %d, FP32" % g,
                   "zones": Gu.zones(), "patches": Gu.npatch, "ms_per_step": msu / args.steps,
                   "value": Gu.zones() * args.steps / (msu / 1e3), "kernels_ms": kernu, **diagu,
-                  "roofline": roofline(Gu.descs, g, 4, Gu.zones(), msu / args.steps, kernu)}
+                  "roofline": roofline(Gu.descs, g, 4, Gu.zones(), msu / args.steps, kernu, groups=diagu["schedule_groups"])}
         log("bench: uneven FP32 %.3f ms/step, %.3e zone-updates/s" % (msu / args.steps, uneven["value"]))
 
     shared = None
@@ -684,7 +710,7 @@ def main():
         ms4, _, kern4, diag4 = run_batch(W, G4, q4, b4, (1.0 / N4,) * 3, W.WMB_FP32, g, s4, args.warmup, 1,
                                          divb_at=(10, 20, 50))
         del q4, b4
-        c4 = {"workload": "3D Orszag-Tang extension, 512^3 as 512 patches of 64^3, ghost %d, FP32, %d graph-replayed "
+        c4 = {"workload": "3D Orszag-Tang extension, 512^3 as 512 patches of 64^3, ghost %d, FP32, %d "
                           "steps" % (g, s4),
               "zones": G4.zones(), "patches": G4.npatch, "steps": s4, "ms_per_step": ms4 / s4,
               "value": G4.zones() * s4 / (ms4 / 1e3), "kernels_ms": kern4, **diag4,
@@ -790,7 +816,7 @@ def main():
     if not kern32:  # counter-collection runs skip the per-kernel pass
         print(json.dumps({"metric": METRIC, "value": value, "unit": "zone-updates/s", "partial": True}), flush=True)
         return
-    roof = roofline(G.descs, g, 4, zones, ms32 / args.steps, kern32, prof)
+    roof = roofline(G.descs, g, 4, zones, ms32 / args.steps, kern32, prof, groups=diag32["schedule_groups"])
     if prof:
         roof["valu_busy_sweeps"] = {k: v.get("valu_busy") for k, v in prof["per_class"].items() if k.startswith("sweep")}
         roof["profile"] = os.path.relpath(PROFILE_JSON, ROOT)
