@@ -38,21 +38,21 @@ namespace wmb {
 // Reciprocal and roots: hardware v_rcp_f32 / v_sqrt_f32 (about 1 ulp) in the
 // FP32 path.  In FP64 the hardware estimate (5.6e-8) and one correction of
 // third order (the root: of second order and a residual), 5 and 8 instructions
-// for the 11 and 17 of the operators.  Measured over all operands: the
-// reciprocal rounds as the operator does (0, infinities and NaN by the fix-up;
-// only below 2^-1024, where the operator overflows, it is NaN), the root of a
-// normal number to within a unit in the last place.  The root of a subnormal x
-// has a residual rounded to 2^-1074, so its error is up to that of x being
-// rounded by half of that.  It has to be that good: frsq of the transverse
+// for the 11 and 17 of the operators.  Measured over operands of all exponents:
+// the reciprocal is the operator's (0, infinities and NaN by the fix-up), the
+// root of a normal number within a unit in the last place of it.  The root of a
+// subnormal x has a residual rounded to 2^-1074, so its error is up to that of x
+// being rounded by half of that.  It has to be that good: frsq of the transverse
 // field's square makes a unit vector, so a root that is short by a factor,
 // however small itself, makes Alfven and slow waves that are too strong by its
-// square (clamped at 2^-1022, fields of 1e-157 blew a sheared flow up).
+// square (clamped at 2^-1022, fields of 1e-157 blew a sheared flow up).  The root
+// of infinity is NaN, where the operator's infinity made a NaN a line later.
 // (The reciprocal root as their composition too, and the limiter's quotient with
 // a residual: forms of fewer instructions, as accurate against 64-bit
 // references, move the last bit, which the low-beta blast multiplies by 1e12.)
-// With the branch of each_wave, at 512 x 32^3: Step-1 sweeps 0.81 / 0.81 / 0.83
-// -> 0.73 / 0.59 / 0.70 ms, the fused corrector 2.88 -> 2.62, a step 9.17 ->
-// 8.53.
+// With the branch of each_wave and the swizzled records, at 512 x 32^3: Step-1
+// sweeps 0.81 / 0.81 / 0.83 -> 0.74 / 0.57 / 0.60 ms, the fused corrector 2.88
+// -> 2.67, a step 9.17 -> 8.31.
 __device__ __forceinline__ float frcp(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ __forceinline__ double frcp(double x) {
     const double y = __builtin_amdgcn_rcp(x), e = __builtin_fma(-x, y, 1.0);

@@ -2526,7 +2526,8 @@ int wmb_init_patches(wmb_ctx* c, int32_t npatch, const wmb_patch_desc* d, void* 
     c->nfrozen = 0;
     if ((rc = build_sweeps(c))) return rc;
     // the fused corrector in FP32, and in FP64 shared-halo steps (512 x 32^3,
-    // bands of 4 rows: 3.62 against 3.88 ms for the three sweeps).  The halo
+    // bands of 4 rows: 8.31 ms a step against 8.82 with the three sweeps; 64 x
+    // 48^3, 6 rows, would be faster with the sweeps, 3.94 against 4.29).  The halo
     // scheme in FP64 keeps the sweeps; whole steps with one patch frozen,
     // sweeps / the best bands, ms: 27 x 48^3 2.05 / 2.14, 64 x 64^3 10.67 /
     // 10.99, 64 x 32^3 1.66 / 1.64, 512 x 32^3 12.72 / 12.62
