@@ -67,12 +67,14 @@ __device__ __forceinline__ double fsqrt(double x) {
 }
 __device__ __forceinline__ float frsq(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double frsq(double x) { return frcp(fsqrt(x)); }
-// smallest |alpha| divided by in the limiter's gamma (keeps the reciprocal away
-// from overflow).  Both limiter values are bounded by the face's own g-tilde,
-// so |dg| by a multiple of |alpha|: below, what gamma adds to the flux is below
-// it too
+// |alpha| above which the limiter's gamma divides by it (keeps the reciprocal
+// away from overflow; in FP64 the smallest normal number, so that a wave of any
+// strength above it is limited as a strong one is: with 2^-960, fields weaker
+// than that were off by a third of themselves).  Both limiter values are bounded by the face's own
+// g-tilde, so |dg| by a multiple of |alpha|: below, what gamma adds to the flux
+// is below it too
 __device__ __forceinline__ float alpha_min(float) { return 1e-30f; }
-__device__ __forceinline__ double alpha_min(double) { return 0x1p-960; }
+__device__ __forceinline__ double alpha_min(double) { return 0x1p-1022; }
 // the limiter's gamma = dg / alpha
 __device__ __forceinline__ float gdiv(float dg, float alpha) { return dg * frcp(alpha); }
 __device__ __forceinline__ double gdiv(double dg, double alpha) {

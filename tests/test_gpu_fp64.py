@@ -95,3 +95,28 @@ def test_vanishing_field(wmb, field, walls):
     assert np.isfinite(qg).all() and np.isfinite(bg).all()
     sim.close()
     orc.close()
+
+
+@pytest.mark.parametrize("tiny", [1e-200, 1e-288, 1e-292, 1e-300])
+def test_weak_waves_are_limited_alike(wmb, tiny):
+    """The tube of test_vanishing_waves, four steps: m_z and B_z, whose waves
+    have the strength `tiny`, within 1e-11 of `tiny` of the oracle's, as fields
+    of any size are of their scale."""
+    G = I.patch_grid([16, 16], [8], [8])
+    q, b = I.shock_tube_x(G.shape, gamma=5 / 3, left=(1.0, 0.0, 0.0, 0.0, 0.5, 0.0, 1.0),
+                          right=(0.2, 0.0, 0.0, 0.0, -0.5, 0.0, 0.1), bx=0.75)
+    x = np.sin(2 * np.pi * (np.arange(G.shape[2]) + 0.5) / G.shape[2])
+    q, b = q.copy(), b.copy()
+    q[3] += tiny * x
+    q[6] += tiny * x[::-1]
+    b[2] += tiny * x[::-1]
+    kw = dict(dx=(1 / 32,) * 3)
+    sim = gpu_sim(wmb, G, q, b, 0, **kw)
+    orc = oracle_sim(G, q, b, **kw)
+    _lockstep(sim, orc, 4)
+    qg, bg = I.gather(G, [sim.get_state(i) for i in range(G.npatch)])
+    qo, bo = oracle_gather(G, orc)
+    for g, o in ((qg[3], qo[3]), (qg[6], qo[6]), (bg[2], bo[2])):
+        assert np.abs(g - o).max() <= 1e-11 * tiny
+    sim.close()
+    orc.close()
