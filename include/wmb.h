@@ -221,7 +221,8 @@ int wmb_diagnostics_noalloc(wmb_ctx *c, double *dev_out);
    (3 x 8 x vol, lab component order, B_par row 0), 3 b^{n+1/2} (3 x vol),
    5 Step-6/7 fluxes (3 x 8 x vol), 6 Step-9 edge EMFs (3 x vol; only after
    a step run with wmb_keep_stages on, else WMB_ESTATE).  Values outside the
-   ranges the step needs are unspecified; with scratch groups only the
+   ranges the step needs are unspecified, and so are the intermediates of a patch
+   that took no part in it (frozen or absent before it); with scratch groups only the
    patches of the last group hold their own.  After a shared-halo step the
    ranges of the ghosts are formed again first, from the step's start.  Other stages (the Step-3 edges are
    overwritten by Step 9) give WMB_EINVAL.  Synchronous. */
